@@ -313,8 +313,9 @@ int npga_solve(const npga_factor *f, double r, const npga_options *opt, float *x
  *   of L is split exactly into three bfloat16 planes (24 significant bits)
  *   and the six plane products of weight >= 2^-24 are accumulated in float32
  *   (float64 every 256 periods), which matches the float32 product to its
- *   rounding.  ws (device, 256-byte aligned) holds the planes:
- *   npga_syrk_split_workspace_size(n, T) bytes (3 n ceil64(T) bfloat16).
+ *   rounding.  ws (device, 256-byte aligned):
+ *   npga_syrk_split_workspace_size(n, T) bytes, which hold the planes (3
+ *   ceil128(n) ceil64(T) bfloat16) and up to 96 MiB of float64 partial tiles.
  *   L 16-byte aligned, ld % 4 == 0.  The solve's covariance path uses it.
  *   NPGA_ERR_WORKSPACE if ws is missing or small.
  * ------------------------------------------------------------------------- */
@@ -347,7 +348,8 @@ int npga_syrk_split(const float *L, int64_t n, int64_t T, int64_t ld, float *Sig
  *   sigma   device ell float32 output: leading singular values of Y
  *   gamma_out (host) receives gamma
  *   ws      npga_sketch_workspace_size(n, T, k, ell) bytes (it includes the
- *           three bfloat16 planes of L and S, 6 (n + k) ceil64(T) bytes)
+ *           three bfloat16 planes of L and S, 6 (ceil128(n) + ceil128(k))
+ *           ceil64(T) bytes, and up to 96 MiB of partial tiles)
  * Requires 1 <= ell <= k <= 8192.  Y = L S runs on the bfloat16 matrix
  * cores with three-plane operands (the six plane products of weight
  * >= 2^-24 per entry product; float32 accumulation, float64 every 256

@@ -175,8 +175,12 @@ constexpr size_t kAutoSyrkMaxBytes = (size_t)4 << 30;
 int resolve_path(int requested, int64_t n, int64_t cols, int dtype = NPGA_F32) {
   if (requested == NPGA_PATH_GEMV || requested == NPGA_PATH_SYRK) return requested;
   if (dtype != NPGA_F32 || cols < n) return NPGA_PATH_GEMV;
+  // (the planes counted without the padding of their storage to whole
+  // 128-row panels and without the split tiles' partial sums)
   const SolveLayout l = npga::solve_layout(n, cols, NPGA_PATH_SYRK);
-  return l.total <= kAutoSyrkMaxBytes ? NPGA_PATH_SYRK : NPGA_PATH_GEMV;
+  const size_t planes = (size_t)3 * (size_t)n * (size_t)((cols + 63) / 64 * 64) * sizeof(uint16_t);
+  const size_t need = l.total - align_up(npga::syrk_split_bytes(n, cols), 256) + align_up(planes, 256);
+  return need <= kAutoSyrkMaxBytes ? NPGA_PATH_SYRK : NPGA_PATH_GEMV;
 }
 
 bool options_valid(const npga_options &o) {

@@ -19,6 +19,7 @@
 
 #include <algorithm>
 #include <cstdint>
+#include <type_traits>
 
 #include "npga_device.h"
 #include "npga_internal.h"
@@ -163,19 +164,35 @@ __global__ __launch_bounds__(512) void k_syrk(const float *__restrict__ L, int64
 // every 256 periods like the float32 kernel.  Six bfloat16 products run at
 // 2.5 PFLOP/s against one float32 product at 157 TFLOP/s.
 //
-// k_split_t: L (float32, column-major, ld) -> three planes stored
-//   row-major, P_pl[i ldt + t], with zeros for t in [T, ldt); one 64 x 64
-//   tile per workgroup, transposed through LDS.
-// k_mm16<true>: 128 x 128 tiles of the lower triangle, eight wavefronts of
-//   32 x 64; 32-period stages of both row panels (three planes each) in LDS,
-//   double buffered; the mirrored tile is written too.  k_mm16<false>: the
-//   same on all tiles of a general product C = A B (the sketch Y = L S).
+// Plane layout.  The planes are stored in the order the matrix instruction
+// reads them: a fragment is 32 rows x 16 periods of one plane, 1 KiB, lane
+// l = 32 h + r of a wavefront holding row r, periods 8 h .. 8 h + 7; a stage
+// is one 16-period step of a 128-row panel, [3 planes][4 row groups] of
+// fragments, 12 KiB in one piece; a panel's stages follow each other.  A
+// stage goes from memory to LDS by global_load_lds (1 KiB per wavefront
+// instruction, lane-linear on both sides) without passing through
+// registers, every fragment is then one ds_read_b128 per lane at 16 lane
+// bytes (no bank conflicts, no padding), and rows past n and periods past T
+// are zeros, so the GEMM has no bounds checks.
+//
+// k_split_t: L (float32, column-major, ld) -> fragments; one 64 x 64 tile
+//   per workgroup, transposed through LDS.
+// k_split_k: the same for a matrix whose rows are contiguous along the
+//   contraction (the sketch).
+// k_mm16<true>: 128 x 128 tiles of the lower triangle; the mirrored tile is
+//   written too.  k_mm16<false>: all tiles of C = A B (the sketch Y = L S).
 // --------------------------------------------------------------------------
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 typedef unsigned int u4v __attribute__((ext_vector_type(4)));
 
 constexpr int kSplitTile = 64;
-constexpr int kLDH = 40;  // LDS row length in bfloat16 (80 bytes, 16-byte aligned)
+constexpr int kMmStep = 16;                  // periods of a stage
+constexpr int kMmGroup = 4;                  // stages per padding unit (64 periods)
+constexpr int kMmFlush = 16;                 // stages between float64 flushes (256 periods)
+constexpr int kFrag = 512;                   // bfloat16 entries of a fragment
+constexpr int kPanelStage = 12 * kFrag;      // [plane][row group] of one panel
+constexpr int kMmRing = 6;                   // stages of both panels in LDS (144 KiB)
+constexpr int kTileElems = kTile * kTile;
 
 __device__ __forceinline__ uint32_t rne_bf16(float f) {  // finite inputs
   const uint32_t u = __float_as_uint(f);
@@ -183,8 +200,33 @@ __device__ __forceinline__ uint32_t rne_bf16(float f) {  // finite inputs
 }
 __device__ __forceinline__ float bf16_f32(uint32_t h) { return __uint_as_float(h << 16); }
 
+// h, m, l words of eight consecutive contraction entries
+__device__ __forceinline__ void split8(const float (&v)[8], u4v (&w)[3]) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    uint32_t h2[2], m2[2], l2[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const float x = v[2 * q + e];
+      h2[e] = rne_bf16(x);
+      const float r1 = x - bf16_f32(h2[e]);
+      m2[e] = rne_bf16(r1);
+      l2[e] = rne_bf16(r1 - bf16_f32(m2[e]));
+    }
+    w[0][q] = h2[0] | (h2[1] << 16);
+    w[1][q] = m2[0] | (m2[1] << 16);
+    w[2][q] = l2[0] | (l2[1] << 16);
+  }
+}
+
+// Fragment (row group g, stage st) of a matrix of `stages` stages: plane 0;
+// plane p follows at 4 p fragments.
+__device__ __forceinline__ uint16_t *frag_ptr(uint16_t *P, int64_t g, int64_t st, int64_t stages) {
+  return P + ((g >> 2) * stages + st) * kPanelStage + (g & 3) * kFrag;
+}
+
 __global__ __launch_bounds__(256) void k_split_t(const float *__restrict__ L, int64_t n, int64_t T, int64_t ld,
-                                                 uint16_t *__restrict__ P, int64_t ldt, int64_t plane) {
+                                                 uint16_t *__restrict__ P, int64_t stages) {
   __shared__ float tile[kSplitTile][kSplitTile + 1];  // [t][i]
   const int tid = threadIdx.x;
   const int64_t t0 = (int64_t)blockIdx.x * kSplitTile, i0 = (int64_t)blockIdx.y * kSplitTile;
@@ -206,32 +248,51 @@ __global__ __launch_bounds__(256) void k_split_t(const float *__restrict__ L, in
     tile[tl][il + 3] = v.w;
   }
   __syncthreads();
-  // row i0 + (tid >> 2), periods t0 + 16 (tid & 3) .. +15: two 8-entry groups per plane
-  const int ir = tid >> 2, ts = 16 * (tid & 3);
-  const int64_t i = i0 + ir;
-  if (i >= n) return;
+  // the tile's eight fragments (2 row groups x 4 stages), two per wavefront,
+  // each plane written as 1 KiB in lane order
+  const int lane = tid & 63, wave = tid >> 6, h = lane >> 5, r = lane & 31;
 #pragma unroll
-  for (int g = 0; g < 2; ++g) {
-    uint32_t hw[4], mw[4], lw[4];
+  for (int q = 0; q < 2; ++q) {
+    const int tl = 16 * wave + 8 * h;
+    float v[8];
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      uint32_t h2[2], m2[2], l2[2];
+    for (int e = 0; e < 8; ++e) v[e] = tile[tl + e][32 * q + r];
+    u4v w[3];
+    split8(v, w);
+    uint16_t *out = frag_ptr(P, i0 / 32 + q, t0 / kMmStep + wave, stages) + 8 * lane;
 #pragma unroll
-      for (int e = 0; e < 2; ++e) {
-        const float v = tile[ts + 8 * g + 2 * w + e][ir];
-        h2[e] = rne_bf16(v);
-        const float r1 = v - bf16_f32(h2[e]);
-        m2[e] = rne_bf16(r1);
-        l2[e] = rne_bf16(r1 - bf16_f32(m2[e]));
-      }
-      hw[w] = h2[0] | (h2[1] << 16);
-      mw[w] = m2[0] | (m2[1] << 16);
-      lw[w] = l2[0] | (l2[1] << 16);
+    for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<u4v *>(out + pl * 4 * kFrag) = w[pl];
+  }
+}
+
+// Row j of X (j < rows) at X + j ldx, T entries along the contraction.  One
+// fragment per wavefront iteration; four stages of one row group in a row,
+// so a row's 256 bytes are read together.
+__global__ __launch_bounds__(256) void k_split_k(const float *__restrict__ X, int64_t rows, int64_t T, int64_t ldx,
+                                                 uint16_t *__restrict__ P, int64_t stages, int vec) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = lane >> 5, r = lane & 31;
+  const int64_t g = blockIdx.y;
+  const int64_t st0 = ((int64_t)blockIdx.x * 4 + wave) * kMmGroup;
+  const int64_t j = 32 * g + r;
+#pragma unroll
+  for (int q = 0; q < kMmGroup; ++q) {
+    const int64_t st = st0 + q;
+    if (st >= stages) return;
+    const int64_t t = st * kMmStep + 8 * h;
+    float v[8];
+    if (vec && j < rows && t + 8 <= T) {
+      const f4 a = *reinterpret_cast<const f4 *>(X + j * ldx + t);
+      const f4 b = *reinterpret_cast<const f4 *>(X + j * ldx + t + 4);
+      v[0] = a.x, v[1] = a.y, v[2] = a.z, v[3] = a.w, v[4] = b.x, v[5] = b.y, v[6] = b.z, v[7] = b.w;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = (j < rows && t + e < T) ? X[j * ldx + t + e] : 0.f;
     }
-    const int64_t off = i * ldt + t0 + ts + 8 * g;
-    *reinterpret_cast<u4v *>(P + off) = u4v{hw[0], hw[1], hw[2], hw[3]};
-    *reinterpret_cast<u4v *>(P + plane + off) = u4v{mw[0], mw[1], mw[2], mw[3]};
-    *reinterpret_cast<u4v *>(P + 2 * plane + off) = u4v{lw[0], lw[1], lw[2], lw[3]};
+    u4v w[3];
+    split8(v, w);
+    uint16_t *out = frag_ptr(P, g, st, stages) + 8 * lane;
+#pragma unroll
+    for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<u4v *>(out + pl * 4 * kFrag) = w[pl];
   }
 }
 
@@ -272,152 +333,364 @@ __device__ __forceinline__ bf8 lds_bf8x(const uint16_t *p) {
   return __builtin_bit_cast(bf8, *reinterpret_cast<const u4v *>(p));
 }
 
-// SYM: C = P P^T over the lower-triangle tiles (A = B = P, n x n, mirrored);
-// otherwise C (na x nb) = PA PB^T over all tiles.  Operands: three planes,
-// row-major along the contraction (leading dim ldt, plane strides planeA,
-// planeB); C column-major with leading dim ldc.
+typedef __attribute__((address_space(1))) const void gmem_t;
+typedef __attribute__((address_space(3))) void lmem_t;
+
+// A product C = A B^T of two panel sets (A = B and the lower triangle when
+// SYM), its tiles and their split over the contraction.
+struct Mm16 {
+  const uint16_t *PA, *PB;
+  int64_t na, nb, stages;  // rows of A, rows of B, stages (a multiple of kMmGroup)
+  int ta, tb;              // 128-row panels of A and B
+  int full;                // tiles computed whole by one workgroup (a multiple of 256)
+  int rest;                // the remaining tiles, each split into `parts` stage ranges
+  int parts;
+  int64_t part_stages;     // stages of a range (a multiple of kMmFlush when parts > 1)
+  double *partial;         // rest x parts float64 tiles (parts > 1)
+  float *C;
+  int64_t ldc;
+};
+
+// Tile `tix` of the sequence all workgroups follow: four panel rows at a
+// time, column by column, so that the ~32 tiles an XCD has in flight lie in
+// a 4 x 8 block (12 panels through its L2 instead of 33).
 template <bool SYM>
-__global__ __launch_bounds__(512) void k_mm16(const uint16_t *__restrict__ PA, const uint16_t *__restrict__ PB,
-                                              int64_t na, int64_t nbr, int64_t ldt, int64_t planeA,
-                                              int64_t planeB, float *__restrict__ S, int64_t lds, int tiles_a,
-                                              int tiles_b) {
-  __shared__ __attribute__((aligned(16))) uint16_t As[2][3][kTile * kLDH];
-  __shared__ __attribute__((aligned(16))) uint16_t Bs[2][3][kTile * kLDH];
-  const int ntiles = SYM ? tiles_a * (tiles_a + 1) / 2 : tiles_a * tiles_b;
-  const int b = blockIdx.x;
-  const int per_xcd = (ntiles + 7) / 8;
-  const int tix = (b % 8) * per_xcd + (b / 8);  // consecutive tiles on one XCD
-  if (tix >= ntiles) return;
-  int bi = 0, bj = 0;
+__device__ __forceinline__ void mm16_tile(const Mm16 &m, int tix, int &bi, int &bj) {
+  int b0 = 0, g = (m.ta & 3) ? (m.ta & 3) : 4;  // first row and height of the band
   if (SYM) {
-    while ((bi + 1) * (bi + 2) / 2 <= tix) ++bi;
-    bj = tix - bi * (bi + 1) / 2;
+    for (;;) {
+      const int cnt = g * b0 + g * (g + 1) / 2;
+      if (tix < cnt) break;
+      tix -= cnt;
+      b0 += g;
+      g = 4;
+    }
+    if (tix < g * (b0 + 1)) {
+      bj = tix / g;
+      bi = b0 + tix % g;
+      return;
+    }
+    tix -= g * (b0 + 1);
+    int j = 1;
+    while (tix >= g - j) {
+      tix -= g - j;
+      ++j;
+    }
+    bj = b0 + j;
+    bi = b0 + j + tix;
   } else {
-    bi = tix % tiles_a;
-    bj = tix / tiles_a;
+    for (;;) {
+      const int cnt = g * m.tb;
+      if (tix < cnt) break;
+      tix -= cnt;
+      b0 += g;
+      g = 4;
+    }
+    bj = tix / g;
+    bi = b0 + tix % g;
   }
-  const int64_t row_a = (int64_t)bi * kTile, row_b = (int64_t)bj * kTile;
-  const int64_t n = na, plane = planeA;
-  const uint16_t *P = PA;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wr = wave >> 1, wc = wave & 1;  // rows wr*32.., columns wc*64..
-  const int h = lane >> 5, r = lane & 31;
+}
 
-  // staging: thread tid loads, for each plane, the 8 periods 8 (tid & 3) ..
-  // of panel row tid >> 2
-  const int prow = tid >> 2, pseg = 8 * (tid & 3);
-  const bool oka = row_a + prow < n, okb = row_b + prow < (SYM ? n : nbr);
-  const uint16_t *pa = P + (row_a + prow) * ldt + pseg;
-  const uint16_t *pb = (SYM ? P : PB) + (row_b + prow) * ldt + pseg;
-  const int64_t planeb = SYM ? plane : planeB;
-  u4v ra[3], rb[3];
-  auto gload = [&](int64_t k0) {
-#pragma unroll
-    for (int pl = 0; pl < 3; ++pl) {
-      ra[pl] = oka ? *reinterpret_cast<const u4v *>(pa + pl * plane + k0) : u4v{0u, 0u, 0u, 0u};
-      rb[pl] = okb ? *reinterpret_cast<const u4v *>(pb + pl * planeb + k0) : u4v{0u, 0u, 0u, 0u};
+// Element e of a lane's 64 accumulators (block q = (a, b) of 2 x 2, register
+// v) in the 128 x 128 tile; 32 x 32 output layout: lane (h, r), register v
+// -> row 8 (v/4) + 4 h + (v%4), column r.
+template <bool SYM>
+__device__ __forceinline__ void mm16_store(const Mm16 &m, int bi, int bj, int wr, int wc, int h, int r, int q, int v,
+                                           float val) {
+  const int64_t rr = (int64_t)bi * kTile + wr * 64 + 32 * (q >> 1) + 8 * (v >> 2) + 4 * h + (v & 3);
+  const int64_t cc = (int64_t)bj * kTile + wc * 64 + 32 * (q & 1) + r;
+  if (SYM) {
+    // the plane products of (i, j) and (j, i) are summed in different
+    // orders, so a diagonal tile keeps its lower half and mirrors it
+    if (rr < m.na && cc < m.na && (bi != bj || rr >= cc)) {
+      m.C[rr + cc * m.ldc] = val;
+      m.C[cc + rr * m.ldc] = val;
     }
-  };
-  auto sstore = [&](int buf) {
-#pragma unroll
-    for (int pl = 0; pl < 3; ++pl) {
-      *reinterpret_cast<u4v *>(&As[buf][pl][prow * kLDH + pseg]) = ra[pl];
-      *reinterpret_cast<u4v *>(&Bs[buf][pl][prow * kLDH + pseg]) = rb[pl];
-    }
-  };
+  } else if (rr < m.na && cc < m.nb) {
+    m.C[rr + cc * m.ldc] = val;
+  }
+}
 
-  v16f acc[2];
-  double acc64[2][16];
+// Four wavefronts, one per SIMD, 64 x 64 of the tile each (2 x 2 blocks,
+// float32 accumulators with a float64 total: 64 + 128 registers; 64 x 64 is
+// the largest block whose totals fit beside two register sets of
+// fragments).  Per stage and compute unit: 768 cycles of matrix
+// instructions, 384 of LDS reads, 384 of loads at 64 bytes a cycle.  With
+// everything but the matrix instructions taken out the loads and LDS reads
+// took 4.6 ms at n = 5440, T = 48384, the matrix instructions alone 4.2, the
+// kernel 6.5 (1.32 PFLOP/s of plane products; issuing a stage's six loads
+// in one go instead of between the products: 7.1).  Before, with eight
+// wavefronts of 32 x 64, register staging and padded LDS rows: 11.1 ms at
+// that size (n = 4000, T = 16000: 2.74 ms, now 1.37; n = 501, T = 2003:
+// 103 us, now 17 and the join's 11).
+template <bool SYM>
+__global__ __launch_bounds__(256, 1) void k_mm16(Mm16 m) {
+  __shared__ __attribute__((aligned(16))) uint16_t ring[kMmRing * 2 * kPanelStage];
+  const int u = blockIdx.x;
+  int tix, part = 0;
+  if (u < m.full) {
+    tix = (u & 7) * (m.full >> 3) + (u >> 3);  // consecutive tiles on one XCD
+  } else {
+    const int units = m.rest * m.parts;
+    const int per_xcd = (units + 7) >> 3;
+    const int e = (u & 7) * per_xcd + ((u - m.full) >> 3);
+    if (e >= units) return;
+    part = e / m.rest;
+    tix = m.full + e % m.rest;
+  }
+  int bi = 0, bj = 0;
+  mm16_tile<SYM>(m, tix, bi, bj);
+  const bool split = u >= m.full && m.parts > 1;
+  const int64_t s0 = split ? part * m.part_stages : 0;
+  const int64_t s1 = split ? (s0 + m.part_stages < m.stages ? s0 + m.part_stages : m.stages) : m.stages;
+  const int ns = (int)(s1 - s0);
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wr = wave >> 1, wc = wave & 1;
+
+  // staging: wavefronts 0, 1 bring the A panel's fragments, 2, 3 the B
+  // panel's, six each
+  const uint16_t *src = (wave < 2 ? m.PA + ((int64_t)bi * m.stages + s0) * kPanelStage
+                                  : (SYM ? m.PA : m.PB) + ((int64_t)bj * m.stages + s0) * kPanelStage) +
+                        (wave & 1) * 6 * kFrag + 8 * lane;
+  const int dst = (wave >> 1) * kPanelStage + (wave & 1) * 6 * kFrag;
+  int issued = 0, wbuf = 0;
+  // past the last stage the last one is fetched again (never read), so that
+  // every step has the same number of loads in flight
+  // (a stage's six loads are spread between its products: the compute unit
+  // takes 64 bytes a cycle, and a wavefront waits at a load that does not
+  // fit in the queue)
+  auto issue = [&](auto j_c) {
+    constexpr int j = decltype(j_c)::value;
+    __builtin_amdgcn_global_load_lds((gmem_t *)(src + (j / 3) * 3 * kFrag),
+                                     (lmem_t *)(ring + wbuf + dst + (j / 3) * 3 * kFrag), 16, (j % 3) * 1024, 0);
+  };
+  auto issued_stage = [&]() {
+    if (++issued < ns) src += kPanelStage;
+    wbuf += 2 * kPanelStage;
+    if (wbuf == kMmRing * 2 * kPanelStage) wbuf = 0;
+  };
+#define MM16_J(j) std::integral_constant<int, j>{}
+
+  v16f acc[4];
+  double tot[4][16];
 #pragma unroll
-  for (int q = 0; q < 2; ++q)
+  for (int q = 0; q < 4; ++q)
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       acc[q][v] = 0.f;
-      acc64[q][v] = 0.0;
+      tot[q][v] = 0.0;
     }
-  const int64_t nstages = ldt / kKB;  // ldt is a multiple of 64
-  gload(0);
-  sstore(0);
-  __syncthreads();
-  for (int64_t st = 0; st < nstages; ++st) {
-    const int buf = (int)(st & 1);
-    if (st + 1 < nstages) gload((st + 1) * kKB);
+  auto flush = [&](int q, int v0, int v1) {
 #pragma unroll
-    for (int ks = 0; ks < kKB / 16; ++ks) {
-      const int koff = 16 * ks + 8 * h;
-      bf8 a[3], bb[2][3];
+    for (int v = v0; v < v1; ++v) {
+      tot[q][v] += (double)acc[q][v];
+      acc[q][v] = 0.f;
+    }
+  };
+
+  bf8 fa[2][2][3], fb[2][2][3];  // two register sets: this stage's and the next's
+  int rbuf = 0;
+  const int aoff = 2 * wr * kFrag + 8 * lane, boff = kPanelStage + 2 * wc * kFrag + 8 * lane;
+  // pair i = 0..5 of a stage's twelve fragments (plane 2 first: the first
+  // products need planes 2 of A and 0 of B)
+  auto fetch_pair = [&](int set, int i) {
+    const uint16_t *l = ring + rbuf;
+    const int g = i & 1, pl = i >> 1;
+    fa[set][g][2 - pl] = lds_bf8x(l + aoff + (4 * (2 - pl) + g) * kFrag);
+    fb[set][g][pl] = lds_bf8x(l + boff + (4 * pl + g) * kFrag);
+  };
+  auto fetched = [&]() {
+    rbuf += 2 * kPanelStage;
+    if (rbuf == kMmRing * 2 * kPanelStage) rbuf = 0;
+  };
+  auto mma1 = [&](int set, int q, int pa, int pb) {
+    acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[set][q >> 1][pa], fb[set][q & 1][pb], acc[q], 0, 0, 0);
+  };
+  // plane products, smallest terms first
+  constexpr int ka[6] = {2, 1, 0, 1, 0, 0}, kb[6] = {0, 1, 2, 0, 1, 0};
+  // One stage: wait for the next stage's data (its loads are older than the
+  // 6 (kMmRing - 2) newest) and for this stage's LDS reads, meet the other
+  // wavefronts; then six groups of products, each with a sixth of the
+  // refill of the buffer this stage was read from and of the next stage's
+  // reads into the other register set.  fq >= 0: block fq's float32 sums go
+  // to its float64 total beside the other three blocks' products, its own
+  // products come last.  The scheduling barriers keep this order.
+  auto step = [&](auto set_c, auto fq_c) {
+    constexpr int set = decltype(set_c)::value, fq = decltype(fq_c)::value;
+    asm volatile("s_waitcnt vmcnt(24) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    auto part = [&](auto k_c) {
+      constexpr int k = decltype(k_c)::value;
+      fetch_pair(set ^ 1, k);
+      issue(k_c);
+      if constexpr (fq < 0) {
 #pragma unroll
-      for (int pl = 0; pl < 3; ++pl) a[pl] = lds_bf8x(&As[buf][pl][(wr * 32 + r) * kLDH + koff]);
+        for (int q = 0; q < 4; ++q) mma1(set, q, ka[k], kb[k]);
+      } else {
 #pragma unroll
-      for (int q = 0; q < 2; ++q)
-#pragma unroll
-        for (int pl = 0; pl < 3; ++pl) bb[q][pl] = lds_bf8x(&Bs[buf][pl][(wc * 64 + 32 * q + r) * kLDH + koff]);
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        // smallest terms first
-        acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[2], bb[q][0], acc[q], 0, 0, 0);
-        acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], bb[q][1], acc[q], 0, 0, 0);
-        acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], bb[q][2], acc[q], 0, 0, 0);
-        acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], bb[q][0], acc[q], 0, 0, 0);
-        acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], bb[q][1], acc[q], 0, 0, 0);
-        acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], bb[q][0], acc[q], 0, 0, 0);
+        for (int q = 1; q < 4; ++q) mma1(set, (fq + q) & 3, ka[k], kb[k]);
+        if constexpr (k > 0) flush(fq, 4 * (k - 1), k < 5 ? 4 * k : 16);
       }
-    }
-    if (((st + 1) % kFlushStages) == 0 || st + 1 == nstages) {
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    part(MM16_J(0)), part(MM16_J(1)), part(MM16_J(2)), part(MM16_J(3)), part(MM16_J(4)), part(MM16_J(5));
+    if constexpr (fq >= 0) {
 #pragma unroll
-      for (int q = 0; q < 2; ++q)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          acc64[q][v] += (double)acc[q][v];
-          acc[q][v] = 0.f;
-        }
+      for (int k = 0; k < 6; ++k) mma1(set, fq, ka[k], kb[k]);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    if (st + 1 < nstages) sstore(buf ^ 1);
-    __syncthreads();
+    issued_stage();
+    fetched();
+  };
+#define MM16_STEP(set, fq) step(MM16_J(set), MM16_J(fq))
+  static_assert(6 * (kMmRing - 2) == 24 && 6 * (kMmRing - 1) == 30, "loads in flight behind a stage");
+#pragma unroll
+  for (int s = 0; s < kMmRing; ++s) {
+    issue(MM16_J(0)), issue(MM16_J(1)), issue(MM16_J(2)), issue(MM16_J(3)), issue(MM16_J(4)), issue(MM16_J(5));
+    issued_stage();
   }
-  // the tile and its mirror; 32 x 32 output layout: lane (h, r), register v
-  // -> row 8 (v/4) + 4 h + (v%4), column r
+  asm volatile("s_waitcnt vmcnt(30)\n\ts_barrier" ::: "memory");
 #pragma unroll
-  for (int q = 0; q < 2; ++q)
+  for (int k = 0; k < 6; ++k) fetch_pair(0, k);
+  fetched();
+  int s = 0;
+  for (; s + kMmFlush <= ns; s += kMmFlush) {
+    // each block's flush comes at its own quarter of the period
+    MM16_STEP(0, 0), MM16_STEP(1, -1), MM16_STEP(0, -1), MM16_STEP(1, -1);
+    MM16_STEP(0, 1), MM16_STEP(1, -1), MM16_STEP(0, -1), MM16_STEP(1, -1);
+    MM16_STEP(0, 2), MM16_STEP(1, -1), MM16_STEP(0, -1), MM16_STEP(1, -1);
+    MM16_STEP(0, 3), MM16_STEP(1, -1), MM16_STEP(0, -1), MM16_STEP(1, -1);
+  }
+  for (; s < ns; s += 2) MM16_STEP(0, -1), MM16_STEP(1, -1);
+#undef MM16_STEP
+#undef MM16_J
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no load may still write this workgroup's LDS at its end
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int64_t rr = row_a + wr * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
-      const int64_t cc = row_b + wc * 64 + 32 * q + r;
-      if (SYM) {
-        // the plane products of (i, j) and (j, i) are summed in different
-        // orders, so a diagonal tile keeps its lower half and mirrors it
-        if (rr < n && cc < n && (bi != bj || rr >= cc)) {
-          const float val = (float)acc64[q][v];
-          S[rr + cc * lds] = val;
-          S[cc + rr * lds] = val;
-        }
-      } else if (rr < n && cc < nbr) {
-        S[rr + cc * lds] = (float)acc64[q][v];
-      }
-    }
+  for (int q = 0; q < 4; ++q) flush(q, 0, 16);
+
+  if (split) {
+    double *out = m.partial + ((int64_t)(tix - m.full) * m.parts + part) * kTileElems + threadIdx.x;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) out[(16 * q + v) * 256] = tot[q][v];
+    return;
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) mm16_store<SYM>(m, bi, bj, wr, wc, lane >> 5, lane & 31, q, v, (float)tot[q][v]);
 }
 
-int64_t split_ldt(int64_t T) { return (T + kSplitTile - 1) / kSplitTile * kSplitTile; }
+// The split tiles: their ranges' float64 sums added in range order.  Grid:
+// (tiles, 4 blocks of a tile).
+template <bool SYM>
+__global__ __launch_bounds__(256) void k_mm16_join(Mm16 m) {
+  const int tix = m.full + blockIdx.x, q = blockIdx.y;
+  int bi = 0, bj = 0;
+  mm16_tile<SYM>(m, tix, bi, bj);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const double *in = m.partial + (int64_t)blockIdx.x * m.parts * kTileElems + 16 * q * 256 + threadIdx.x;
+  double t[16];
+#pragma unroll
+  for (int v = 0; v < 16; ++v) t[v] = in[v * 256];
+  for (int p = 1; p < m.parts; ++p)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) t[v] += in[(int64_t)p * kTileElems + v * 256];
+#pragma unroll
+  for (int v = 0; v < 16; ++v)
+    mm16_store<SYM>(m, bi, bj, wave >> 1, wave & 1, lane >> 5, lane & 31, q, v, (float)t[v]);
+}
 
-size_t syrk_split_bytes(int64_t n, int64_t T) { return (size_t)3 * (size_t)n * (size_t)split_ldt(T) * 2; }
+namespace {
 
-int launch_syrk_split(const float *L, int64_t n, int64_t T, int64_t ld, uint16_t *planes, float *Sigma,
-                      int64_t lds, hipStream_t s) {
-  const int64_t ldt = split_ldt(T);
-  const int64_t plane = n * ldt;
-  hipLaunchKernelGGL(k_split_t, dim3((unsigned)(ldt / kSplitTile), (unsigned)((n + kSplitTile - 1) / kSplitTile)),
-                     dim3(256), 0, s, L, n, T, ld, planes, ldt, plane);
-  if (hipGetLastError() != hipSuccess) return (int)hipErrorLaunchFailure;
-  const int nb = (int)((n + kTile - 1) / kTile);
-  const int ntiles = nb * (nb + 1) / 2;
-  const int grid = ((ntiles + 7) / 8) * 8;
-  hipLaunchKernelGGL(k_mm16<true>, dim3(grid), dim3(512), 0, s, planes, planes, n, n, ldt, plane, plane, Sigma,
-                     lds, nb, nb);
+constexpr int kMmUnits = 256;     // workgroups in flight: one per compute unit
+constexpr int kMmMaxParts = 768;  // float64 tiles of split sums (96 MiB)
+
+int64_t mm16_stages(int64_t T) {
+  return (T + kMmStep * kMmGroup - 1) / (kMmStep * kMmGroup) * kMmGroup;
+}
+int64_t panel_elems(int64_t rows, int64_t T) { return (rows + kTile - 1) / kTile * mm16_stages(T) * kPanelStage; }
+
+// Whole tiles in rounds of one per compute unit; what is left over would
+// occupy a last round only partly (n = 4000: 16 of 528 tiles, a third
+// round as long as the others), so each left-over tile is cut into stage
+// ranges, as many as make the extra rounds shortest; a range costs about 30
+// stages (its float64 tile written and added again).
+void mm16_plan(Mm16 &m, int64_t tiles) {
+  m.full = (int)(tiles / kMmUnits * kMmUnits);
+  m.rest = (int)(tiles - m.full);
+  m.parts = 1;
+  m.part_stages = m.stages;
+  if (m.rest == 0) return;
+  int64_t best = m.stages;
+  for (int p = 2; p <= 64 && (int64_t)p * m.rest <= kMmMaxParts; ++p) {
+    const int64_t len = ((m.stages + p - 1) / p + kMmFlush - 1) / kMmFlush * kMmFlush;
+    const int64_t cnt = (m.stages + len - 1) / len;
+    if (cnt != p) continue;
+    const int64_t cost = (cnt * m.rest + kMmUnits - 1) / kMmUnits * len + 30;
+    if (cost < best) {
+      best = cost;
+      m.parts = p;
+      m.part_stages = len;
+    }
+  }
+}
+
+int64_t mm16_tiles(bool sym, int64_t ta, int64_t tb) { return sym ? ta * (ta + 1) / 2 : ta * tb; }
+
+size_t mm16_partial_bytes(bool sym, int64_t na, int64_t nb, int64_t T) {
+  Mm16 m{};
+  m.stages = mm16_stages(T);
+  mm16_plan(m, mm16_tiles(sym, (na + kTile - 1) / kTile, (nb + kTile - 1) / kTile));
+  return m.parts > 1 ? sizeof(double) * (size_t)m.rest * (size_t)m.parts * kTileElems : 0;
+}
+
+template <bool SYM>
+int launch_mm16(Mm16 m, hipStream_t s) {
+  m.ta = (int)((m.na + kTile - 1) / kTile);
+  m.tb = (int)((m.nb + kTile - 1) / kTile);
+  mm16_plan(m, mm16_tiles(SYM, m.ta, m.tb));
+  const int grid = m.full + (m.rest * m.parts + 7) / 8 * 8;
+  hipLaunchKernelGGL(k_mm16<SYM>, dim3(grid), dim3(256), 0, s, m);
+  if (m.parts > 1) {
+    if (hipGetLastError() != hipSuccess) return (int)hipErrorLaunchFailure;
+    hipLaunchKernelGGL(k_mm16_join<SYM>, dim3(m.rest, 4), dim3(256), 0, s, m);
+  }
   return (int)hipGetLastError();
 }
 
+int launch_split_t(const float *A, int64_t n, int64_t T, int64_t ld, uint16_t *P, hipStream_t s) {
+  const int64_t stages = mm16_stages(T);
+  const int64_t rows = (n + kTile - 1) / kTile * kTile;
+  hipLaunchKernelGGL(k_split_t, dim3((unsigned)(stages / kMmGroup), (unsigned)(rows / kSplitTile)), dim3(256), 0, s,
+                     A, n, T, ld, P, stages);
+  return (int)hipGetLastError();
+}
+
+}  // namespace
+
+size_t syrk_split_bytes(int64_t n, int64_t T) {
+  return sizeof(uint16_t) * (size_t)panel_elems(n, T) + mm16_partial_bytes(true, n, n, T);
+}
+
+int launch_syrk_split(const float *L, int64_t n, int64_t T, int64_t ld, uint16_t *planes, float *Sigma,
+                      int64_t lds, hipStream_t s) {
+  if (launch_split_t(L, n, T, ld, planes, s)) return (int)hipErrorLaunchFailure;
+  Mm16 m{};
+  m.PA = m.PB = planes;
+  m.na = m.nb = n;
+  m.stages = mm16_stages(T);
+  m.partial = reinterpret_cast<double *>(planes + panel_elems(n, T));
+  m.C = Sigma;
+  m.ldc = lds;
+  return launch_mm16<true>(m, s);
+}
+
 size_t gemm_split_bytes(int64_t m, int64_t ncols, int64_t K) {
-  return (size_t)3 * (size_t)(m + ncols) * (size_t)split_ldt(K) * 2;
+  return sizeof(uint16_t) * (size_t)(panel_elems(m, K) + panel_elems(ncols, K)) +
+         mm16_partial_bytes(false, m, ncols, K);
 }
 
 int launch_split_rows(const float *X, int64_t rows, int64_t T, int64_t ldx, uint16_t *P, int64_t ldt,
@@ -431,21 +704,24 @@ int launch_split_rows(const float *X, int64_t rows, int64_t T, int64_t ldx, uint
 
 int launch_gemm_split(const float *A, int64_t lda, const float *B, int64_t ldb, float *C, int64_t ldc, int64_t M,
                       int64_t N, int64_t K, uint16_t *planes, hipStream_t s) {
-  const int64_t ldt = split_ldt(K);
-  const int64_t planeA = M * ldt, planeB = N * ldt;
-  uint16_t *PA = planes, *PB = planes + 3 * planeA;
-  hipLaunchKernelGGL(k_split_t, dim3((unsigned)(ldt / kSplitTile), (unsigned)((M + kSplitTile - 1) / kSplitTile)),
-                     dim3(256), 0, s, A, M, K, lda, PA, ldt, planeA);
+  const int64_t stages = mm16_stages(K);
+  uint16_t *PB = planes + panel_elems(M, K);
+  if (launch_split_t(A, M, K, lda, planes, s)) return (int)hipErrorLaunchFailure;
+  const int64_t groups = (N + kTile - 1) / kTile * (kTile / 32);
+  const int vec = (ldb % 4) == 0 && (reinterpret_cast<uintptr_t>(B) % 16) == 0;
+  hipLaunchKernelGGL(k_split_k, dim3((unsigned)((stages + 15) / 16), (unsigned)groups), dim3(256), 0, s, B, N, K, ldb,
+                     PB, stages, vec);
   if (hipGetLastError() != hipSuccess) return (int)hipErrorLaunchFailure;
-  const int64_t groups = N * (ldt / 8);
-  const int sgrid = (int)std::min<int64_t>((groups + 255) / 256, 65536);
-  hipLaunchKernelGGL(k_split_rows, dim3(sgrid), dim3(256), 0, s, B, N, K, ldb, PB, ldt, planeB);
-  if (hipGetLastError() != hipSuccess) return (int)hipErrorLaunchFailure;
-  const int ta = (int)((M + kTile - 1) / kTile), tb = (int)((N + kTile - 1) / kTile);
-  const int grid = ((ta * tb + 7) / 8) * 8;
-  hipLaunchKernelGGL(k_mm16<false>, dim3(grid), dim3(512), 0, s, PA, PB, M, N, ldt, planeA, planeB, C, ldc, ta,
-                     tb);
-  return (int)hipGetLastError();
+  Mm16 m{};
+  m.PA = planes;
+  m.PB = PB;
+  m.na = M;
+  m.nb = N;
+  m.stages = stages;
+  m.partial = reinterpret_cast<double *>(PB + panel_elems(N, K));
+  m.C = C;
+  m.ldc = ldc;
+  return launch_mm16<false>(m, s);
 }
 
 // g = 2 Sigma x (+ 2 gamma x); the serial tail runs as a separate launch.
