@@ -183,7 +183,8 @@ typedef struct npga_result {
   double sweep_ms;        /* mean duration of the gradient launch (fused sweep, or the
                              covariance-path SYMV+tail), timed with HIP events on
                              `stream` around one launch per chunk of the main phase   */
-  int32_t sweep_samples;  /* number of launches averaged into sweep_ms               */
+  int32_t sweep_samples;  /* number of launches averaged into sweep_ms (0, and sweep_ms
+                             0, where the iterations ran as one launch)              */
   int32_t dykstra_used;   /* 1 if the step projections ran by Dykstra's method: asked
                              for (projection = 1), or the dual search could not
                              bracket nu and the solve was repeated with it          */
@@ -269,6 +270,16 @@ size_t npga_solve_workspace_size(int64_t n, int64_t cols, const npga_options *op
  * npga_solve_workspace_size with opt->path = AUTO (or opt NULL) sizes for
  * the float32 choice, which also covers a bfloat16 factor (GEMV).           */
 int npga_auto_path(int64_t n, int64_t cols, int32_t dtype);
+
+/* For up to 2048 assets npga_solve may run a whole phase (step-size
+ * estimate, iterations, refinement round) as one launch of up to 32
+ * workgroups that wait for each other's gradient pieces.  The waits are
+ * bounded: when one lasts longer than `us` microseconds (default 50000; other
+ * work may keep some of the workgroups from starting) the launch ends and
+ * the solve goes on with a launch per step, with the same result.  us < 0:
+ * always a launch per step.  Applies to the calling host thread; returns the
+ * previous value.                                                          */
+int64_t npga_set_loop_wait(int64_t us);
 int npga_solve(const npga_factor *f, double r, const npga_options *opt, float *x,
                npga_result *res, void *ws, size_t ws_bytes, hipStream_t stream);
 

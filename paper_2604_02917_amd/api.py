@@ -94,6 +94,7 @@ def _load():
         "npga_struct_size": (sz, [i32]),
         "npga_solve_workspace_size": (sz, [i64, i64, ctypes.POINTER(_Options)]),
         "npga_auto_path": (ctypes.c_int, [i64, i64, i32]),
+        "npga_set_loop_wait": (i64, [i64]),
         "npga_solve": (ctypes.c_int, [ctypes.POINTER(_Factor), dbl, ctypes.POINTER(_Options), vp,
                                       ctypes.POINTER(_Result), vp, sz, vp]),
         "npga_project": (ctypes.c_int, [vp, vp, i64, dbl, vp, vp, vp, sz, vp]),

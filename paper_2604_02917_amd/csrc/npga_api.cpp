@@ -100,6 +100,11 @@ int sweep_grid_for(int64_t cols) {
   return (int)std::max<int64_t>(1, std::min<int64_t>(g, 256));
 }
 
+size_t loop_bytes(int64_t n, int64_t cols, int path) {
+  const int64_t half = std::max(loop_plan(n, cols, path, NPGA_F32).half, loop_plan(n, cols, path, NPGA_BF16).half);
+  return sizeof(unsigned long long) * (size_t)(8 + 2 * half);
+}
+
 SolveLayout solve_layout(int64_t n, int64_t cols, int path, bool pcg) {
   SolveLayout l{};
   l.slots = slots_for(n);
@@ -136,6 +141,8 @@ SolveLayout solve_layout(int64_t n, int64_t cols, int path, bool pcg) {
   l.off_xa = take(sizeof(double) * npad);
   l.off_ga = take(sizeof(double) * npad);
   l.off_ua = take(sizeof(double) * (size_t)cols);
+  // exchange words of the one-launch phases (two halves and the abort word)
+  l.off_loop = take(loop_bytes(n, cols, path));
   l.pcg = pcg;
   if (pcg) {
     l.off_pre_y = take(sizeof(float) * (size_t)npad * kPreK);
@@ -176,10 +183,12 @@ int resolve_path(int requested, int64_t n, int64_t cols, int dtype = NPGA_F32) {
   if (requested == NPGA_PATH_GEMV || requested == NPGA_PATH_SYRK) return requested;
   if (dtype != NPGA_F32 || cols < n) return NPGA_PATH_GEMV;
   // (the planes counted without the padding of their storage to whole
-  // 128-row panels and without the split tiles' partial sums)
+  // 128-row panels and without the split tiles' partial sums, and no
+  // exchange words of the one-launch phases)
   const SolveLayout l = npga::solve_layout(n, cols, NPGA_PATH_SYRK);
   const size_t planes = (size_t)3 * (size_t)n * (size_t)((cols + 63) / 64 * 64) * sizeof(uint16_t);
-  const size_t need = l.total - align_up(npga::syrk_split_bytes(n, cols), 256) + align_up(planes, 256);
+  const size_t need = l.total - align_up(npga::syrk_split_bytes(n, cols), 256) -
+                      align_up(npga::loop_bytes(n, cols, NPGA_PATH_SYRK), 256) + align_up(planes, 256);
   return need <= kAutoSyrkMaxBytes ? NPGA_PATH_SYRK : NPGA_PATH_GEMV;
 }
 
@@ -213,7 +222,19 @@ struct Carved {
   int64_t lds;
   bool precise = false;       // refinement steps with float64 products (H p by two float64 passes)
   double *uscratch = nullptr; // cols doubles for those passes
+  npga::LoopPlan loop{};              // one-launch phases (groups 0: a launch per step)
+  unsigned long long *xch = nullptr;  // their exchange words
 };
+
+// Phases of one solve: the launch-per-step path's chunks, or one launch of up
+// to kLoopSteps steps at a time.  Shared by the phases of a solve, because
+// the sequence numbers of the exchange go on from phase to phase.
+struct LoopRun {
+  bool on = false;
+  uint32_t seq = 0;
+};
+constexpr int kLoopSteps = 4096;
+thread_local int64_t g_loop_wait_us = 50000;
 
 // Refinement method for refine_method = 0.  The primal-dual active-set
 // updates need inner solves accurate enough for the sign of every entry; a
@@ -267,6 +288,8 @@ Carved carve(const npga_factor *f, const SolveLayout &l, void *ws, int path) {
   c.planes = (path == NPGA_PATH_SYRK) ? reinterpret_cast<uint16_t *>(base + l.off_planes) : nullptr;
   a.ybt = reinterpret_cast<double *>(base + l.off_bt);
   a.gybt = a.ybt + l.ldp;
+  c.loop = npga::loop_plan(f->n, f->cols, path, f->dtype);
+  c.xch = reinterpret_cast<unsigned long long *>(base + l.off_loop);
   return c;
 }
 
@@ -308,6 +331,30 @@ int step(const Carved &c, int path, int slots, hipStream_t s) {
   return npga::launch_reduce_tail(c.a, slots, s);
 }
 
+// The exchange words cleared for a solve that may use the one-launch phases
+// (backtracking, Dykstra's projections, float64 products and the
+// preconditioned face solves take the launches).
+int loop_start(const Carved &c, LoopRun *lr, hipStream_t s) {
+  lr->seq = 0;
+  lr->on = c.loop.groups > 0 && !c.a.dykstra && !c.a.backtrack && g_loop_wait_us >= 0;
+  if (!lr->on || c.loop.groups == 1) return 0;
+  return npga::launch_zero_f32(reinterpret_cast<float *>(c.xch), 2 * (8 + 2 * c.loop.half), s);
+}
+
+// One launch of at most `steps` steps of c.a.mode.
+int loop_launch(const Carved &c, LoopRun *lr, int path, int slots, int steps, hipStream_t s) {
+  npga::LoopArgs la{};
+  la.mat = path == NPGA_PATH_SYRK ? static_cast<const void *>(c.sigma) : c.a.L;
+  la.ld = path == NPGA_PATH_SYRK ? c.lds : c.a.ld;
+  la.xch = c.xch;
+  la.half = c.loop.half;
+  la.seq0 = lr->seq;
+  la.steps = steps;
+  la.wait_ticks = 100 * (long long)g_loop_wait_us;
+  lr->seq += (uint32_t)steps;
+  return npga::launch_loop(c.a, la, c.loop.groups, slots, path, s);
+}
+
 // ||L_eff||_2^2 by Lanczos on L_eff L_eff^T (default) or by the power method
 // of the paper's Remark (power_iters sweeps); then alpha.  Lanczos stops at a
 // Ritz residual of lz_tol theta.  For the step size that need only be a
@@ -319,7 +366,8 @@ double step_lanczos_tol(const npga_options &o) {
   return std::min(1e-2, std::max(0.25 * (o.step_safety - 1.0), 1e-4));
 }
 
-int estimate_step(const Carved &c, int path, int slots, const npga_options &o, hipStream_t s, double lz_tol) {
+int estimate_step(const Carved &c, int path, int slots, const npga_options &o, hipStream_t s, double lz_tol,
+                  LoopRun *lr = nullptr, int32_t *host_words = nullptr) {
   if (o.alpha > 0.0) return npga::launch_set_alpha(c.st, o.step_safety, s, o.alpha);  // given by the caller
   if (npga::launch_random_unit(c.a.xbuf0, c.a.xs, c.a.n, o.seed, s)) return 1;
   Carved cp = c;
@@ -328,6 +376,11 @@ int estimate_step(const Carved &c, int path, int slots, const npga_options &o, h
     cp.a.mode = npga::kTailLanczos;
     if (npga::launch_lanczos_init(cp.a, lz_tol, s)) return 1;
     steps = std::min(o.power_iters, npga::kLanczosMax);
+    if (lr && lr->on) {
+      cp.a.host_done = host_words;
+      if (loop_launch(cp, lr, path, slots, steps, s)) return 1;
+      return npga::launch_set_alpha(c.st, o.step_safety, s);
+    }
   } else {
     cp.a.mode = npga::kTailPower;
   }
@@ -369,6 +422,41 @@ int map_done(int done) {
   }
 }
 
+// A phase by one-launch steps until the device reports done; *left: the
+// phase stopped early (a wait ran out), the launches take over.
+int run_phase_loop(const Carved &c, LoopRun *lr, int path, int slots, int64_t max_steps, hipStream_t s, DevState *pin,
+                   hipEvent_t *evs, hipEvent_t ev0, int *done_out, double *phase_ms, bool *left) {
+  *left = false;
+  Carved ci = c;
+  int32_t *word = &pin[0].done;
+  ci.a.host_done = pinned_dev(pin, word);
+  for (int64_t at = 0; at < max_steps; at += kLoopSteps) {
+    word[0] = kStatusUnset;
+    const int steps = (int)std::min<int64_t>(kLoopSteps, max_steps - at);
+    if (loop_launch(ci, lr, path, slots, steps, s)) return NPGA_ERR_HIP;
+    if (hipEventRecord(evs[0], s) != hipSuccess) return NPGA_ERR_HIP;
+    if (hipEventSynchronize(evs[0]) != hipSuccess) return NPGA_ERR_HIP;
+    int32_t done = 0;
+    if (!read_status(word, &done)) return NPGA_ERR_HIP;
+    if (done != npga::kRunning) {
+      float ms = 0.f;
+      (void)hipEventElapsedTime(&ms, ev0, evs[0]);
+      *phase_ms = ms;
+      *done_out = done;
+      return NPGA_OK;
+    }
+    const volatile int32_t *ran = word + 1;
+    if (*ran < 0) {
+      lr->on = false;
+      *left = true;
+      return NPGA_OK;
+    }
+  }
+  *done_out = npga::kMaxIter;
+  *phase_ms = 0.0;
+  return NPGA_OK;
+}
+
 // Runs chunks of `check_every` iterations until the device reports done.
 // Two chunks are kept in flight; the status of chunk j is read while chunk
 // j+1 runs.  Returns the final done code via *done_out and the GPU time
@@ -381,7 +469,13 @@ struct SweepTimer {
 
 int run_phase(const Carved &c, int path, int slots, int check_every, int64_t max_chunks, hipStream_t s,
               DevState *pin, hipEvent_t *evs, hipEvent_t ev0, int *done_out, double *phase_ms,
-              SweepTimer *tm) {
+              SweepTimer *tm, LoopRun *lr = nullptr) {
+  if (lr && lr->on && !c.precise && !c.a.pre_y) {
+    bool left = false;
+    const int e = run_phase_loop(c, lr, path, slots, max_chunks * check_every, s, pin, evs, ev0, done_out, phase_ms,
+                                 &left);
+    if (e || !left) return e;
+  }
   int64_t issued = 0, consumed = 0;
   // the last tail of a chunk stores the chunk's done word into its pinned slot
   Carved last = c;
@@ -505,6 +599,12 @@ const char *npga_status_string(int status) {
   }
 }
 
+int64_t npga_set_loop_wait(int64_t us) {
+  const int64_t old = g_loop_wait_us;
+  g_loop_wait_us = us < 0 ? -1 : std::min<int64_t>(us, 10000000);
+  return old;
+}
+
 int npga_auto_path(int64_t n, int64_t cols, int32_t dtype) {
   if (n < 1 || n > NPGA_MAX_N || cols < 1 || (dtype != NPGA_F32 && dtype != NPGA_BF16)) return -1;
   return resolve_path(NPGA_PATH_AUTO, n, cols, dtype);
@@ -523,8 +623,13 @@ size_t npga_solve_workspace_size(int64_t n, int64_t cols, const npga_options *op
   return t;
 }
 
+// kAgainByLaunches: a one-launch phase could not run to its end (the waits
+// between its workgroups are bounded) before anything was decided; the
+// caller repeats the solve with a launch per step.
+constexpr int kAgainByLaunches = -1;
+
 static int solve_once(const npga_factor *f, double r, const npga_options *opt, float *x, npga_result *res,
-                      void *ws, size_t ws_bytes, hipStream_t stream) {
+                      void *ws, size_t ws_bytes, hipStream_t stream, bool by_loop = true) {
   const auto t0 = Clock::now();
   npga_options o;
   npga_default_options(&o);
@@ -572,7 +677,12 @@ static int solve_once(const npga_factor *f, double r, const npga_options *opt, f
                                       c.lds, stream));
 
   // step size alpha = 1/(safety L_f_hat) from ||L_eff||_2^2 (Sec. 3.1 Remark)
-  LAUNCHCHK(estimate_step(c, path, slots, o, stream, step_lanczos_tol(o)));
+  LoopRun lr;
+  if (by_loop) LAUNCHCHK(loop_start(c, &lr, stream));
+  const bool lz_loop = lr.on;
+  int32_t *lz_words = &pin[1].done;  // done code and steps run, stored by the device
+  lz_words[1] = 0;
+  LAUNCHCHK(estimate_step(c, path, slots, o, stream, step_lanczos_tol(o), &lr, pinned_dev(pin, lz_words)));
 
   // x^0 = Pi_F(x_in or 1/n)
   LAUNCHCHK(npga::launch_set_vector(c.a.xbuf0, o.warm_start ? x : nullptr, nullptr, f->n,
@@ -584,8 +694,13 @@ static int solve_once(const npga_factor *f, double r, const npga_options *opt, f
   double tol_ms = 0.0;
   // refused backtracking trials take launches without advancing the iteration
   const int64_t main_chunks = ((int64_t)o.max_iter + (c.a.backtrack ? 4096 : 0)) / o.check_every + 4;
-  int e = run_phase(c, path, slots, o.check_every, main_chunks, stream, pin, evs, ev0, &done, &tol_ms, &tm);
+  int e = run_phase(c, path, slots, o.check_every, main_chunks, stream, pin, evs, ev0, &done, &tol_ms, &tm,
+                    &lr);
   if (e) return e;
+  if (lz_loop && *static_cast<const volatile int32_t *>(lz_words + 1) < 0) {
+    HIPCHK(hipStreamSynchronize(stream));
+    return kAgainByLaunches;
+  }
   const int main_done = done;
   HIPCHK(hipMemcpyAsync(&pin[2], c.st, sizeof(DevState), hipMemcpyDeviceToHost, stream));
   HIPCHK(hipStreamSynchronize(stream));
@@ -656,7 +771,8 @@ static int solve_once(const npga_factor *f, double r, const npga_options *opt, f
       cr.precise = precise;
       cr.uscratch = ua;
       cr.a.mode = blocking ? npga::kTailCG : npga::kTailPdas;
-      e = run_phase(cr, path, slots, o.check_every, ref_chunks, stream, pin, evs, ev0, &done, &rms, nullptr);
+      e = run_phase(cr, path, slots, o.check_every, ref_chunks, stream, pin, evs, ev0, &done, &rms, nullptr,
+                    &lr);
       if (e) return e;
       HIPCHK(hipMemcpyAsync(&pin[2], c.st, sizeof(DevState), hipMemcpyDeviceToHost, stream));
       HIPCHK(hipStreamSynchronize(stream));
@@ -720,10 +836,11 @@ int npga_solve(const npga_factor *f, double r, const npga_options *opt, float *x
   npga_options o;
   npga_default_options(&o);
   if (opt) o = *opt;
-  const int e = solve_once(f, r, &o, x, res, ws, ws_bytes, stream);
+  int e = solve_once(f, r, &o, x, res, ws, ws_bytes, stream);
+  if (e == kAgainByLaunches) e = solve_once(f, r, &o, x, res, ws, ws_bytes, stream, false);
   if (e != NPGA_ERR_BRACKET || o.projection == 1) return e;
   o.projection = 1;
-  return solve_once(f, r, &o, x, res, ws, ws_bytes, stream);
+  return solve_once(f, r, &o, x, res, ws, ws_bytes, stream, false);
 }
 
 int npga_project(const double *v, const double *mu, int64_t n, double r, double *x, double *nu_tau,

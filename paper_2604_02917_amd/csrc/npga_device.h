@@ -395,7 +395,7 @@ __device__ int dykstra_F(double (&v)[E], const double (&mu)[E], double r, int ma
 // flags) instead of the dual search; a separate instantiation, so the dual
 // search's kernels carry none of its registers.
 template <int E, bool DYK = false, int NW = 4>
-__device__ ProjResult project_F(double (&v)[E], const double (&mu)[E], double r, double tolphi,
+__device__ __forceinline__ ProjResult project_F(double (&v)[E], const double (&mu)[E], double r, double tolphi,
                                 double nu_warm, double tau_warm, BlockReducer<5, NW> &red, int dyk_iters = 0) {
   ProjResult out{0.0, 0.0, 0, 0};
   int passes = 0, flags = 0;

@@ -253,7 +253,7 @@ int batch_default_config(int64_t n, int64_t cols, int32_t m);
 // Workspace carving for a solve.
 struct SolveLayout {
   size_t off_state, off_status_dev, off_xs, off_x0, off_x1, off_g0, off_g1, off_part, off_usq,
-      off_sigma, off_planes, off_vecs, off_bt, off_xa, off_ga, off_ua, total;
+      off_sigma, off_planes, off_vecs, off_bt, off_xa, off_ga, off_ua, off_loop, total;
   // the refinement's preconditioner (pcg): Y, pre_mat, a1, a2, and the
   // multi-vector product's GEMM buffers (Omega, U^T, split partials, column
   // sums, active list)
@@ -267,7 +267,27 @@ struct SolveLayout {
 
 int slots_for(int64_t n);
 SolveLayout solve_layout(int64_t n, int64_t cols, int path, bool pcg = false);
+size_t loop_bytes(int64_t n, int64_t cols, int path);  // exchange words of the one-launch phases
 int sweep_grid_for(int64_t cols);
+
+// A phase of a small solve in one launch (npga_loop.hip).
+constexpr int kLoopMaxGroups = 32;
+constexpr int64_t kLoopMaxBytes = 512 << 10;  // streamed and exchanged per workgroup and iteration
+struct LoopArgs {
+  const void *mat;          // Sigma (leading dim ld) or the factor L
+  int64_t ld;
+  unsigned long long *xch;  // abort word, 7 unused, then two halves of `half` words
+  int64_t half;
+  uint32_t seq0;            // sequence number before this launch's first step
+  int32_t steps;            // steps of this launch at most
+  long long wait_ticks;     // bound of a wait, in ticks of the 100 MHz counter
+};
+struct LoopPlan {
+  int groups;               // workgroups; 0: not for this shape
+  int64_t half;
+};
+LoopPlan loop_plan(int64_t n, int64_t cols, int path, int dtype);
+int launch_loop(const SolveArgs &a, const LoopArgs &la, int groups, int slots, int path, hipStream_t s);
 
 // ---- launchers (defined in the .hip files; return hipError_t as int) ----
 int launch_prepare(const SolveArgs &a, hipStream_t s);

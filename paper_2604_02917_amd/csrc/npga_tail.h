@@ -24,7 +24,7 @@ namespace npga {
 // y and grad f(y).  NW: wavefronts of the workgroup (thread t owns entries
 // t + 64 NW j, j < E).
 template <int E, bool DYK = false, bool BT = false, int NW = 4>
-__device__ void tail_npga(const SolveArgs &a, double usq_total, double *redbuf) {
+__device__ __forceinline__ void tail_npga(const SolveArgs &a, double usq_total, double *redbuf) {
   constexpr int NT = 64 * NW;
   DevState *st = a.st;
   const int tid = threadIdx.x;
@@ -386,7 +386,7 @@ __device__ inline double ritz_last_component(const double *al, const double *be,
 // value's own error is of the order of the squared residual) or the
 // recurrence breaks down; rho2 receives theta.
 template <int E>
-__device__ void tail_lanczos(const SolveArgs &a, double *redbuf) {
+__device__ __forceinline__ void tail_lanczos(const SolveArgs &a, double *redbuf) {
   DevState *st = a.st;
   const int tid = threadIdx.x;
   BlockReducer<5> red{redbuf, 0};
@@ -500,7 +500,7 @@ __device__ __forceinline__ void face_multipliers(const double (&g)[E], const dou
 }
 
 template <int E, int NW = 4>
-__device__ void tail_cg(const SolveArgs &a, double *redbuf, double *mbuf, int64_t *ibuf) {
+__device__ __forceinline__ void tail_cg(const SolveArgs &a, double *redbuf, double *mbuf, int64_t *ibuf) {
   constexpr int NT = 64 * NW;
   DevState *st = a.st;
   const int tid = threadIdx.x;
@@ -811,7 +811,7 @@ __device__ void tail_cg(const SolveArgs &a, double *redbuf, double *mbuf, int64_
 // using the plain projected gradient.
 // ---------------------------------------------------------------------------
 template <int E, int NW = 4>
-__device__ void tail_pdas(const SolveArgs &a, double *redbuf) {
+__device__ __forceinline__ void tail_pdas(const SolveArgs &a, double *redbuf) {
   constexpr int NT = 64 * NW;
   DevState *st = a.st;
   const int tid = threadIdx.x;
