@@ -152,7 +152,7 @@ SolveLayout solve_layout(int64_t n, int64_t cols, int path, bool pcg) {
     l.off_pre_a2 = take(sizeof(double) * (size_t)npad);
     l.off_pre_x = take(sizeof(float) * (size_t)npad * kPreK);
     l.off_pre_ut = take(sizeof(float) * (size_t)kPreK * (size_t)cols);
-    l.off_pre_p = take(sizeof(float) * (size_t)kPreMaxSplits * (size_t)n * kPreK);
+    l.off_pre_p = take(sizeof(float) * (size_t)kPreMaxSplits * (size_t)((n + 3) / 4 * 4) * kPreK);
     l.off_pre_usq = take(sizeof(double) * (size_t)((cols + 31) / 32) * kPreK);
     l.off_pre_act = take(sizeof(int32_t) * (size_t)(kPreK + 1));
     l.off_pre_z = take(sizeof(double) * (size_t)npad);
@@ -1217,17 +1217,13 @@ namespace {
 struct BatchLayout {
   SolveLayout single;
   size_t off_states, off_X, off_vec, off_Ut, off_P, off_usq, off_status, off_act, off_U16, off_Lt, off_sigma,
-      off_planes, off_l32, off_prec, total;
-  int64_t npad, ldx, ldut, ldpm, ldq, ldu16, ldlt, lds, ld32, ldsp;
+      off_planes, off_l32, off_prec, off_xp, total;
+  int64_t npad, ldx, ldut, ldpm, ldpi, ldq, ldu16, ldlt, lds, ld32, stages, xpstride;
   bool cov;
 };
 
 constexpr int kMaxSplits = 64;
-// Tile of the covariance form's GEMM 2 Sigma X whatever the number of running
-// targets: 64 x 64 (the table's 64 x 64 entry; measured at C4 with the
-// float32 GEMM against the factor form's choice of 128 x m-wide tiles: 6535
-// vs 5304 solves/s; the bfloat16 split-plane GEMM takes the same tile)
-constexpr int kCovConfig = 6;
+constexpr int64_t kUSplitMax = 512;
 constexpr int kNumVec = 9;  // xbuf0, xbuf1, gbuf0, gbuf1, pvec, fvec, gvec, xa, ga
 
 // cov: the covariance form (Sigma, the bfloat16 planes the SYRK reads, and a
@@ -1240,6 +1236,7 @@ BatchLayout batch_layout(int64_t n, int64_t cols, int32_t m, bool cov = false) {
   l.ldx = l.npad;
   l.ldut = (m + 3) / 4 * 4;
   l.ldpm = (m + 3) / 4 * 4;
+  l.ldpi = (n + 3) / 4 * 4;
   l.ldq = l.ldpm;
   size_t off = align_up(l.single.total, 256);
   auto take = [&](size_t bytes) {
@@ -1251,8 +1248,8 @@ BatchLayout batch_layout(int64_t n, int64_t cols, int32_t m, bool cov = false) {
   l.off_X = take(sizeof(float) * (size_t)l.ldx * (size_t)m);
   l.off_vec = take(sizeof(double) * (size_t)kNumVec * (size_t)l.npad * (size_t)m);
   l.off_Ut = take(sizeof(float) * (size_t)l.ldut * (size_t)cols);
-  l.off_P = take(sizeof(float) * (size_t)kMaxSplits * (size_t)n * (size_t)l.ldpm);
-  const int64_t utiles_max = (cols + 63) / 64;
+  l.off_P = take(sizeof(float) * (size_t)kMaxSplits * (size_t)l.ldpi * (size_t)l.ldpm);
+  const int64_t utiles_max = (cols + 31) / 32;
   l.off_usq = take(sizeof(double) * (size_t)utiles_max * (size_t)l.ldq);
   l.off_status = take(sizeof(int32_t) * (size_t)(2 * (m + 1)));
   l.off_act = take(sizeof(int32_t) * (size_t)(m + 1));
@@ -1266,9 +1263,11 @@ BatchLayout batch_layout(int64_t n, int64_t cols, int32_t m, bool cov = false) {
     l.off_U16 = l.off_Lt = 0;
     l.off_sigma = take(sizeof(float) * (size_t)l.lds * (size_t)n);
     // the SYRK's planes of L, then (once Sigma is formed) Sigma's three
-    // bfloat16 planes for the iteration GEMM
-    l.ldsp = (n + 63) / 64 * 64;
-    l.off_planes = take(std::max(npga::syrk_split_bytes(n, cols), sizeof(uint16_t) * 3 * (size_t)n * (size_t)l.ldsp));
+    // bfloat16 planes for the iteration GEMM; the iterates' planes
+    l.stages = npga::split_stages(n);
+    l.xpstride = 48 * l.stages;
+    l.off_planes = take(std::max(npga::syrk_split_bytes(n, cols), sizeof(uint16_t) * (size_t)npga::split_k_elems(n, n)));
+    l.off_xp = take(sizeof(uint16_t) * (size_t)m * (size_t)l.xpstride);
     l.off_l32 = take(sizeof(float) * (size_t)l.ld32 * (size_t)cols);
   } else {
     // bfloat16 factors: U planes and the row-major copy of L
@@ -1289,28 +1288,26 @@ bool batch_uses_covariance(int requested, int64_t n, int64_t cols) {
   return requested == NPGA_PATH_AUTO && resolve_path(NPGA_PATH_AUTO, n, cols, NPGA_F32) == NPGA_PATH_SYRK;
 }
 
-// Split and tile counts of a configuration for this factor.
-npga::BatchArgs with_config(npga::BatchArgs b, const npga::BatchConfig &cfg) {
+// Split and tile counts of a configuration for this factor and at most
+// `running` running targets.
+npga::BatchArgs with_config(npga::BatchArgs b, const npga::BatchConfig &cfg, int32_t running) {
   const int64_t cols = b.base.cols;
   if (b.covariance) {
-    // Sigma X split over the contraction so that a launch has about 512
-    // workgroups (chunks of whole 32-row stages; measured at n = 2000 with
-    // 64 x 64 tiles and the split-plane GEMM: 256, 384, 512, 768 and 1024
-    // workgroups took 20.5, 18.4, 16.0, 20.0 and 18.2 us per iteration)
-    const int64_t n = b.base.n;
-    const int64_t tiles = ((n + cfg.u_bm - 1) / cfg.u_bm) * ((b.m + cfg.u_bn - 1) / cfg.u_bn);
-    int64_t want = std::max<int64_t>(1, std::min<int64_t>((512 + tiles - 1) / tiles, kMaxSplits));
-    want = std::min<int64_t>(want, (n + 31) / 32);
-    const int64_t kc = ((n + want - 1) / want + 31) / 32 * 32;
-    b.kchunk = kc;
-    b.splits = (int32_t)((n + kc - 1) / kc);
+    npga::cov_plan(b, running);
     b.utiles = 0;
     return b;
   }
+  b.running = running;
   const int64_t kc = ((cols + cfg.splits - 1) / cfg.splits + 31) / 32 * 32;
   b.kchunk = kc;
   b.splits = (int32_t)((cols + kc - 1) / kc);
-  if (b.Lt) {
+  // The U GEMM: the configuration's tiles, or 32 x 32 tiles split over the
+  // assets inside a workgroup while those are at most kUSplitMax workgroups
+  // (one to two rounds of the chip)
+  b.u_split = (cols + 31) / 32 * ((running + 31) / 32) <= kUSplitMax ? 1 : 0;
+  if (b.u_split) {
+    b.utiles = (int32_t)((cols + 31) / 32);
+  } else if (b.Lt) {
     const int bt = cfg.g_bn == 32 ? 128 : 64;  // period tile of the bfloat16 U GEMM
     b.utiles = (int32_t)((cols + bt - 1) / bt);
   } else {
@@ -1354,6 +1351,7 @@ npga::BatchArgs carve_batch(const npga_factor *f, const BatchLayout &l, void *ws
   b.ldut = l.ldut;
   b.P = reinterpret_cast<float *>(base + l.off_P);
   b.ldpm = l.ldpm;
+  b.ldpi = l.ldpi;
   b.usq_part = reinterpret_cast<double *>(base + l.off_usq);
   b.ldq = l.ldq;
   int32_t *act = reinterpret_cast<int32_t *>(base + l.off_act);
@@ -1366,7 +1364,7 @@ npga::BatchArgs carve_batch(const npga_factor *f, const BatchLayout &l, void *ws
     b.ldu16 = l.ldu16;
     b.u16plane = (int64_t)m * l.ldu16;
   }
-  return with_config(b, cfg);
+  return with_config(b, cfg, m);
 }
 
 // Per-call preparation of the bfloat16 path: Lt = L row-major (zero past
@@ -1451,18 +1449,19 @@ int pcg_build(const npga_factor *f, const SolveLayout &l, char *base, hipStream_
   b.ldut = npga::kPreK;
   b.P = reinterpret_cast<float *>(base + l.off_pre_p);
   b.ldpm = npga::kPreK;
+  b.ldpi = (f->n + 3) / 4 * 4;
   b.usq_part = reinterpret_cast<double *>(base + l.off_pre_usq);
   b.ldq = npga::kPreK;
   int32_t *act = reinterpret_cast<int32_t *>(base + l.off_pre_act);
   b.act = act;
   b.mact = act + npga::kPreK;
   const npga::BatchConfig &cfg = batch_config_of(-1, f->n, f->cols, npga::kPreK);
-  b = with_config(b, cfg);
+  b = with_config(b, cfg, npga::kPreK);
   if (b.splits > npga::kPreMaxSplits || b.utiles > (f->cols + 31) / 32) return 1;
   if (npga::launch_pre_omega(a.xs, l.ldp, f->n, s)) return 1;
   if (npga::launch_bact_all(b, act, act + npga::kPreK, s)) return 1;
   if (npga::launch_bgemm(b, cfg, s)) return 1;
-  return npga::launch_pre_reduce(b.P, b.ldpm, b.splits, f->n, reinterpret_cast<float *>(base + l.off_pre_y),
+  return npga::launch_pre_reduce(b.P, b.ldpm, b.ldpi, b.splits, f->n, reinterpret_cast<float *>(base + l.off_pre_y),
                                  reinterpret_cast<float *>(base + l.off_pre_yt), l.ldp, s);
 }
 
@@ -1493,7 +1492,7 @@ int run_batch_phase(const npga::BatchArgs &b0, const npga::BatchConfig &req, int
   auto issue = [&](int slot) -> int {
     const npga::BatchConfig &cfg =
         b0.covariance ? req : config_for_running(req, b0.base.n, b0.base.cols, running);
-    const npga::BatchArgs b = with_config(b0, cfg);
+    const npga::BatchArgs b = with_config(b0, cfg, running);
     for (int i = 0; i < check_every; ++i) {
       if (i == 0 && tm && hipEventRecord(tm->a[slot], s) != hipSuccess) return NPGA_ERR_HIP;
       if (npga::launch_bgemm(b, cfg, s)) return NPGA_ERR_HIP;
@@ -1587,10 +1586,9 @@ int npga_solve_batched(const npga_factor *f, const double *r_targets, int32_t m,
   DevState *pin = pinned_status();
   BatchPinned *bp = batch_pinned(m);
   if (!pin || !bp) return NPGA_ERR_HIP;
-  // the covariance form tiles by the batch width (batch_config tunes the
-  // factor form's GEMM pair)
-  const npga::BatchConfig &cfg = cov ? npga::kBatchConfigTable[kCovConfig]
-                                     : batch_config_of(o.batch_config, f->n, f->cols, m);
+  // (batch_config tunes the factor form's GEMM pair; the covariance form
+  // plans its GEMM from the running targets)
+  const npga::BatchConfig &cfg = batch_config_of(o.batch_config, f->n, f->cols, m);
   Carved c = carve(f, lay.single, ws, NPGA_PATH_GEMV);
   npga::BatchArgs b = carve_batch(f, lay, ws, m, cfg);
   const int slots = lay.single.slots;
@@ -1653,10 +1651,12 @@ int npga_solve_batched(const npga_factor *f, const double *r_targets, int32_t m,
     LAUNCHCHK(npga::launch_syrk_split(L32, f->n, f->cols, ld32, planes, sigma, lay.lds, stream));
     // Sigma's bfloat16 planes over the SYRK's (the SYRK is done with them
     // in stream order): the iteration GEMM runs on the bfloat16 matrix cores
-    LAUNCHCHK(npga::launch_split_rows(sigma, f->n, f->n, lay.lds, planes, lay.ldsp, f->n * lay.ldsp, stream));
+    LAUNCHCHK(npga::launch_split_k(sigma, f->n, f->n, lay.lds, planes, stream));
     b.Sp = planes;
-    b.ldsp = lay.ldsp;
-    b.spplane = f->n * lay.ldsp;
+    b.Xp = reinterpret_cast<uint16_t *>(base + lay.off_xp);
+    b.xpstride = lay.xpstride;
+    b.stages = lay.stages;
+    LAUNCHCHK(npga::launch_zero_f32(reinterpret_cast<float *>(b.Xp), (int64_t)m * lay.xpstride / 2, stream));
     b.base.L = sigma;
     b.base.ld = lay.lds;
     b.base.cols = f->n;
@@ -1664,7 +1664,7 @@ int npga_solve_batched(const npga_factor *f, const double *r_targets, int32_t m,
     b.Lt = nullptr;
     b.U16 = nullptr;
     b.covariance = 1;
-    b = with_config(b, cfg);
+    b = with_config(b, cfg, m);
   }
   LAUNCHCHK(batch_prepare_b16(b, lay, stream));
   LAUNCHCHK(npga::launch_bset_x0(b, o.warm_start ? X : nullptr, ldx, stream));

@@ -1,23 +1,24 @@
 // Batched solves: m targets r_1..r_m on one factor L (points of the
 // efficient frontier, Sec. 5), each running Algorithm 1 with its own state.
 //
-// One iteration of all targets is four launches:
+// One iteration of all targets is three launches:
 //   k_bgemm_u : U^T = X^T L  (m x T): v_mfma_f32_32x32x2f32 over tiles of
 //               periods t x targets j, both operands contiguous along the
 //               asset index i (the contraction);
-//   k_bgemm_g : P[s] = L_{:, T_s} U_{T_s, :}  (n x m) for the period range
-//               T_s of split s: L tiles contiguous along the output rows i,
+//   k_bgemm_g : P[s] = (L_{:, T_s} U_{T_s, :})^T  (m x n) for the period
+//               range T_s of split s: L tiles contiguous along the assets i,
 //               U^T tiles contiguous along the targets j;
-//   k_breduce : g_j = 2 sum_s P[s][:, j] in a fixed order, plus the epilogue
-//               of target j's mode (ridge term, anchor, CG direction);
-//   k_btail   : one workgroup per target runs that target's serial tail
-//               (stopping test, momentum, projection; or a face-CG step).
+//   k_btail   : one workgroup per target: g_j = 2 sum_s P[s][j] in a fixed
+//               order, the epilogue of its mode (ridge term, anchor, CG
+//               direction) and its serial tail (stopping test, momentum,
+//               projection; or a face-CG step).
 // L is read twice per iteration for all m targets instead of once per
 // target, and the arithmetic moves from the vector ALUs to the matrix cores.
 // The covariance form (Sigma = L L^T formed once) replaces the GEMM pair by
-// one GEMM P[s] = Sigma[:, K_s] X[K_s, :] (k_cov16).
+// one GEMM P[s] = (Sigma[:, K_s] X[K_s, :])^T (k_cov16).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 
 #include "npga_device.h"
@@ -28,7 +29,6 @@ namespace npga {
 
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef unsigned int u2v __attribute__((ext_vector_type(2)));
-typedef unsigned int u4v __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 
 const BatchConfig kBatchConfigTable[kBatchConfigs] = {
@@ -111,11 +111,7 @@ constexpr int LDK = KB + 4;  // row length (floats) of contraction-contiguous LD
 // step s pairs k = s (lanes 0-31) with k = 16 + s (lanes 32-63) on both
 // operands.  Epilogue: U^T and per-tile column sums of U^2 (float64).
 // --------------------------------------------------------------------------
-// KSPLIT (covariance form, L := Sigma): the contraction is split over
-// grid.z in ranges of b.kchunk rows, and each split writes its partial
-// product into P[(z n + t) ldpm + j] (the layout k_breduce sums) instead
-// of U^T; no column sums.
-template <typename TL, int BM, int BN, int WM, int WN, bool KSPLIT = false>
+template <typename TL, int BM, int BN, int WM, int WN>
 __global__ __launch_bounds__(256) void k_bgemm_u(BatchArgs b) {
   constexpr int PM = BM / (32 * WM), PN = BN / (32 * WN);
   constexpr int QA = BM / 32, QB = BN / 32;
@@ -138,8 +134,7 @@ __global__ __launch_bounds__(256) void k_bgemm_u(BatchArgs b) {
   const int ma = *b.mact;
   if (j0 >= ma) return;
   (void)m;
-  const int64_t kbeg = KSPLIT ? (int64_t)blockIdx.z * b.kchunk : 0;
-  const int64_t kend = KSPLIT ? (kbeg + b.kchunk < n ? kbeg + b.kchunk : n) : n;
+  const int64_t kbeg = 0, kend = n;
   // targets of this thread's X columns (column c -> target act[c])
   const float *xcol[QB];
 #pragma unroll
@@ -150,8 +145,6 @@ __global__ __launch_bounds__(256) void k_bgemm_u(BatchArgs b) {
 
   typename R::type ra[QA];
   f4 rb[QB];
-  // (a split's range starts and, except at n, ends on a multiple of 32, so
-  // a float4 never straddles kend below n)
   auto gload = [&](int64_t k0) {
     const int64_t k = k0 + kq;
 #pragma unroll
@@ -230,22 +223,6 @@ __global__ __launch_bounds__(256) void k_bgemm_u(BatchArgs b) {
     __syncthreads();
   }
 
-  if constexpr (KSPLIT) {
-    float *Pz = b.P + (int64_t)blockIdx.z * n * b.ldpm;
-#pragma unroll
-    for (int p = 0; p < PM; ++p)
-#pragma unroll
-      for (int q = 0; q < PN; ++q) {
-        const int64_t j = j0 + wc * 32 * PN + 32 * q + r;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int64_t t = t0 + wr * 32 * PM + 32 * p + 8 * (v >> 2) + 4 * h + (v & 3);
-          if (t < T && j < ma) Pz[t * b.ldpm + j] = acc[p][q][v];
-        }
-      }
-    return;
-  }
-
   // epilogue: U^T (coalesced along j) and column sums of U^2 over this tile
   double cs[PN];
 #pragma unroll
@@ -280,7 +257,104 @@ __global__ __launch_bounds__(256) void k_bgemm_u(BatchArgs b) {
 }
 
 // --------------------------------------------------------------------------
-// P[s] = L_{:, T_s} U_{T_s, :}.  Tile: BM assets x BN targets over the
+// U^T = X^T L for factors whose tiles would leave most of the chip idle: 32
+// periods x 32 targets a workgroup, its eight wavefronts every eighth
+// 16-asset step each (operands straight from memory to registers, four steps
+// ahead), the eight sums added in float64 in LDS.
+// --------------------------------------------------------------------------
+template <typename TL>
+__global__ __launch_bounds__(512) void k_bgemm_u_split(BatchArgs b) {
+  constexpr int D = 4;  // steps in flight
+  typedef Raw4<TL> R;
+  __shared__ float red[8][16][64];
+  const int64_t T = b.base.cols, n = b.base.n, ld = b.base.ld;
+  const int ma = *b.mact;
+  const int64_t t0 = (int64_t)blockIdx.x * 32;
+  const int c0 = (int)blockIdx.y * 32;
+  if (c0 >= ma) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int h = lane >> 5, r = lane & 31;
+  // lane: period t0 + r and target c0 + r, assets 8 h .. 8 h + 7 of a step;
+  // matrix step q pairs assets q and 8 + q.  Past the last: the last, dropped
+  const int c = c0 + r < ma ? c0 + r : ma - 1;
+  const float *X = b.base.xs + (int64_t)b.act[c] * b.ldx + 8 * h;
+  const TL *L = static_cast<const TL *>(b.base.L) + (t0 + r < T ? t0 + r : T - 1) * ld;
+  const int64_t last = ld - 4;
+  const int steps = (int)((n + 15) / 16);
+  const int cnt = (steps - wave + 7) >> 3;
+  f4 xa[D][2];
+  typename R::type lb[D][2];
+  auto load = [&](int slot, int t) {
+    const int64_t k0 = 16 * (int64_t)(wave + 8 * (t < cnt ? t : cnt - 1));
+    const int64_t kl = k0 + 8 * h;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      xa[slot][q] = *reinterpret_cast<const f4 *>(X + k0 + 4 * q);  // zero-padded to a multiple of 256
+      lb[slot][q] = R::load(L + (kl + 4 * q < last ? kl + 4 * q : last));
+    }
+  };
+  v16f acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+  if (cnt > 0) {
+#pragma unroll
+    for (int t = 0; t < D; ++t) {
+      load(t, t);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    for (int s0 = 0; s0 < cnt; s0 += D) {
+#pragma unroll
+      for (int u = 0; u < D; ++u) {
+        if (s0 + u < cnt) {
+          const int64_t k = 16 * (int64_t)(wave + 8 * (s0 + u)) + 8 * h;
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+            f4 l = R::widen(lb[u][q]);
+            const int64_t row = k + 4 * q;  // asset rows past n (ld may exceed n) are not data
+            l.x = row + 0 < n ? l.x : 0.f;
+            l.y = row + 1 < n ? l.y : 0.f;
+            l.z = row + 2 < n ? l.z : 0.f;
+            l.w = row + 3 < n ? l.w : 0.f;
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(l.x, xa[u][q].x, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(l.y, xa[u][q].y, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(l.z, xa[u][q].z, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(l.w, xa[u][q].w, acc, 0, 0, 0);
+          }
+        }
+        load(u, s0 + u + D);
+      }
+    }
+  }
+#pragma unroll
+  for (int v = 0; v < 16; ++v) red[wave][v][lane] = acc[v];
+  __shared__ double qs[8][64];
+  __syncthreads();
+  // register v of lane (h, r): period t0 + 8 (v / 4) + 4 h + v % 4, target c0 + r
+  double q = 0.0;
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    const int v = 8 * e + wave;
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < 8; ++w) s += (double)red[w][v][lane];
+    const int64_t t = t0 + 8 * (v >> 2) + 4 * h + (v & 3);
+    const float val = t < T ? (float)s : 0.f;
+    q = fma((double)val, (double)val, q);
+    if (t < T && c0 + r < ma) b.Ut[c0 + r + t * b.ldut] = val;
+  }
+  qs[wave][lane] = q;
+  __syncthreads();
+  if (tid < 32 && c0 + tid < ma) {
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < 8; ++w) s += qs[w][tid] + qs[w][tid + 32];
+    b.usq_part[(int64_t)blockIdx.x * b.ldq + b.act[c0 + tid]] = s;
+  }
+}
+
+// --------------------------------------------------------------------------
+// P[s] = (L_{:, T_s} U_{T_s, :})^T.  Tile: BM assets x BN targets over the
 // period range of split s (grid.y).  Both LDS tiles are indexed [k][row];
 // MFMA step s takes k = 2s + h.  Output rows i >= n and columns j >= m are
 // never stored, so garbage there (padding of L or U^T) stays in unused
@@ -372,128 +446,189 @@ __global__ __launch_bounds__(256) void k_bgemm_g(BatchArgs b) {
       for (int p = 0; p < PM; ++p)
 #pragma unroll
         for (int q = 0; q < PN; ++q)
-          acc[p][q] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[p], bv[q], acc[p][q], 0, 0, 0);
+          acc[p][q] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv[q], av[p], acc[p][q], 0, 0, 0);
     }
     if (s + 1 < nk) sstore(buf ^ 1);
     __syncthreads();
   }
 
-  float *P = b.P + (int64_t)blockIdx.y * n * b.ldpm;
+  // targets on the output's rows, assets along the lanes
+  float *P = b.P + (int64_t)blockIdx.y * b.ldpm * b.ldpi;
 #pragma unroll
   for (int p = 0; p < PM; ++p)
 #pragma unroll
     for (int q = 0; q < PN; ++q) {
-      const int64_t j = j0 + wc * 32 * PN + 32 * q + r;
+      const int64_t i = i0 + wr * 32 * PM + 32 * p + r;
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        const int64_t i = i0 + wr * 32 * PM + 32 * p + 8 * (v >> 2) + 4 * h + (v & 3);
-        if (i < n && j < ma) P[i * b.ldpm + j] = acc[p][q][v];
+        const int64_t j = j0 + wc * 32 * PN + 32 * q + 8 * (v >> 2) + 4 * h + (v & 3);
+        if (i < n && j < ma) P[j * b.ldpi + i] = acc[p][q][v];
       }
     }
 }
 
 // --------------------------------------------------------------------------
-// g_j = 2 sum_s P[s][:, j] (fixed order over s, float64) and the epilogue of
-// the current mode.  A 16 x 32 tile (rows i x GEMM columns c) per
-// workgroup: the partial reads run along c, eight splits in flight per
-// thread; the tile is transposed through LDS so the per-target reads and
-// writes run along i.
+// One workgroup per running target (GEMM column c): its gradient g = 2 sum_s
+// P[s][c] in a fixed order (float64), the element-wise epilogue of its mode,
+// and its serial tail.  The partials run along the assets, so a workgroup
+// reads its own column's S n floats coalesced (64 KB at n = 2000 and eight
+// splits); the gradient and the step input reach the tail through LDS.  A
+// separate reduce launch before the tail (5.6 us at n = 2000, 128 targets)
+// and its gap are saved.
 // --------------------------------------------------------------------------
-constexpr int RB = 16;  // rows of a reduce tile
 
-__global__ __launch_bounds__(256) void k_breduce(BatchArgs b) {
-  __shared__ double tile[RB][33];
-  const int64_t n = b.base.n;
-  const int ma = *b.mact;
-  const int64_t i0 = (int64_t)blockIdx.x * RB;
-  const int c0 = blockIdx.y * 32;  // GEMM column block (running targets)
-  const int tid = threadIdx.x;
-  if (c0 >= ma) return;
-  {
-    const int cc = tid & 31, ii = tid >> 5;
-    const int64_t split_stride = n * b.ldpm;
-    const int S = b.splits;
+// The planes of x (n floats at xs in LDS; zeros past n) into target j's fragment pieces: one 16-byte group of each plane a thread.
+__device__ __forceinline__ void store_x_planes(const BatchArgs &b, int j, const float *xs) {
+  uint16_t *out = b.Xp + (int64_t)j * b.xpstride;
+  for (int64_t q = threadIdx.x; 8 * q < b.base.n; q += 256) {
+    float v[8];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int64_t i = i0 + ii + 8 * h;
-      double s = 0.0;
-      if (i < n && c0 + cc < ma) {
-        const float *p = b.P + i * b.ldpm + c0 + cc;
-        int sp = 0;
-        for (; sp + 8 <= S; sp += 8) {
-          float v[8];
+    for (int e = 0; e < 8; ++e) v[e] = (8 * q + e < b.base.n) ? xs[8 * q + e] : 0.f;
+    u4v w[3];
+    split8(v, w);
+    uint16_t *o = out + (q >> 1) * 48 + (q & 1) * 8;
 #pragma unroll
-          for (int e = 0; e < 8; ++e) v[e] = p[(int64_t)(sp + e) * split_stride];
-#pragma unroll
-          for (int e = 0; e < 8; ++e) s += (double)v[e];
-        }
-        for (; sp < S; ++sp) s += (double)p[(int64_t)sp * split_stride];
-      }
-      tile[ii + 8 * h][cc] = s;
-    }
-  }
-  __syncthreads();
-  const int il = tid & 15, cq = tid >> 4;
-  const int64_t i = i0 + il;
-  if (i >= n) return;
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int cl = cq + 16 * h;
-    if (c0 + cl >= ma) continue;
-    const SolveArgs a = target_args(b, b.act[c0 + cl]);
-    const DevState *st = a.st;
-    if (st->done != kRunning) continue;
-    const double tot = tile[il][cl];
-    if (a.mode == kTailNpga) {
-      const double *xk = (st->iter & 1) ? a.xbuf1 : a.xbuf0;
-      npga_store_grad_step(a, st, i, 2.0 * tot + (a.ga ? a.ga[i] : 0.0) + 2.0 * st->gamma * xk[i]);
-    } else if (a.mode == kTailGrad) {
-      a.gbuf0[i] = 2.0 * tot + 2.0 * st->gamma * a.xbuf0[i];
-    } else if (a.mode == kTailCG) {
-      a.gbuf0[i] = 2.0 * tot + 2.0 * st->gamma * a.pvec[i];
-    }
+    for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<u4v *>(o + 16 * pl) = w[pl];
   }
 }
 
-// One workgroup per target: the serial tail of that target's iteration.
 template <int E>
 __global__ __launch_bounds__(256) void k_btail(BatchArgs b) {
-  const SolveArgs a = target_args(b, blockIdx.x);
-  if (a.st->done != kRunning) return;
+  __shared__ __attribute__((aligned(16))) double gl[2][256 * E];  // g_k and the step input (CG: H p)
   __shared__ double redbuf[64];
   __shared__ double mbuf[8];
   __shared__ int64_t ibuf[8];
+  // the new iterate in float32 for its planes: the tails read the step input
+  // at their start and write the iterate at their end
+  float *xl = reinterpret_cast<float *>(gl[1]);
+  const int tid = threadIdx.x, c = blockIdx.x;
+  const int64_t n = b.base.n;
+  const int ma = *b.mact, j = b.act[c];  // (act has m entries; those past the running ones are not used)
+  // The partials need only the column, the vectors the target's state: both
+  // chains of loads run side by side.  Entries past n and splits past the
+  // last read the last one and are dropped.
+  int off[E];
+  double tot[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    off[e] = (int)(tid + 256 * e < n ? tid + 256 * e : n - 1);
+    tot[e] = 0.0;
+  }
+  const float *part = b.P + (int64_t)c * b.ldpi;
+  const int64_t split_stride = b.ldpm * b.ldpi;
+  constexpr int F = E <= 8 ? 8 : (E <= 16 ? 4 : 2);  // splits in flight
+  float pv[F][E];
+  auto load_parts = [&](int sp) {
+#pragma unroll
+    for (int f = 0; f < F; ++f) {
+      const float *ps = part + (int64_t)(sp + f < b.splits ? sp + f : b.splits - 1) * split_stride;
+#pragma unroll
+      for (int e = 0; e < E; ++e) pv[f][e] = ps[off[e]];
+    }
+  };
+  load_parts(0);
+  if (c >= ma) return;
+  SolveArgs a = target_args(b, j);
+  DevState *st = a.st;
+  if (st->done != kRunning) return;
+  const int cur = st->iter & 1;
+  const double *xk = cur ? a.xbuf1 : a.xbuf0;
+  const double *xp = cur ? a.xbuf0 : a.xbuf1;
+  double *gk = cur ? a.gbuf1 : a.gbuf0;
+  const double *gp = cur ? a.gbuf0 : a.gbuf1;
+  const bool npga = a.mode == kTailNpga;
+  // NPGA: x_k, x_{k-1}, g_{k-1}; CG: p; gradient only: x
+  const double *r0 = npga ? xk : (a.mode == kTailGrad ? a.xbuf0 : a.pvec);
+  double u0[E], u1[E], u2[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    u0[e] = r0[off[e]];
+    u1[e] = npga ? xp[off[e]] : 0.0;
+    u2[e] = npga ? gp[off[e]] : 0.0;
+  }
+  for (int sp = 0;;) {
+#pragma unroll
+    for (int f = 0; f < F; ++f)
+#pragma unroll
+      for (int e = 0; e < E; ++e) tot[e] += (sp + f < b.splits) ? (double)pv[f][e] : 0.0;
+    sp += F;
+    if (sp >= b.splits) break;
+    load_parts(sp);
+  }
   double usq = -1.0;  // covariance form: f = x^T g / 2 in the tails
-  if (!b.covariance && (a.mode == kTailNpga || a.mode == kTailGrad)) {
+  if (!b.covariance && (a.mode == kTailGrad || (npga && st->iter % st->check_every == 0))) {
     BlockReducer<5> red5{redbuf, 0};
     double acc[5] = {0, 0, 0, 0, 0};
-    for (int w = threadIdx.x; w < b.utiles; w += 256) acc[0] += b.usq_part[(int64_t)w * b.ldq + blockIdx.x];
+    for (int w = tid; w < b.utiles; w += 256) acc[0] += b.usq_part[(int64_t)w * b.ldq + j];
     red5.sum(acc);
     usq = acc[0];
     __syncthreads();
   }
-  if (a.mode == kTailNpga)
-    tail_npga<E>(a, usq, redbuf);
-  else if (a.mode == kTailCG)
-    tail_cg<E>(a, redbuf, mbuf, ibuf);
-  else if (a.mode == kTailGrad)
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int64_t i = tid + 256 * e;
+    if (i >= n) continue;
+    const double g = 2.0 * tot[e];
+    if (npga) {
+      // g_k kept for the next iteration; v = y - alpha grad f(y), as
+      // npga_store_grad_step forms it
+      const double gi = g + (a.ga ? a.ga[i] : 0.0) + 2.0 * st->gamma * u0[e];
+      const double y = fma(st->beta, u0[e] - u1[e], u0[e]);
+      const double gy = fma(st->beta, gi - u2[e], gi);
+      gk[i] = gi;
+      gl[0][i] = gi;
+      gl[1][i] = fma(-st->alpha, gy, y);
+    } else if (a.mode == kTailGrad) {
+      a.gbuf0[i] = g + 2.0 * st->gamma * u0[e];
+    } else {
+      gl[0][i] = g + 2.0 * st->gamma * u0[e];
+    }
+  }
+  if (b.covariance) a.xs = xl;
+  if (a.mode == kTailNpga) {
+    SolveArgs t = a;
+    t.gbuf0 = gl[cur];
+    t.gbuf1 = gl[1 - cur];
+    tail_npga<E>(t, usq, redbuf);
+  } else if (a.mode == kTailCG) {
+    SolveArgs t = a;
+    t.gbuf0 = gl[0];
+    tail_cg<E>(t, redbuf, mbuf, ibuf);
+  } else if (a.mode == kTailGrad) {
     tail_grad<E>(a, usq, redbuf);
+  }
+  if (b.covariance) {
+    __syncthreads();
+    store_x_planes(b, j, xl);
+  }
 }
 
 template <int E>
 __global__ __launch_bounds__(256) void k_bproject_init(BatchArgs b) {
   __shared__ double redbuf[64];
-  const SolveArgs a = target_args(b, blockIdx.x);
+  __shared__ float xl[256 * E];
+  SolveArgs a = target_args(b, blockIdx.x);
   if (a.st->done != kRunning) return;
+  if (b.covariance) a.xs = xl;
   project_init_body<E>(a, redbuf);
+  if (b.covariance) {
+    __syncthreads();
+    store_x_planes(b, blockIdx.x, xl);
+  }
 }
 
 template <int E>
 __global__ __launch_bounds__(256) void k_bcg_init(BatchArgs b) {
   __shared__ double redbuf[64];
-  const SolveArgs a = target_args(b, blockIdx.x);
+  __shared__ float xl[256 * E];
+  SolveArgs a = target_args(b, blockIdx.x);
   if (a.st->done != kRunning) return;
+  if (b.covariance) a.xs = xl;
   cg_init_body<E>(a, redbuf);
+  if (b.covariance) {
+    __syncthreads();
+    store_x_planes(b, blockIdx.x, xl);
+  }
 }
 
 // X[:, j] = x_j (float32); grid (row blocks, m).
@@ -649,7 +784,10 @@ template <typename TL>
 static int launch_bgemm_t(const BatchArgs &b, const BatchConfig &c, hipStream_t s) {
   const int64_t T = b.base.cols, n = b.base.n;
   const dim3 gu((unsigned)((T + c.u_bm - 1) / c.u_bm), (unsigned)((b.m + c.u_bn - 1) / c.u_bn));
-  if (c.u_bm == 128 && c.u_bn == 128)
+  if (b.u_split)
+    hipLaunchKernelGGL(k_bgemm_u_split<TL>, dim3((unsigned)((T + 31) / 32), (unsigned)((b.running + 31) / 32)),
+                       dim3(512), 0, s, b);
+  else if (c.u_bm == 128 && c.u_bn == 128)
     hipLaunchKernelGGL((k_bgemm_u<TL, 128, 128, 2, 2>), gu, dim3(256), 0, s, b);
   else if (c.u_bm == 64 && c.u_bn == 128)
     hipLaunchKernelGGL((k_bgemm_u<TL, 64, 128, 1, 4>), gu, dim3(256), 0, s, b);
@@ -678,157 +816,159 @@ static int launch_bgemm_t(const BatchArgs &b, const BatchConfig &c, hipStream_t 
   return (int)hipGetLastError();
 }
 
-// Covariance form on the bfloat16 matrix cores: P_z = Sigma[:, K_z] X[K_z, :]
-// (the split-partial layout k_breduce sums) with Sigma given as three
-// bfloat16 planes (split once per call) and each float32 column of X split
-// into three planes as it is staged, v = v_h + v_m + v_l exactly; the six
-// largest plane products (h h, h m, m h, h l, m m, l h: the dropped m l,
-// l m and l l are below 2^-24 of the leading one) on
-// v_mfma_f32_32x32x16_bf16 with float32 accumulation over the range, as the
-// split SYRK does.  Tile: 64 rows of Sigma x 64 GEMM columns,
-// four wavefronts of 32 x 32; 32-deep stages of both panels, double
-// buffered.  Grid: (row tiles, column tiles, ranges).
-constexpr int C16K = 32;            // contraction depth of one stage
-constexpr int C16LD = C16K + 8;     // LDS row length in bfloat16 (80 bytes)
-
-__global__ __launch_bounds__(256) void k_cov16(BatchArgs b) {
-  __shared__ __attribute__((aligned(16))) uint16_t As[2][3][64 * C16LD];
-  __shared__ __attribute__((aligned(16))) uint16_t Bs[2][3][64 * C16LD];
+// Covariance form on the bfloat16 matrix cores: P_z = (Sigma[:, K_z]
+// X[K_z, :])^T for the 16-row stages K_z of range z, both operands as three
+// bfloat16 planes (v = v_h + v_m + v_l exactly); the six largest plane
+// products (h h, h m, m h, h l, m m, l h: the dropped m l, l m and l l are
+// below 2^-24 of the leading one) on v_mfma_f32_32x32x16_bf16 with float32
+// accumulation, as the split SYRK does.
+//
+// Tile: 64 rows of Sigma x 32 NC running targets.  The four wavefronts take
+// every fourth stage of the range each, so a fragment is used by one
+// wavefront only and comes straight from memory to its registers (Sigma's
+// fragments lane-linear, X's gathered from the running targets' pieces), D
+// stages ahead; no LDS and no barrier until the four sums meet at the end.
+// Bound by the 64 bytes a cycle a compute unit takes from its L2 (12 KiB a
+// stage at 64 columns) and by latency: at n = 2000 a compute unit has 32
+// stages.
+template <int NC>
+__global__ __launch_bounds__(256, 1) void k_cov16(BatchArgs b) {
+  constexpr int D = 4;  // stages in flight
+  __shared__ float red[4][2 * NC][16][64];
   const int64_t n = b.base.n;
-  const int64_t i0 = (int64_t)blockIdx.x * 64;
-  const int64_t j0 = (int64_t)blockIdx.y * 64;
   const int ma = *b.mact;
-  if (j0 >= ma) return;
-  const int64_t kbeg = (int64_t)blockIdx.z * b.kchunk;
-  const int64_t kend = (kbeg + b.kchunk < n) ? kbeg + b.kchunk : n;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wr = wave >> 1, wc = wave & 1;
+  // workgroups with the same range of the contraction on the same XCDs (and,
+  // with fewer than eight ranges, the same part of the rows): what an XCD
+  // reads of Sigma and X together is an eighth of Sigma and, at most, that
+  // share of X, which its L2 keeps from one iteration to the next
+  const int gx = (int)((n + 63) / 64), sx = b.splits < 8 ? b.splits : 8, rx = 8 / sx;
+  const int gp = (gx + rx - 1) / rx, xcd = blockIdx.x & 7;
+  int loc = blockIdx.x >> 3;
+  const int bz = xcd % sx + sx * (loc % (b.splits / sx));
+  loc /= b.splits / sx;
+  const int bx = (xcd / sx) * gp + loc % gp, by = loc / gp;
+  const int c0 = by * 32 * NC;
+  if (c0 >= ma || bx >= gx) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int h = lane >> 5, r = lane & 31;
-  // staging: row tid / 4 of each panel, contraction entries 8 (tid % 4) .. +7
-  // of a stage
-  const int prow = tid >> 2, pseg = 8 * (tid & 3);
-  const bool oka = i0 + prow < n;
-  const uint16_t *pa = b.Sp + (i0 + prow) * b.ldsp + pseg;
-  const int64_t cb = j0 + prow;
-  const float *xc = (cb < ma) ? b.base.xs + (int64_t)b.act[cb] * b.ldx + pseg : nullptr;
-  u4v ra[3];
-  f4 rx[2];
-  auto gload = [&](int64_t k0) {
+  const int64_t kb = (int64_t)bz * b.kchunk;
+  const int64_t ke = (kb + b.kchunk < b.stages) ? kb + b.kchunk : b.stages;
+  const int cnt = (int)((ke - kb - wave + 3) >> 2);  // this wavefront's stages: kb + wave, + 4, ...
+  const uint16_t *pa[2], *pb[NC];
 #pragma unroll
-    for (int pl = 0; pl < 3; ++pl)
-      ra[pl] = oka ? *reinterpret_cast<const u4v *>(pa + pl * b.spplane + k0) : u4v{0u, 0u, 0u, 0u};
-    // k0 + pseg + 8 <= ldx (X columns are padded to a multiple of 256), so
-    // both loads stay in the column; entries at or past kend are masked at
-    // the split
-    rx[0] = xc ? *reinterpret_cast<const f4 *>(xc + k0) : f4{0.f, 0.f, 0.f, 0.f};
-    rx[1] = xc ? *reinterpret_cast<const f4 *>(xc + k0 + 4) : f4{0.f, 0.f, 0.f, 0.f};
-  };
-  auto sstore = [&](int buf, int64_t k0) {
+  for (int g = 0; g < 2; ++g) pa[g] = frag_ptr(b.Sp, 2 * (int64_t)bx + g, kb + wave, b.stages) + 8 * lane;
 #pragma unroll
-    for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<u4v *>(&As[buf][pl][prow * C16LD + pseg]) = ra[pl];
-    const float v[8] = {rx[0].x, rx[0].y, rx[0].z, rx[0].w, rx[1].x, rx[1].y, rx[1].z, rx[1].w};
-    uint32_t hw[4], mw[4], lw[4];
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      uint32_t h2[2], m2[2], l2[2];
-#pragma unroll
-      for (int e = 0; e < 2; ++e) {
-        const float x = (k0 + pseg + 2 * w + e < kend) ? v[2 * w + e] : 0.f;
-        const uint32_t hb = (__float_as_uint(x) + 0x7fffu + ((__float_as_uint(x) >> 16) & 1u)) >> 16;
-        const float r1 = x - __uint_as_float(hb << 16);
-        const uint32_t mb = (__float_as_uint(r1) + 0x7fffu + ((__float_as_uint(r1) >> 16) & 1u)) >> 16;
-        const float r2 = r1 - __uint_as_float(mb << 16);
-        h2[e] = hb;
-        m2[e] = mb;
-        l2[e] = (__float_as_uint(r2) + 0x7fffu + ((__float_as_uint(r2) >> 16) & 1u)) >> 16;
-      }
-      hw[w] = h2[0] | (h2[1] << 16);
-      mw[w] = m2[0] | (m2[1] << 16);
-      lw[w] = l2[0] | (l2[1] << 16);
-    }
-    *reinterpret_cast<u4v *>(&Bs[buf][0][prow * C16LD + pseg]) = u4v{hw[0], hw[1], hw[2], hw[3]};
-    *reinterpret_cast<u4v *>(&Bs[buf][1][prow * C16LD + pseg]) = u4v{mw[0], mw[1], mw[2], mw[3]};
-    *reinterpret_cast<u4v *>(&Bs[buf][2][prow * C16LD + pseg]) = u4v{lw[0], lw[1], lw[2], lw[3]};
-  };
-  v16f acc;
-#pragma unroll
-  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-  const int64_t nk = (kend - kbeg + C16K - 1) / C16K;
-  gload(kbeg);
-  sstore(0, kbeg);
-  __syncthreads();
-  for (int64_t st = 0; st < nk; ++st) {
-    const int buf = (int)(st & 1);
-    if (st + 1 < nk) gload(kbeg + (st + 1) * C16K);
-#pragma unroll
-    for (int ks = 0; ks < C16K / 16; ++ks) {
-      const int koff = 16 * ks + 8 * h;
-      bf16x8_t a[3], bb[3];
-#pragma unroll
-      for (int pl = 0; pl < 3; ++pl) {
-        a[pl] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u4v *>(&As[buf][pl][(wr * 32 + r) * C16LD + koff]));
-        bb[pl] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u4v *>(&Bs[buf][pl][(wc * 32 + r) * C16LD + koff]));
-      }
-      // smallest terms first
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[2], bb[0], acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], bb[1], acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], bb[2], acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], bb[0], acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], bb[1], acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], bb[0], acc, 0, 0, 0);
-    }
-    if (st + 1 < nk) sstore(buf ^ 1, kbeg + (st + 1) * C16K);
-    __syncthreads();
+  for (int q = 0; q < NC; ++q) {
+    const int c = c0 + 32 * q + r;
+    pb[q] = b.Xp + (int64_t)b.act[c < ma ? c : ma - 1] * b.xpstride + (kb + wave) * 48 + 8 * h;
   }
-  // 32 x 32 output layout: lane (h, r), register v -> row 8 (v / 4) + 4 h + v % 4, column r
-  float *out = b.P + (int64_t)blockIdx.z * n * b.ldpm;
+  typedef bf16x8_t frag_t;
+  frag_t fa[D][2][3], fb[D][NC][3];
+  auto load = [&](int slot, int t) {
+    const int64_t s = 4 * (int64_t)(t < cnt ? t : cnt - 1);  // past the end the last one again, not used
 #pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const int64_t row = i0 + wr * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
-    const int64_t col = j0 + wc * 32 + r;
-    if (row < n && col < ma) out[row * b.ldpm + col] = acc[v];
+    for (int pl = 0; pl < 3; ++pl) {
+#pragma unroll
+      for (int g = 0; g < 2; ++g)
+        fa[slot][g][pl] =
+            __builtin_bit_cast(frag_t, *reinterpret_cast<const u4v *>(pa[g] + s * kPanelStage + pl * 4 * kFrag));
+#pragma unroll
+      for (int q = 0; q < NC; ++q)
+        fb[slot][q][pl] = __builtin_bit_cast(frag_t, *reinterpret_cast<const u4v *>(pb[q] + s * 48 + 16 * pl));
+    }
+  };
+  v16f acc[2][NC];
+#pragma unroll
+  for (int g = 0; g < 2; ++g)
+#pragma unroll
+    for (int q = 0; q < NC; ++q)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[g][q][v] = 0.f;
+  if (cnt > 0) {
+#pragma unroll
+    for (int t = 0; t < D; ++t) {
+      load(t, t);
+      __builtin_amdgcn_sched_barrier(0);  // in the order of use
+    }
+    for (int t0 = 0; t0 < cnt; t0 += D) {
+#pragma unroll
+      for (int u = 0; u < D; ++u) {
+        if (t0 + u < cnt) {
+          // plane products, smallest terms first; targets on the output's
+          // rows, so that a lane's results run along the assets
+          constexpr int ka[6] = {2, 1, 0, 1, 0, 0}, kx[6] = {0, 1, 2, 0, 1, 0};
+#pragma unroll
+          for (int k = 0; k < 6; ++k)
+#pragma unroll
+            for (int g = 0; g < 2; ++g)
+#pragma unroll
+              for (int q = 0; q < NC; ++q)
+                acc[g][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[u][q][kx[k]], fa[u][g][ka[k]], acc[g][q], 0, 0, 0);
+        }
+        load(u, t0 + u + D);
+      }
+    }
+  }
+#pragma unroll
+  for (int g = 0; g < 2; ++g)
+#pragma unroll
+    for (int q = 0; q < NC; ++q)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) red[wave][g * NC + q][v][lane] = acc[g][q][v];
+  __syncthreads();
+  // block k = (g, q), register v -> target c0 + 32 q + 8 (v / 4) + 4 h + v % 4,
+  // asset 64 x + 32 g + r
+  float *out = b.P + (int64_t)bz * b.ldpm * b.ldpi;
+#pragma unroll
+  for (int e = 0; e < 8 * NC; ++e) {
+    const int idx = 4 * e + wave;  // (k, v)
+    const int k = idx >> 4, v = idx & 15;
+    const double s = ((double)red[0][k][v][lane] + (double)red[1][k][v][lane]) +
+                     ((double)red[2][k][v][lane] + (double)red[3][k][v][lane]);
+    const int64_t col = c0 + 32 * (k % NC) + 8 * (v >> 2) + 4 * h + (v & 3);
+    const int64_t row = (int64_t)bx * 64 + 32 * (k / NC) + r;
+    if (row < n && col < ma) out[col * b.ldpi + row] = (float)s;
   }
 }
 
-// Covariance form: G = Sigma X split over the contraction (k_breduce sums
-// the splits), by k_cov16 on Sigma's bfloat16 planes when they are given,
-// else by the float32 U GEMM on L := Sigma (symmetric).
-static int launch_bcov(const BatchArgs &b, const BatchConfig &c, hipStream_t s) {
-  const int64_t n = b.base.n;
-  const unsigned gy = (unsigned)((b.m + c.u_bn - 1) / c.u_bn);
-  const dim3 g((unsigned)((n + c.u_bm - 1) / c.u_bm), gy, (unsigned)b.splits);
-  if (b.Sp) {
-    if (c.u_bm != 64 || c.u_bn != 64 || (b.kchunk % C16K) != 0) return (int)hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_cov16, g, dim3(256), 0, s, b);
-    return (int)hipGetLastError();
-  }
-  if (c.u_bm == 128 && c.u_bn == 128)
-    hipLaunchKernelGGL((k_bgemm_u<float, 128, 128, 2, 2, true>), g, dim3(256), 0, s, b);
-  else if (c.u_bm == 128 && c.u_bn == 64)
-    hipLaunchKernelGGL((k_bgemm_u<float, 128, 64, 2, 2, true>), g, dim3(256), 0, s, b);
-  else if (c.u_bm == 128 && c.u_bn == 32)
-    hipLaunchKernelGGL((k_bgemm_u<float, 128, 32, 4, 1, true>), g, dim3(256), 0, s, b);
-  else if (c.u_bm == 64 && c.u_bn == 64)
-    hipLaunchKernelGGL((k_bgemm_u<float, 64, 64, 2, 2, true>), g, dim3(256), 0, s, b);
-  else if (c.u_bm == 64 && c.u_bn == 128)
-    hipLaunchKernelGGL((k_bgemm_u<float, 64, 128, 1, 4, true>), g, dim3(256), 0, s, b);
+// Ranges and width for `running` targets: 64 columns a workgroup (32 when no
+// more run), the contraction split so that a launch has about one workgroup
+// per compute unit, with at least four stages (one a wavefront) in a range.
+void cov_plan(BatchArgs &b, int running) {
+  const int w = running <= 32 ? 32 : 64;
+  const int64_t tiles = ((b.base.n + 63) / 64) * ((running + w - 1) / w);
+  int64_t want = std::max<int64_t>(1, 256 / tiles);
+  want = std::min<int64_t>(std::min<int64_t>(want, kCovMaxSplits), (b.stages + 3) / 4);
+  // 1, 2, 4 or a multiple of 8 ranges (the ranges are spread over the XCDs)
+  want = want >= 8 ? want / 8 * 8 : (want >= 4 ? 4 : want >= 2 ? 2 : 1);
+  b.kchunk = (b.stages + want - 1) / want;
+  b.splits = (int32_t)want;  // (a last range may be empty: its sums are zeros)
+  b.running = running;
+}
+
+static int launch_bcov(const BatchArgs &b, hipStream_t s) {
+  if (!b.Sp || !b.Xp || b.splits < 1 || b.running < 1) return (int)hipErrorInvalidValue;
+  const int nc = b.running <= 32 ? 1 : 2;
+  const int gx = (int)((b.base.n + 63) / 64), gy = (b.running + 32 * nc - 1) / (32 * nc);
+  const int sx = std::min(b.splits, 8), rx = 8 / sx;
+  const unsigned grid = (unsigned)(8 * (b.splits / sx) * ((gx + rx - 1) / rx) * gy);
+  if (nc == 1)
+    hipLaunchKernelGGL(k_cov16<1>, dim3(grid), dim3(256), 0, s, b);
   else
-    return (int)hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_cov16<2>, dim3(grid), dim3(256), 0, s, b);
   return (int)hipGetLastError();
 }
 
 int launch_bgemm(const BatchArgs &b, const BatchConfig &c, hipStream_t s) {
-  if (b.covariance) return launch_bcov(b, c, s);
+  if (b.covariance) return launch_bcov(b, s);
   if (b.Lt) return launch_b16_gemm(b, c, s);
   if (b.base.dtype == NPGA_BF16) return launch_bgemm_t<bf16_t>(b, c, s);
   return launch_bgemm_t<float>(b, c, s);
 }
 
 int launch_breduce_tail(const BatchArgs &b, int slots, hipStream_t s) {
-  const dim3 gr((unsigned)((b.base.n + RB - 1) / RB), (unsigned)((b.m + 31) / 32));
-  hipLaunchKernelGGL(k_breduce, gr, dim3(256), 0, s, b);
-  if (hipGetLastError() != hipSuccess) return (int)hipErrorLaunchFailure;
-#define CALL(E) hipLaunchKernelGGL(k_btail<E>, dim3((unsigned)b.m), dim3(256), 0, s, b)
+#define CALL(E) hipLaunchKernelGGL(k_btail<E>, dim3((unsigned)b.running), dim3(256), 0, s, b)
   BATCH_SLOT_SWITCH(slots, CALL)
 #undef CALL
   return (int)hipGetLastError();

@@ -9,7 +9,7 @@
 // then give L^T X and L U to float32 accuracy.  Both GEMMs read their
 // operands contiguous along the contraction:
 //   k_b16_u : U[c][t] = sum_i X[i][c] L[i][t]     (L column-major, X columns)
-//   k_b16_g : P[s][i][c] = sum_{t in T_s} Lt[i][t] U[c][t]
+//   k_b16_g : P[s][c][i] = sum_{t in T_s} Lt[i][t] U[c][t]
 // where Lt is a row-major copy of L made once per batched solve.  U is
 // stored directly as its three bfloat16 planes.
 #include <hip/hip_runtime.h>
@@ -23,26 +23,17 @@ namespace npga {
 
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
-typedef unsigned int u4v __attribute__((ext_vector_type(4)));
 typedef unsigned int u2v __attribute__((ext_vector_type(2)));
 
 constexpr int KB16 = 32;          // contraction depth of one LDS stage
 constexpr int LDH = KB16 + 8;     // LDS row length in bfloat16 (80 bytes)
 
-// float32 -> bfloat16 bits, round to nearest even (finite inputs)
-__device__ __forceinline__ uint32_t bf16_rne(float f) {
-  const uint32_t u = __float_as_uint(f);
-  return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
-}
-__device__ __forceinline__ float bf16_val(uint32_t h) { return __uint_as_float(h << 16); }
-
-// Three-plane split of a float32 value.
+// Three-plane split of one value.
 __device__ __forceinline__ void split3(float v, uint32_t &h, uint32_t &m, uint32_t &l) {
-  h = bf16_rne(v);
-  const float r1 = v - bf16_val(h);
-  m = bf16_rne(r1);
-  const float r2 = r1 - bf16_val(m);
-  l = bf16_rne(r2);
+  h = rne_bf16(v);
+  const float r1 = v - bf16_f32(h);
+  m = rne_bf16(r1);
+  l = rne_bf16(r1 - bf16_f32(m));
 }
 
 __device__ __forceinline__ bf8 lds_bf8(const uint16_t *p) {
@@ -210,6 +201,107 @@ __global__ __launch_bounds__(256) void k_b16_u(BatchArgs b) {
 }
 
 // --------------------------------------------------------------------------
+// U = X^T L for factors whose tiles would leave most of the chip idle (701
+// periods in 128-period tiles are six workgroups, each a chain of n / 32
+// stages at a memory round trip apiece: 43 us at n = 1500).  32 targets x 32
+// periods a workgroup; its eight wavefronts take every eighth 16-asset step
+// each, so an operand is used by one wavefront only and comes straight from
+// memory to its registers, four steps ahead; the eight sums meet in LDS at
+// the end (added in float64).  9.6 us at n = 1500, T = 701, 24 targets.
+// --------------------------------------------------------------------------
+__global__ __launch_bounds__(512) void k_b16_u_split(BatchArgs b) {
+  constexpr int D = 4;  // steps in flight
+  __shared__ float red[8][16][64];
+  const int64_t T = b.base.cols, n = b.base.n, ld = b.base.ld;
+  const int ma = *b.mact;
+  const int64_t t0 = (int64_t)blockIdx.x * 32;
+  const int c0 = (int)blockIdx.y * 32;
+  if (c0 >= ma) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int h = lane >> 5, r = lane & 31;
+  // lane: target c0 + r and period t0 + r, assets 8 h .. 8 h + 7 of a step;
+  // targets, periods and steps past the last read the last and are dropped
+  const int c = c0 + r < ma ? c0 + r : ma - 1;
+  const float *X = b.base.xs + (int64_t)b.act[c] * b.ldx + 8 * h;
+  const uint16_t *L = static_cast<const uint16_t *>(b.base.L) + (t0 + r < T ? t0 + r : T - 1) * ld;
+  const int64_t last = (ld - 8) / 8 * 8;  // columns hold ld >= n entries, ld % 8 == 0
+  const int steps = (int)((n + 15) / 16);
+  const int cnt = (steps - wave + 7) >> 3;  // this wavefront's steps: wave, wave + 8, ...
+  f4 xa[D][2];
+  u4v lb[D];
+  auto load = [&](int slot, int t) {
+    const int64_t k0 = 16 * (int64_t)(wave + 8 * (t < cnt ? t : cnt - 1));
+    xa[slot][0] = *reinterpret_cast<const f4 *>(X + k0);  // X columns are padded to a multiple of 256 with zeros
+    xa[slot][1] = *reinterpret_cast<const f4 *>(X + k0 + 4);
+    const int64_t kl = k0 + 8 * h;
+    lb[slot] = *reinterpret_cast<const u4v *>(L + (kl < last ? kl : last));
+  };
+  v16f acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+  if (cnt > 0) {
+#pragma unroll
+    for (int t = 0; t < D; ++t) {
+      load(t, t);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    for (int s0 = 0; s0 < cnt; s0 += D) {
+#pragma unroll
+      for (int u = 0; u < D; ++u) {
+        if (s0 + u < cnt) {
+          const int64_t k = 16 * (int64_t)(wave + 8 * (s0 + u)) + 8 * h;
+          const float v8[8] = {xa[u][0].x, xa[u][0].y, xa[u][0].z, xa[u][0].w,
+                               xa[u][1].x, xa[u][1].y, xa[u][1].z, xa[u][1].w};
+          u4v w[3];
+          split8(v8, w);
+          // asset rows past n (ld may exceed n) are not data
+          u4v lv = lb[u];
+          if (k + 8 > n) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              const int64_t row = k + 2 * q;
+              lv[q] &= row + 1 < n ? 0xffffffffu : (row < n ? 0x0000ffffu : 0u);
+            }
+          }
+          const bf8 bb = __builtin_bit_cast(bf8, lv);
+#pragma unroll
+          for (int pl = 2; pl >= 0; --pl)
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, w[pl]), bb, acc, 0, 0, 0);
+        }
+        load(u, s0 + u + D);
+      }
+    }
+  }
+#pragma unroll
+  for (int v = 0; v < 16; ++v) red[wave][v][lane] = acc[v];
+  __syncthreads();
+  // register v of lane (h, r): target c0 + 8 (v / 4) + 4 h + v % 4, period t0 + r
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    const int v = 8 * e + wave;
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < 8; ++w) s += (double)red[w][v][lane];
+    const float val = (t0 + r < T) ? (float)s : 0.f;
+    const int cc = c0 + 8 * (v >> 2) + 4 * h + (v & 3);
+    double q = (double)val * (double)val;
+#pragma unroll
+    for (int off = 1; off < 32; off <<= 1) q += __shfl_xor(q, off, 64);
+    if (cc >= ma) continue;
+    if (t0 + r < T) {
+      uint32_t hh, mm, ll;
+      split3(val, hh, mm, ll);
+      uint16_t *u = b.U16 + (int64_t)cc * b.ldu16 + t0 + r;
+      u[0] = (uint16_t)hh;
+      u[b.u16plane] = (uint16_t)mm;
+      u[2 * b.u16plane] = (uint16_t)ll;
+    }
+    if (r == 0) b.usq_part[(int64_t)blockIdx.x * b.ldq + b.act[cc]] = q;
+  }
+}
+
+// --------------------------------------------------------------------------
 // P[s] = Lt_{:, T_s} U_{T_s}: BM assets x BN GEMM columns over the period
 // range of split s; U's three planes give three products per step.
 // --------------------------------------------------------------------------
@@ -302,25 +394,26 @@ __global__ __launch_bounds__(256) void k_b16_g(BatchArgs b) {
       for (int p = 0; p < PM; ++p)
 #pragma unroll
         for (int q = 0; q < PN; ++q) {
-          acc[p][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[p], bb[q][2], acc[p][q], 0, 0, 0);
-          acc[p][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[p], bb[q][1], acc[p][q], 0, 0, 0);
-          acc[p][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[p], bb[q][0], acc[p][q], 0, 0, 0);
+          acc[p][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bb[q][2], a[p], acc[p][q], 0, 0, 0);
+          acc[p][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bb[q][1], a[p], acc[p][q], 0, 0, 0);
+          acc[p][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bb[q][0], a[p], acc[p][q], 0, 0, 0);
         }
     }
     if (s + 1 < nk) sstore(buf ^ 1);
     __syncthreads();
   }
 
-  float *P = b.P + (int64_t)blockIdx.y * n * b.ldpm;
+  // columns of the product on the output's rows, assets along the lanes
+  float *P = b.P + (int64_t)blockIdx.y * b.ldpm * b.ldpi;
 #pragma unroll
   for (int p = 0; p < PM; ++p)
 #pragma unroll
     for (int q = 0; q < PN; ++q) {
-      const int64_t c = c0 + wc * 32 * PN + 32 * q + r;
+      const int64_t i = i0 + wr * 32 * PM + 32 * p + r;
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        const int64_t i = i0 + wr * 32 * PM + 32 * p + 8 * (v >> 2) + 4 * h + (v & 3);
-        if (i < n && c < ma) P[i * b.ldpm + c] = acc[p][q][v];
+        const int64_t c = c0 + wc * 32 * PN + 32 * q + 8 * (v >> 2) + 4 * h + (v & 3);
+        if (i < n && c < ma) P[c * b.ldpi + i] = acc[p][q][v];
       }
     }
 }
@@ -345,7 +438,10 @@ __global__ __launch_bounds__(256) void k_transpose16(const uint16_t *L, int64_t 
 int launch_b16_gemm(const BatchArgs &b, const BatchConfig &c, hipStream_t s) {
   const int64_t T = b.base.cols, n = b.base.n;
   const int bn = c.g_bn;  // width of the target tiles
-  if (bn == 128) {
+  if (b.u_split) {
+    const dim3 gu((unsigned)((T + 31) / 32), (unsigned)((b.running + 31) / 32));
+    hipLaunchKernelGGL(k_b16_u_split, gu, dim3(512), 0, s, b);
+  } else if (bn == 128) {
     const dim3 gu((unsigned)((T + 63) / 64), (unsigned)((b.m + 127) / 128));
     hipLaunchKernelGGL((k_b16_u<128, 64, 2, 2>), gu, dim3(256), 0, s, b);
   } else if (bn == 64) {

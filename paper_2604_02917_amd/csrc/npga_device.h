@@ -39,6 +39,50 @@ __device__ __forceinline__ f4 load4_nt<bf16_t>(const bf16_t *p) {
   return r;
 }
 
+// Exact split of a float32 into three bfloat16 planes, v = v_h + v_m + v_l
+// (v_h = bf16(v), v_m = bf16(v - v_h), v_l = bf16(v - v_h - v_m), each
+// difference exact in float32; finite inputs).
+typedef unsigned int u4v __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ uint32_t rne_bf16(float f) {
+  const uint32_t u = __float_as_uint(f);
+  return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
+}
+__device__ __forceinline__ float bf16_f32(uint32_t h) { return __uint_as_float(h << 16); }
+
+// h, m, l words of eight consecutive entries
+__device__ __forceinline__ void split8(const float (&v)[8], u4v (&w)[3]) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    uint32_t h2[2], m2[2], l2[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const float x = v[2 * q + e];
+      h2[e] = rne_bf16(x);
+      const float r1 = x - bf16_f32(h2[e]);
+      m2[e] = rne_bf16(r1);
+      l2[e] = rne_bf16(r1 - bf16_f32(m2[e]));
+    }
+    w[0][q] = h2[0] | (h2[1] << 16);
+    w[1][q] = m2[0] | (m2[1] << 16);
+    w[2][q] = l2[0] | (l2[1] << 16);
+  }
+}
+
+// Fragment order of a matrix in three bfloat16 planes (the order the
+// 32 x 32 x 16 matrix instruction reads it): 1 KiB per 32 rows x 16
+// contraction entries of a plane, lane 32 h + r holding row r, entries
+// 8 h .. 8 h + 7; a stage of a 128-row panel is [3 planes][4 row groups].
+constexpr int kFrag = 512;               // bfloat16 entries of a fragment
+constexpr int kPanelStage = 12 * kFrag;
+
+// Row group g (32 rows), stage st of a matrix of `stages` stages: plane 0;
+// plane p follows at 4 p fragments.
+template <typename T>
+__device__ __forceinline__ T *frag_ptr(T *P, int64_t g, int64_t st, int64_t stages) {
+  return P + ((g >> 2) * stages + st) * kPanelStage + (g & 3) * kFrag;
+}
+
 // Wavefront sums (all 64 lanes active).  Within each 16-lane row four DPP
 // steps (swap neighbours, swap pairs, mirror the half-row, mirror the row)
 // leave the row total in every lane of the row; the four row totals are

@@ -208,8 +208,9 @@ struct BatchArgs {
   int64_t ldx;         // floats between consecutive columns of X
   float *Ut;           // U^T, m x cols, leading dim ldut
   int64_t ldut;
-  float *P;            // G partials: P[(s * n + i) * ldpm + j]
+  float *P;            // G partials: P[(s * ldpm + c) * ldpi + i] (column c of the running targets)
   int64_t ldpm;
+  int64_t ldpi;
   int32_t splits;      // number of t-ranges of the G GEMM
   int64_t kchunk;      // t-range length of one split (multiple of 32)
   double *usq_part;    // per-tile ||U_{:,j}||^2 partials: [tile * ldq + j]
@@ -227,16 +228,19 @@ struct BatchArgs {
   uint16_t *U16;
   int64_t ldu16;
   int64_t u16plane;
-  // covariance form (base.L = Sigma, n x n float32, base.cols = n): the
-  // gradient is 2 Sigma X by one GEMM split over the contraction into
-  // `splits` ranges of `kchunk` rows; the tails take f = x^T g / 2
+  // covariance form: the gradient is 2 Sigma X by one GEMM whose contraction
+  // is split into `splits` ranges of `kchunk` 16-row stages; the tails take
+  // f = x^T g / 2.  Sp: Sigma as three bfloat16 planes in fragment order
+  // (`stages` stages); Xp: target j's float32 iterate as three planes,
+  // [stage][plane][16] from Xp + j xpstride, written by the kernel that
+  // writes the iterate (zeros past n)
   int32_t covariance;
-  // when set, Sigma as three bfloat16 planes (row i of plane p at
-  // Sp + p spplane + i ldsp, zeros past n): the GEMM runs on the bfloat16
-  // matrix cores with X split into planes as it is staged
   const uint16_t *Sp;
-  int64_t ldsp;
-  int64_t spplane;
+  uint16_t *Xp;
+  int64_t xpstride;
+  int64_t stages;
+  int32_t u_split;     // the U GEMM by 32 x 32 tiles split over the assets inside a workgroup
+  int32_t running;     // host's upper bound of *mact (columns a launch has to cover)
 };
 
 // Tile configuration of the two batched GEMMs.
@@ -247,6 +251,8 @@ struct BatchConfig {
 };
 
 constexpr int kBatchConfigs = 12;
+constexpr int kCovMaxSplits = 64;  // contraction ranges of the covariance form's GEMM
+void cov_plan(BatchArgs &b, int running);  // its ranges for this many running targets
 extern const BatchConfig kBatchConfigTable[kBatchConfigs];
 int batch_default_config(int64_t n, int64_t cols, int32_t m);
 
@@ -328,16 +334,17 @@ size_t gemm_split_bytes(int64_t m, int64_t ncols, int64_t K);
 int launch_gemm_split(const float *A, int64_t lda, const float *B, int64_t ldb, float *C, int64_t ldc, int64_t M,
                       int64_t N, int64_t K, uint16_t *planes, hipStream_t s);
 // Three bfloat16 planes of `rows` float32 rows contiguous along T (row j at
-// X + j ldx): P[p plane + j ldt + t], zeros for t in [T, ldt), ldt % 8 == 0.
-int launch_split_rows(const float *X, int64_t rows, int64_t T, int64_t ldx, uint16_t *P, int64_t ldt,
-                      int64_t plane, hipStream_t s);
+// X + j ldx) in fragment order: split_k_elems(rows, T) entries at P.
+int64_t split_k_elems(int64_t rows, int64_t T);
+int64_t split_stages(int64_t T);  // 16-entry stages of a contraction of T
+int launch_split_k(const float *X, int64_t rows, int64_t T, int64_t ldx, uint16_t *P, hipStream_t s);
 
 // Preconditioner set-up of the refinement: Omega (signs) into the batched
-// GEMM input X (column c at X + c ldx), and Y[i][c] = 2 sum_s P[s][i][c]
+// GEMM input X (column c at X + c ldx), and Y[i][c] = 2 sum_s P[s][c][i]
 // (the split partials of the GEMM pair, fixed order) in float32, row-major
 // into Y and column-major (column c at Yt + c ldyt) into Yt.
 int launch_pre_omega(float *X, int64_t ldx, int64_t n, hipStream_t s);
-int launch_pre_reduce(const float *P, int64_t ldpm, int32_t splits, int64_t n, float *Y, float *Yt, int64_t ldyt,
+int launch_pre_reduce(const float *P, int64_t ldpm, int64_t ldpi, int32_t splits, int64_t n, float *Y, float *Yt, int64_t ldyt,
                       hipStream_t s);
 // Preconditioned start of a refinement round (after launch_cg_init): the
 // first round forms S and estimates sigma, later rounds reuse them.

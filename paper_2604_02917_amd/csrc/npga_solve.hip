@@ -768,15 +768,15 @@ __global__ __launch_bounds__(256) void k_pre_omega(float *X, int64_t ldx, int64_
 
 // Y[i][c] = 2 sum_s P[(s n + i) ldpm + c], the splits in order, stored
 // row-major (Y) and column-major (Yt).
-__global__ __launch_bounds__(256) void k_pre_reduce(const float *P, int64_t ldpm, int32_t splits, int64_t n,
-                                                    float *Y, float *Yt, int64_t ldyt) {
+__global__ __launch_bounds__(256) void k_pre_reduce(const float *P, int64_t ldpm, int64_t ldpi, int32_t splits,
+                                                    int64_t n, float *Y, float *Yt, int64_t ldyt) {
   const int64_t total = n * kPreK;
   for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < total; e += (int64_t)gridDim.x * 256) {
-    const int64_t i = e / kPreK, c = e % kPreK;
+    const int64_t i = e % n, c = e / n;  // the partials run along i
     double acc = 0.0;
-    for (int32_t sp = 0; sp < splits; ++sp) acc += (double)P[((int64_t)sp * n + i) * ldpm + c];
+    for (int32_t sp = 0; sp < splits; ++sp) acc += (double)P[((int64_t)sp * ldpm + c) * ldpi + i];
     const float y = (float)(2.0 * acc);
-    Y[e] = y;
+    Y[i * kPreK + c] = y;
     Yt[c * ldyt + i] = y;
   }
 }
@@ -1068,12 +1068,12 @@ int launch_pre_omega(float *X, int64_t ldx, int64_t n, hipStream_t s) {
   return (int)hipGetLastError();
 }
 
-int launch_pre_reduce(const float *P, int64_t ldpm, int32_t splits, int64_t n, float *Y, float *Yt, int64_t ldyt,
-                      hipStream_t s) {
+int launch_pre_reduce(const float *P, int64_t ldpm, int64_t ldpi, int32_t splits, int64_t n, float *Y, float *Yt,
+                      int64_t ldyt, hipStream_t s) {
   if (ldyt < n) return (int)hipErrorInvalidValue;
   const int64_t total = n * kPreK;
   const int grid = (int)std::min<int64_t>((total + 255) / 256, 4096);
-  hipLaunchKernelGGL(k_pre_reduce, dim3(grid), dim3(256), 0, s, P, ldpm, splits, n, Y, Yt, ldyt);
+  hipLaunchKernelGGL(k_pre_reduce, dim3(grid), dim3(256), 0, s, P, ldpm, ldpi, splits, n, Y, Yt, ldyt);
   return (int)hipGetLastError();
 }
 

@@ -183,47 +183,13 @@ __global__ __launch_bounds__(512) void k_syrk(const float *__restrict__ L, int64
 //   written too.  k_mm16<false>: all tiles of C = A B (the sketch Y = L S).
 // --------------------------------------------------------------------------
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
-typedef unsigned int u4v __attribute__((ext_vector_type(4)));
 
 constexpr int kSplitTile = 64;
 constexpr int kMmStep = 16;                  // periods of a stage
 constexpr int kMmGroup = 4;                  // stages per padding unit (64 periods)
 constexpr int kMmFlush = 16;                 // stages between float64 flushes (256 periods)
-constexpr int kFrag = 512;                   // bfloat16 entries of a fragment
-constexpr int kPanelStage = 12 * kFrag;      // [plane][row group] of one panel
 constexpr int kMmRing = 6;                   // stages of both panels in LDS (144 KiB)
 constexpr int kTileElems = kTile * kTile;
-
-__device__ __forceinline__ uint32_t rne_bf16(float f) {  // finite inputs
-  const uint32_t u = __float_as_uint(f);
-  return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
-}
-__device__ __forceinline__ float bf16_f32(uint32_t h) { return __uint_as_float(h << 16); }
-
-// h, m, l words of eight consecutive contraction entries
-__device__ __forceinline__ void split8(const float (&v)[8], u4v (&w)[3]) {
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    uint32_t h2[2], m2[2], l2[2];
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      const float x = v[2 * q + e];
-      h2[e] = rne_bf16(x);
-      const float r1 = x - bf16_f32(h2[e]);
-      m2[e] = rne_bf16(r1);
-      l2[e] = rne_bf16(r1 - bf16_f32(m2[e]));
-    }
-    w[0][q] = h2[0] | (h2[1] << 16);
-    w[1][q] = m2[0] | (m2[1] << 16);
-    w[2][q] = l2[0] | (l2[1] << 16);
-  }
-}
-
-// Fragment (row group g, stage st) of a matrix of `stages` stages: plane 0;
-// plane p follows at 4 p fragments.
-__device__ __forceinline__ uint16_t *frag_ptr(uint16_t *P, int64_t g, int64_t st, int64_t stages) {
-  return P + ((g >> 2) * stages + st) * kPanelStage + (g & 3) * kFrag;
-}
 
 __global__ __launch_bounds__(256) void k_split_t(const float *__restrict__ L, int64_t n, int64_t T, int64_t ld,
                                                  uint16_t *__restrict__ P, int64_t stages) {
@@ -293,39 +259,6 @@ __global__ __launch_bounds__(256) void k_split_k(const float *__restrict__ X, in
     uint16_t *out = frag_ptr(P, g, st, stages) + 8 * lane;
 #pragma unroll
     for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<u4v *>(out + pl * 4 * kFrag) = w[pl];
-  }
-}
-
-// Three planes of a matrix whose rows are already contiguous along the
-// contraction (column j of S: S[t + j lds], t < T): P_pl[j ldt + t], zeros
-// for t in [T, ldt).  A thread splits 8 consecutive entries.
-__global__ __launch_bounds__(256) void k_split_rows(const float *__restrict__ X, int64_t rows, int64_t T,
-                                                    int64_t ldx, uint16_t *__restrict__ P, int64_t ldt,
-                                                    int64_t plane) {
-  const int64_t groups = ldt / 8;
-  for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < rows * groups; e += (int64_t)gridDim.x * 256) {
-    const int64_t j = e / groups, t0 = 8 * (e % groups);
-    uint32_t hw[4], mw[4], lw[4];
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      uint32_t h2[2], m2[2], l2[2];
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        const int64_t t = t0 + 2 * w + q;
-        const float v = (t < T) ? X[j * ldx + t] : 0.f;
-        h2[q] = rne_bf16(v);
-        const float r1 = v - bf16_f32(h2[q]);
-        m2[q] = rne_bf16(r1);
-        l2[q] = rne_bf16(r1 - bf16_f32(m2[q]));
-      }
-      hw[w] = h2[0] | (h2[1] << 16);
-      mw[w] = m2[0] | (m2[1] << 16);
-      lw[w] = l2[0] | (l2[1] << 16);
-    }
-    const int64_t off = j * ldt + t0;
-    *reinterpret_cast<u4v *>(P + off) = u4v{hw[0], hw[1], hw[2], hw[3]};
-    *reinterpret_cast<u4v *>(P + plane + off) = u4v{mw[0], mw[1], mw[2], mw[3]};
-    *reinterpret_cast<u4v *>(P + 2 * plane + off) = u4v{lw[0], lw[1], lw[2], lw[3]};
   }
 }
 
@@ -693,12 +626,15 @@ size_t gemm_split_bytes(int64_t m, int64_t ncols, int64_t K) {
          mm16_partial_bytes(false, m, ncols, K);
 }
 
-int launch_split_rows(const float *X, int64_t rows, int64_t T, int64_t ldx, uint16_t *P, int64_t ldt,
-                      int64_t plane, hipStream_t s) {
-  if (ldt % 8 != 0 || ldt < T) return (int)hipErrorInvalidValue;
-  const int64_t groups = rows * (ldt / 8);
-  const int sgrid = (int)std::min<int64_t>((groups + 255) / 256, 65536);
-  hipLaunchKernelGGL(k_split_rows, dim3(sgrid), dim3(256), 0, s, X, rows, T, ldx, P, ldt, plane);
+int64_t split_stages(int64_t T) { return mm16_stages(T); }
+int64_t split_k_elems(int64_t rows, int64_t T) { return panel_elems(rows, T); }
+
+int launch_split_k(const float *X, int64_t rows, int64_t T, int64_t ldx, uint16_t *P, hipStream_t s) {
+  const int64_t stages = mm16_stages(T);
+  const int64_t groups = (rows + kTile - 1) / kTile * (kTile / 32);
+  const int vec = (ldx % 4) == 0 && (reinterpret_cast<uintptr_t>(X) % 16) == 0;
+  hipLaunchKernelGGL(k_split_k, dim3((unsigned)((stages + 15) / 16), (unsigned)groups), dim3(256), 0, s, X, rows, T,
+                     ldx, P, stages, vec);
   return (int)hipGetLastError();
 }
 
@@ -707,11 +643,7 @@ int launch_gemm_split(const float *A, int64_t lda, const float *B, int64_t ldb, 
   const int64_t stages = mm16_stages(K);
   uint16_t *PB = planes + panel_elems(M, K);
   if (launch_split_t(A, M, K, lda, planes, s)) return (int)hipErrorLaunchFailure;
-  const int64_t groups = (N + kTile - 1) / kTile * (kTile / 32);
-  const int vec = (ldb % 4) == 0 && (reinterpret_cast<uintptr_t>(B) % 16) == 0;
-  hipLaunchKernelGGL(k_split_k, dim3((unsigned)((stages + 15) / 16), (unsigned)groups), dim3(256), 0, s, B, N, K, ldb,
-                     PB, stages, vec);
-  if (hipGetLastError() != hipSuccess) return (int)hipErrorLaunchFailure;
+  if (launch_split_k(B, N, K, ldb, PB, s)) return (int)hipErrorLaunchFailure;
   Mm16 m{};
   m.PA = planes;
   m.PB = PB;
