@@ -1055,7 +1055,8 @@ SketchLayout sketch_layout(int64_t n, int64_t T, int64_t k, int64_t ell, bool ne
   l.off_frob = take(sizeof(double) * kFrobParts);
   l.off_gamma = take(sizeof(double) * 4);
   // bfloat16 planes of L and S for the sketch product (Gaussian sketch)
-  l.off_planes = gemm ? take(npga::gemm_split_bytes(n, k, T)) : 0;
+  // and, after it, the slots of the tridiagonalisation
+  l.off_planes = take(std::max(gemm ? npga::gemm_split_bytes(n, k, T) : 0, npga::tri_chip_bytes(k)));
   l.total = off;
   return l;
 }
@@ -1155,32 +1156,55 @@ int npga_sketch_str_ex(const float *L, int64_t n, int64_t T, int64_t ldl, const 
   // truncation stage: eigenpairs of G = Y^T Y
   LAUNCHCHK(npga::launch_gram_f64(Y, lay.ldy, n, k, s.A, stream));
   LAUNCHCHK(npga::launch_frob(Y, lay.ldy, n, k, frob, kFrobParts, stream));
-  LAUNCHCHK(npga::launch_tridiag(s, stream));
-  LAUNCHCHK(npga::launch_bisect(s, m_eig, stream));
-  int64_t ell = ell_cap;
-  if (so->ell_rule == NPGA_ELL_KNEE || so->sketch == NPGA_SKETCH_COUNT) {
-    if (so->ell_rule == NPGA_ELL_KNEE) LAUNCHCHK(npga::launch_knee(s.lam, m_eig, so->knee_tau, so->knee_rho, ell_dev, stream));
-    double *h = reinterpret_cast<double *>(&pin[3]);
-    HIPCHK(hipMemcpyAsync(h, gdev + 2, 2 * sizeof(double), hipMemcpyDeviceToHost, stream));
-    HIPCHK(hipStreamSynchronize(stream));
-    if (so->sketch == NPGA_SKETCH_COUNT && *reinterpret_cast<int32_t *>(h + 1) != 0) return NPGA_ERR_INVALID;
-    if (so->ell_rule == NPGA_ELL_KNEE) {
-      ell = *reinterpret_cast<int64_t *>(h);
-      if (ell_out) *ell_out = ell;
-      if (ell < 1) return NPGA_ERR_INVALID;  // no index passes the knee rule
+  // the tridiagonalisation in one launch; should a wait inside it run out,
+  // that launch's columns and what follows once more, by launches
+  void *slots = base + lay.off_planes;
+  double *h = reinterpret_cast<double *>(&pin[3]);  // [0, 1]: gamma; or ell, bad input; [2]: the launch's flag
+  bool by_chip = g_loop_wait_us >= 0;
+  if (by_chip)
+    LAUNCHCHK(npga::launch_tridiag_chip(s, slots, 100 * (long long)g_loop_wait_us, stream));
+  else
+    LAUNCHCHK(npga::launch_tridiag(s, 0, k, stream));
+  for (;;) {
+    auto again = [&]() -> bool {  // after a synchronisation; true: the launch gave up
+      uint64_t flag = 0;
+      std::memcpy(&flag, h + 2, sizeof(flag));
+      return by_chip && flag != 0;
+    };
+    if (by_chip) HIPCHK(hipMemcpyAsync(h + 2, slots, sizeof(double), hipMemcpyDeviceToHost, stream));
+    LAUNCHCHK(npga::launch_bisect(s, m_eig, stream));
+    int64_t ell = ell_cap;
+    if (so->ell_rule == NPGA_ELL_KNEE || so->sketch == NPGA_SKETCH_COUNT) {
+      if (so->ell_rule == NPGA_ELL_KNEE)
+        LAUNCHCHK(npga::launch_knee(s.lam, m_eig, so->knee_tau, so->knee_rho, ell_dev, stream));
+      HIPCHK(hipMemcpyAsync(h, gdev + 2, 2 * sizeof(double), hipMemcpyDeviceToHost, stream));
+      HIPCHK(hipStreamSynchronize(stream));
+      if (so->sketch == NPGA_SKETCH_COUNT && *reinterpret_cast<int32_t *>(h + 1) != 0) return NPGA_ERR_INVALID;
+      if (again()) {
+        by_chip = false;
+        LAUNCHCHK(npga::launch_tridiag_resume(s, stream));
+        continue;
+      }
+      if (so->ell_rule == NPGA_ELL_KNEE) {
+        ell = *reinterpret_cast<int64_t *>(h);
+        if (ell_out) *ell_out = ell;
+        if (ell < 1) return NPGA_ERR_INVALID;  // no index passes the knee rule
+      }
     }
+    if (ell_out) *ell_out = ell;
+    LAUNCHCHK(npga::launch_inverse_iter(s, ell, lay.stride, stream));
+    LAUNCHCHK(npga::launch_backtransform(s, ell, V32, stream));
+    // L_eff = Y V_ell (n x ell)
+    LAUNCHCHK(npga::launch_gemm_f32(Y, lay.ldy, V32, k, Leff, ldle, n, ell, k, stream));
+    // ridge stage and singular values
+    LAUNCHCHK(npga::launch_finish_str(s, ell, n, so->ridge_coef, frob, kFrobParts, sigma, gdev, so->kappa_tar,
+                                      stream));
+    HIPCHK(hipMemcpyAsync(h, gdev, 2 * sizeof(double), hipMemcpyDeviceToHost, stream));
+    HIPCHK(hipStreamSynchronize(stream));
+    if (!again()) break;
+    by_chip = false;
+    LAUNCHCHK(npga::launch_tridiag_resume(s, stream));
   }
-  if (ell_out) *ell_out = ell;
-  LAUNCHCHK(npga::launch_inverse_iter(s, ell, lay.stride, stream));
-  LAUNCHCHK(npga::launch_backtransform(s, ell, V32, stream));
-  // L_eff = Y V_ell (n x ell)
-  LAUNCHCHK(npga::launch_gemm_f32(Y, lay.ldy, V32, k, Leff, ldle, n, ell, k, stream));
-  // ridge stage and singular values
-  LAUNCHCHK(npga::launch_finish_str(s, ell, n, so->ridge_coef, frob, kFrobParts, sigma, gdev, so->kappa_tar,
-                                    stream));
-  double *h = reinterpret_cast<double *>(&pin[3]);
-  HIPCHK(hipMemcpyAsync(h, gdev, 2 * sizeof(double), hipMemcpyDeviceToHost, stream));
-  HIPCHK(hipStreamSynchronize(stream));
   *gamma_out = h[0];
   if (!is_fin(h[0])) return NPGA_ERR_NUMERIC;
   return NPGA_OK;

@@ -8,10 +8,12 @@
 // matrix G = Y^T Y (k x k).  It is computed by a dense symmetric
 // eigensolver written for the GPU (float64 throughout):
 //   1. G by float64 MFMA (exact products of the float32 entries of Y);
-//   2. Householder tridiagonalisation G = Q T Q^T, one reflector per step
-//      (a one-workgroup kernel forms the reflector, a grid kernel applies the
+//   2. Householder tridiagonalisation G = Q T Q^T, one reflector per step:
+//      while the trailing matrix is larger than the chip's registers, a
+//      one-workgroup kernel forms the reflector and a grid kernel applies the
 //      previous rank-2 update to the trailing columns and forms the next
-//      symmetric matrix-vector product in the same pass);
+//      symmetric matrix-vector product in the same pass; then one launch for
+//      all that is left (npga_tri.hip);
 //   3. the ell largest eigenvalues of T by bisection on Sturm counts;
 //   4. their eigenvectors of T by inverse iteration (tridiagonal LU with
 //      partial pivoting);
@@ -899,11 +901,11 @@ int launch_frob(const float *Y, int64_t ldy, int64_t n, int64_t k, double *part,
   return (int)hipGetLastError();
 }
 
-int launch_tridiag(const SketchState &s, hipStream_t st) {
+int launch_tridiag(const SketchState &s, int64_t i_begin, int64_t i_end, hipStream_t st) {
   const int64_t k = s.k;
   const int64_t nb = (k + kTT - 1) / kTT;
   const int64_t tiles_max = nb * (nb + 1) / 2;
-  for (int64_t i = 0; i < k; ++i) {
+  for (int64_t i = i_begin; i < i_end; ++i) {
     hipLaunchKernelGGL(k_tri_small, dim3(1), dim3(kTriThreads), 0, st, s, i);
     if (i + 1 < k) {
       const int64_t nbr = nb - (i + 1) / kTT;
