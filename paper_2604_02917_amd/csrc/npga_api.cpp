@@ -1166,8 +1166,8 @@ int npga_sketch_str_ex(const float *L, int64_t n, int64_t T, int64_t ldl, const 
   else
     LAUNCHCHK(npga::launch_tridiag(s, 0, k, stream));
   for (;;) {
+    uint64_t flag = 0;
     auto again = [&]() -> bool {  // after a synchronisation; true: the launch gave up
-      uint64_t flag = 0;
       std::memcpy(&flag, h + 2, sizeof(flag));
       return by_chip && flag != 0;
     };
@@ -1182,7 +1182,7 @@ int npga_sketch_str_ex(const float *L, int64_t n, int64_t T, int64_t ldl, const 
       if (so->sketch == NPGA_SKETCH_COUNT && *reinterpret_cast<int32_t *>(h + 1) != 0) return NPGA_ERR_INVALID;
       if (again()) {
         by_chip = false;
-        LAUNCHCHK(npga::launch_tridiag_resume(s, stream));
+        LAUNCHCHK(npga::launch_tridiag_resume(s, slots, flag, stream));
         continue;
       }
       if (so->ell_rule == NPGA_ELL_KNEE) {
@@ -1203,7 +1203,7 @@ int npga_sketch_str_ex(const float *L, int64_t n, int64_t T, int64_t ldl, const 
     HIPCHK(hipStreamSynchronize(stream));
     if (!again()) break;
     by_chip = false;
-    LAUNCHCHK(npga::launch_tridiag_resume(s, stream));
+    LAUNCHCHK(npga::launch_tridiag_resume(s, slots, flag, stream));
   }
   *gamma_out = h[0];
   if (!is_fin(h[0])) return NPGA_ERR_NUMERIC;

@@ -82,6 +82,7 @@ struct Waiter {
 template <int A, int B>
 __device__ __forceinline__ bool get_words(const unsigned long long *p, uint32_t i, uint32_t a_stride, int a_last,
                                           uint32_t b_stride, uint32_t tag, float (&out)[A][B], Waiter &w) {
+  if (w.ticks == 0) return false;  // no time to wait: the first exchange is where it ends
   for (;;) {
     unsigned long long v[A][B];
 #pragma unroll

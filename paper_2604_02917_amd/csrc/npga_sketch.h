@@ -33,15 +33,16 @@ int launch_frob(const float *Y, int64_t ldy, int64_t n, int64_t k, double *part,
 size_t tri_scratch_bytes(int64_t k);
 // Columns i_begin .. i_end - 1 with a launch per stage of a step.
 int launch_tridiag(const SketchState &s, int64_t i_begin, int64_t i_end, hipStream_t st);
-// All columns, the last kTriMax of them in one launch with the trailing
-// matrix in registers (npga_tri.hip).  slots: tri_chip_bytes(k) bytes whose
-// first word is nonzero afterwards if that launch could not run to its end
-// (a wait between its workgroups lasted longer than `ticks` of the 100 MHz
-// counter); launch_tridiag_resume then does those columns again.
-constexpr int64_t kTriMax = 3072;
+// All columns, the last kTriMax of them with the trailing matrix on the chip
+// (npga_tri.hip).  slots: tri_chip_bytes(k) bytes whose first word is nonzero
+// afterwards if a launch could not run to its end (a wait between its
+// workgroups lasted longer than `ticks` of the 100 MHz counter);
+// launch_tridiag_resume, given that word, then does its columns and what
+// follows with a launch per stage.
+constexpr int64_t kTriMax = 3584;
 size_t tri_chip_bytes(int64_t k);
 int launch_tridiag_chip(const SketchState &s, void *slots, long long ticks, hipStream_t st);
-int launch_tridiag_resume(const SketchState &s, hipStream_t st);
+int launch_tridiag_resume(const SketchState &s, void *slots, uint64_t flag, hipStream_t st);
 int launch_bisect(const SketchState &s, int64_t ell, hipStream_t st);
 int launch_inverse_iter(const SketchState &s, int64_t ell, int64_t stride, hipStream_t st);
 int launch_backtransform(const SketchState &s, int64_t ell, float *V32, hipStream_t st);

@@ -19,18 +19,23 @@
 // word that no arithmetic produces; a reader waits for the entries it needs.
 // Entries are stored and read at device scope.  Every wait is bounded: a
 // workgroup whose wait runs out raises the abort word and all leave; the
-// upper triangle still holds the trailing matrix (the reflectors go to the
-// lower one), and the caller goes on with a launch per stage.
+// upper triangle (or what the launch before left) still holds the trailing
+// matrix, and the caller goes on with a launch per stage.
 //
-// Bound by the exchange (about 2 us) and by the redundant vector work of a
-// step (its reductions over the workgroup).  The operations are those of
-// npga_sketch.hip, all in float64.  Measured, all columns: k = 403 4.9 ms by
-// launches, 2.25 ms here (5.6 us a column); k = 4096 80 ms by launches, 59.5
-// ms here, of which the last 3072 columns 28 ms.
+// The operations are those of npga_sketch.hip, all in float64.  Bound by a
+// step's latency: the exchange (about 1.2 us) and three sums over the
+// workgroup, one after the other.  Measured, us a column: 2.2 up to order
+// 512, 2.3 to 1024, 2.9 to 2048, 5.9 from 3584 to 2048 (the registers do not
+// hold those, and some rows stand in LDS); by launches 12 at order 403 and 16
+// to 33 at 2048 to 4096.  Without the wait before the first look at the slots
+// (kNap) the same columns took 3.9, 4.5, 5.0 and 7.7.  All columns of a k = 403
+// sketch: 4.9 ms by launches, 0.87 ms here; k = 4096: 80 ms by launches, 32 ms
+// here, of which the first 512 columns, still by launches, 17 ms.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cstdint>
+#include <type_traits>
 
 #include "npga_device.h"
 #include "npga_internal.h"
@@ -43,55 +48,69 @@ namespace {
 constexpr int kTriT = 512;  // threads of a workgroup: eight wavefronts
 constexpr unsigned long long kTriUnset = 0xFFFFDEAD5EAF0001ull;
 
+// One launch: the first n columns of a symmetric matrix of order m that
+// stands at row and column i0 of the whole.
 struct TriRun {
-  int64_t i0;        // first column
-  int64_t m;         // order of the trailing matrix: k - i0
-  int64_t lds;       // doubles between slots (whole 256-byte lines: a line never holds two steps)
-  unsigned long long *p, *x;  // slots of p and of the next row
-  unsigned long long *head;   // abort word
+  int64_t i0, m, n;
+  const double *src;  // its rows (m of them, lsrc apart)
+  int64_t lsrc;
+  const double *p0, *v0;  // p and v of the column before (i0 > 0)
+  unsigned long long *p, *x;  // slots of p and of the next row, one for each column
+  int64_t lds;  // words between slots (a multiple of 32: no 256-byte line holds two columns' words)
+  double *rest, *vrest;  // n < m: the trailing matrix of order m - n and its v afterwards
+  unsigned long long *head;  // abort word: 0, or 1 + the number of the launch that gave up
+  unsigned long long stage;
   long long ticks;
 };
 
-// Sum over the workgroup; every thread gets the same bits.
-__device__ __forceinline__ double tri_sum(double v, double (&buf)[2][8], int &par) {
+// Sum over the workgroup; every thread gets the same bits.  buf: its own
+// eight words for each of a step's sums, so one barrier is enough.
+__device__ __forceinline__ double tri_sum(double v, double *buf) {
   v = wave_sum_f64(v);
-  if ((threadIdx.x & 63) == 0) buf[par][threadIdx.x >> 6] = v;
+  if ((threadIdx.x & 63) == 0) buf[threadIdx.x >> 6] = v;
   __syncthreads();
-  double t = buf[par][0];
-#pragma unroll
-  for (int w = 1; w < 8; ++w) t += buf[par][w];
-  par ^= 1;
-  return t;
+  return ((buf[0] + buf[1]) + (buf[2] + buf[3])) + ((buf[4] + buf[5]) + (buf[6] + buf[7]));
 }
 
-// Sums over the wavefront of N (4 or 8) values per lane; lane l returns the
-// total of value l N / 64.
-template <int N>
-__device__ __forceinline__ double wave_reduce_n(double (&t)[N], int lane) {
-  int mask = 32;
-#pragma unroll
-  for (int half = N / 2; half >= 1; half >>= 1) {
-    const bool hi = (lane & mask) != 0;
-#pragma unroll
-    for (int q = 0; q < N / 2; ++q) {
-      if (q < half) {
-        const double send = hi ? t[q] : t[q + half];
-        const double keep = hi ? t[q + half] : t[q];
-        t[q] = keep + __shfl_xor(send, mask);
-      }
-    }
-    mask >>= 1;
+// a: lanes whose bit SWAP (32 or 16) is clear get a + its partner's a, the
+// others b + its partner's b.
+template <int SWAP>
+__device__ __forceinline__ double swap_add(double a, double b) {
+  const unsigned long long ua = (unsigned long long)__double_as_longlong(a);
+  const unsigned long long ub = (unsigned long long)__double_as_longlong(b);
+  typedef unsigned u2 __attribute__((ext_vector_type(2)));
+  u2 lo, hi;
+  if constexpr (SWAP == 32) {
+    lo = __builtin_amdgcn_permlane32_swap((unsigned)ua, (unsigned)ub, false, false);
+    hi = __builtin_amdgcn_permlane32_swap((unsigned)(ua >> 32), (unsigned)(ub >> 32), false, false);
+  } else {
+    lo = __builtin_amdgcn_permlane16_swap((unsigned)ua, (unsigned)ub, false, false);
+    hi = __builtin_amdgcn_permlane16_swap((unsigned)(ua >> 32), (unsigned)(ub >> 32), false, false);
   }
-  double r = t[0];
-#pragma unroll
-  for (int off = 64 / (2 * N); off > 2; off >>= 1) r += __shfl_xor(r, off);
-  r += dpp_f64<0x4E>(r);  // swap pairs
-  r += dpp_f64<0xB1>(r);  // swap neighbours
-  return r;
+  return __longlong_as_double((long long)(((unsigned long long)hi.x << 32) | lo.x)) +
+         __longlong_as_double((long long)(((unsigned long long)hi.y << 32) | lo.y));
+}
+
+// Sums over the wavefront of four values per lane; the lanes of row l / 16
+// return the total of value l / 16.
+__device__ __forceinline__ double wave_sum4(double t0, double t1, double t2, double t3) {
+  double v = swap_add<16>(swap_add<32>(t0, t2), swap_add<32>(t1, t3));
+  v += dpp_f64<0x128>(v);  // rotate the row by 8
+  v += dpp_f64<0x124>(v);  // by 4
+  v += dpp_f64<0x4E>(v);   // swap pairs
+  v += dpp_f64<0xB1>(v);   // swap neighbours
+  return v;
 }
 
 __device__ __forceinline__ unsigned long long tri_get(const unsigned long long *p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// p plus off bytes
+__device__ __forceinline__ const unsigned long long *tri_at(const unsigned long long *p, unsigned off) {
+  return reinterpret_cast<const unsigned long long *>(reinterpret_cast<const char *>(p) + off);
+}
+__device__ __forceinline__ unsigned long long *tri_at(unsigned long long *p, unsigned off) {
+  return reinterpret_cast<unsigned long long *>(reinterpret_cast<char *>(p) + off);
 }
 __device__ __forceinline__ void tri_put(unsigned long long *p, double v) {
   __hip_atomic_store(p, (unsigned long long)__double_as_longlong(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -100,173 +119,240 @@ __device__ __forceinline__ void tri_put(unsigned long long *p, double v) {
 }  // namespace
 
 // Thread t holds columns t + 512 j (j < SL) of its workgroup's rows me + W q
-// (q < ROWS); all indices relative to i0.
-template <int SL, int ROWS>
+// (q < LR + RR), W a power of two up to 256; all indices relative to i0.  The
+// first LR rows, which are finished first, stand in LDS, the others in
+// registers.  A loop for each 512 columns: slots and rows that are finished
+// before it begins are left out of it.
+template <int SL, int RR, int LR, int W, int JEND>
 __global__ __launch_bounds__(kTriT) void k_tri_chip(SketchState s, TriRun a) {
-  __shared__ double vl[SL * kTriT], wl[SL * kTriT];
-  __shared__ double sums[2][8], rowsum[8][16];
-  __shared__ double x0s;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int W = gridDim.x, me = blockIdx.x, m = (int)a.m;
+  constexpr int ROWS = RR + LR;
+  constexpr int ROWS4 = (ROWS + 3) / 4 * 4;
+  // x 64 clocks, see below; the best of 12 to 40, flat within 2 around it
+  constexpr int kNap = SL <= 2 ? 13 : SL == 4 ? 16 : 18;
+  extern __shared__ double alds[];  // LR x SL x 512
+  __shared__ double sums[2][8], rowsum[ROWS4][8];
+  __shared__ double2 own[ROWS4];  // v and w at the own rows
+  __shared__ double pds, x0s;
+  int tid = threadIdx.x;
+  const int lane = tid & 63, wave = tid >> 6;
+  const int me = blockIdx.x, m = (int)a.m;
   const int64_t k = s.k, i0 = a.i0;
-  int par = 0;
-  double A[ROWS][SL], v[SL];
+  if (__syncthreads_or(tri_get(a.head) != 0ull)) return;
+  double A[RR][SL], v[SL];
 #pragma unroll
   for (int q = 0; q < ROWS; ++q) {
-    const int64_t lr = std::min(me + W * q, m - 1);
+    const double *row = a.src + std::min(me + W * q, m - 1) * a.lsrc;
+    asm volatile("" : "+v"(tid));
 #pragma unroll
     for (int j = 0; j < SL; ++j) {
-      const int64_t c = std::min(tid + kTriT * j, m - 1);
-      A[q][j] = s.A[(i0 + c) + (i0 + lr) * k];
+      const double e = row[(unsigned)std::min(tid + kTriT * j, m - 1)];
+      if (q < LR)
+        alds[(q * SL + j) * kTriT + tid] = e;
+      else
+        A[q - LR][j] = e;
     }
   }
+  if (tid < ROWS4) own[tid] = double2{0.0, 0.0};
 #pragma unroll
   for (int j = 0; j < SL; ++j) {
     const int c = tid + kTriT * j;
-    v[j] = (i0 > 0 && c < m) ? s.vcur[i0 + c] : 0.0;
+    v[j] = (i0 > 0 && c < m) ? a.v0[c] : 0.0;
   }
   double tau = i0 > 0 ? s.tau[i0 - 1] : 0.0;
+  __syncthreads();                          // own
 
-  for (int st = 0; st < m; ++st) {
-    const int js = st >> 9;  // slots below are finished
-    const unsigned long long *ps = a.p + (int64_t)st * a.lds, *xs = a.x + (int64_t)st * a.lds;
-    unsigned long long pb[SL], xb[SL], pd;
-    bool lost = false;
-    for (long long t0 = 0;;) {
-      pd = tri_get(ps + st);
-      bool ok = pd != kTriUnset;
+  // columns 512 JS .. 512 JS + 511
+  auto columns = [&](auto js_) __attribute__((always_inline)) {
+    constexpr int JS = decltype(js_)::value;
+    constexpr int Q0 = kTriT / W * JS / 4 * 4;  // rows below are finished
+    const int end = std::min((int)a.n, kTriT * (JS + 1));
+    for (int st = kTriT * JS; st < end; ++st) {
+      // nothing derived from tid is worth a register for longer than a step
+      asm volatile("" : "+v"(tid));
+      const unsigned long long *ps = a.p + (int64_t)st * a.lds, *xs = a.x + (int64_t)st * a.lds;
+      unsigned long long pb[SL], xb[SL];
+      bool lost = st > 0 && a.ticks == 0;  // no time to wait: the first exchange is where it ends
+      // A look that comes too early costs a round trip and holds up the words
+      // on their way, so the first one is made when they are due.
+      __builtin_amdgcn_s_sleep(kNap);
+      for (long long t0 = 0;;) {  // (a lost wait looks once more, and leaves)
+        unsigned off = (unsigned)tid * 8u;
+        asm volatile("" : "+v"(off));  // keeps the addresses out of registers
 #pragma unroll
-      for (int j = 0; j < SL; ++j) {
-        if (j < js) continue;
-        const int c = std::max(st, std::min(tid + kTriT * j, m - 1));
-        pb[j] = tri_get(ps + c);
-        xb[j] = tri_get(xs + c);
-      }
-#pragma unroll
-      for (int j = 0; j < SL; ++j)
-        if (j >= js) ok = ok && pb[j] != kTriUnset && xb[j] != kTriUnset;
-      if (ok) break;
-      if (t0 == 0) {
-        t0 = wall_clock64();
-      } else if (tri_get(a.head) != 0ull || wall_clock64() - t0 >= a.ticks) {
-        lost = true;
-        break;
-      }
-    }
-    double w[SL], x[SL], dot = 0.0;
-#pragma unroll
-    for (int j = 0; j < SL; ++j) {
-      if (j < js) continue;
-      w[j] = __longlong_as_double((long long)pb[j]);
-      x[j] = __longlong_as_double((long long)xb[j]);
-      const int c = tid + kTriT * j;
-      if (c >= st && c < m) dot = fma(w[j], v[j], dot);
-    }
-    if (lost) dot = __longlong_as_double(0x7FF8000000000000ll);
-    const double pv = tri_sum(dot, sums, par);
-    if (!(pv == pv)) {  // a wait ran out here (or the data are not numbers): everybody leaves
-      if (tid == 0) __hip_atomic_store(a.head, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      return;
-    }
-    const double half = 0.5 * tau * pv;
-    const double ws = __longlong_as_double((long long)pd) - half;  // w at row i, where v is 1
-    double xn = 0.0;
-#pragma unroll
-    for (int j = 0; j < SL; ++j) {
-      if (j < js) continue;
-      const int c = tid + kTriT * j;
-      const bool in = c >= st && c < m;
-      w[j] = in ? w[j] - half * v[j] : 0.0;
-      x[j] = in ? x[j] - (v[j] * ws + w[j]) : 0.0;
-      vl[c] = v[j];
-      wl[c] = w[j];
-      if (c == st && me == 0) s.d[i0 + st] = x[j];
-      if (c == st + 1) x0s = x[j];
-      if (c >= st + 2) xn = fma(x[j], x[j], xn);
-    }
-    if (st + 1 == m) break;
-    const double xn2 = tri_sum(xn, sums, par);  // its barrier also publishes vl, wl and x0s
-    const double x0 = x0s;
-    double beta = x0, scale = 0.0;
-    tau = 0.0;
-    if (xn2 > 0.0) {
-      beta = -copysign(sqrt(x0 * x0 + xn2), x0);
-      tau = (beta - x0) / beta;
-      scale = 1.0 / (x0 - beta);
-    }
-    double vn[SL];
-    const bool writes = me == st % W;
-#pragma unroll
-    for (int j = 0; j < SL; ++j) {
-      if (j < js) {
-        vn[j] = 0.0;
-        continue;
-      }
-      const int c = tid + kTriT * j;
-      vn[j] = (c == st + 1) ? 1.0 : ((c >= st + 2 && tau != 0.0) ? x[j] * scale : 0.0);
-      if (writes && c > st && c < m) s.A[(i0 + c) + (i0 + st) * k] = vn[j];
-    }
-    if (me == 0 && tid == 0) {
-      s.e[i0 + st] = beta;
-      s.tau[i0 + st] = tau;
-    }
-    // own rows, RB at a time: the update, the product with v_i, its sum
-    constexpr int RB = ROWS % 8 ? 4 : 8;
-#pragma unroll
-    for (int q0 = 0; q0 < ROWS; q0 += RB) {
-      if (me + W * (q0 + RB - 1) <= st) continue;  // finished rows (their sums are not read)
-      double acc[RB];
-#pragma unroll
-      for (int u = 0; u < RB; ++u) {
-        const int q = q0 + u, lr = me + W * q;
-        acc[u] = 0.0;
-        if (lr <= st || lr >= m) continue;
-        const double vr = vl[lr], wr = wl[lr];
-#pragma unroll
-        for (int j = 0; j < SL; ++j) {
-          if (j < js) continue;
-          A[q][j] -= vr * w[j] + wr * v[j];
-          acc[u] = fma(A[q][j], vn[j], acc[u]);
+        for (int j = JS; j < SL; ++j) {
+          pb[j] = tri_get(tri_at(ps + kTriT * j, off));
+          xb[j] = tri_get(tri_at(xs + kTriT * j, off));
         }
-        if (lr == st + 1) {
-          unsigned long long *xo = a.x + (int64_t)(st + 1) * a.lds;
+        unsigned wait = 0;
 #pragma unroll
-          for (int j = 0; j < SL; ++j) {
+        for (int j = JS; j < SL; ++j) {
+          const int c = tid + kTriT * j;
+          wait |= (unsigned)(c >= st) & (unsigned)(c < m) & ((unsigned)(pb[j] == kTriUnset) | (unsigned)(xb[j] == kTriUnset));
+        }
+        if (lost || !__any((int)wait)) break;
+        if (t0 == 0) {
+          t0 = wall_clock64();
+        } else if (tri_get(a.head) != 0ull || wall_clock64() - t0 >= a.ticks) {
+          lost = true;
+          break;
+        }
+      }
+      double w[SL], x[SL], dot = lost ? __longlong_as_double(0x7FF8000000000000ll) : 0.0;
+#pragma unroll
+      for (int j = JS; j < SL; ++j) {
+        const int c = tid + kTriT * j;
+        w[j] = __longlong_as_double((long long)pb[j]);
+        x[j] = __longlong_as_double((long long)xb[j]);
+        if (j == JS && c == st) pds = w[j];
+        dot = fma((c >= st && c < m) ? w[j] : 0.0, v[j], dot);
+      }
+      const double pv = tri_sum(dot, sums[0]);  // its barrier also publishes pds
+      if (__builtin_amdgcn_readfirstlane(!(pv == pv))) {  // a wait ran out here (or the data are not numbers): everybody leaves
+        if (tid == 0) __hip_atomic_store(a.head, 1 + a.stage, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __builtin_amdgcn_endpgm();  // (a return would have the matrix live on both ways)
+      }
+      const double half = 0.5 * tau * pv;
+      const double ws = pds - half;  // w at row i, where v is 1
+      double xn = 0.0;
+#pragma unroll
+      for (int j = JS; j < SL; ++j) {
+        const int c = tid + kTriT * j;
+        const bool in = c >= st && c < m;
+        w[j] = in ? w[j] - half * v[j] : 0.0;
+        x[j] = in ? x[j] - (v[j] * ws + w[j]) : 0.0;
+        if ((tid & (W - 1)) == me) {  // a column of an own row
+          const int q = tid / W + kTriT / W * j;
+          if (q < ROWS) own[q] = double2{v[j], w[j]};
+        }
+        if (j == JS && c == st && me == 0) s.d[i0 + st] = x[j];
+        if (j <= JS + 1 && c == st + 1) x0s = x[j];
+        const double xt = c >= st + 2 ? x[j] : 0.0;
+        xn = fma(xt, xt, xn);
+      }
+      if (st + 1 == m) __builtin_amdgcn_endpgm();
+      const double xn2 = tri_sum(xn, sums[1]);  // its barrier also publishes own and x0s
+      const double x0 = x0s;
+      const bool refl = xn2 > 0.0;
+      const double nrm = -copysign(sqrt(x0 * x0 + xn2), x0);
+      const double beta = refl ? nrm : x0;
+      tau = refl ? (nrm - x0) / nrm : 0.0;
+      const double scale = refl ? 1.0 / (x0 - nrm) : 0.0;
+#pragma unroll
+      for (int j = JS; j < SL; ++j) {  // v_i
+        const int c = tid + kTriT * j;
+        x[j] = (c == st + 1) ? 1.0 : ((c >= st + 2 && refl) ? x[j] * scale : 0.0);
+      }
+      if (me == st % W) {
+        double *vo = s.A + i0 + (i0 + st) * k;
+#pragma unroll
+        for (int j = JS; j < SL; ++j) {
+          const int c = tid + kTriT * j;
+          if (c > st && c < m) vo[kTriT * j + (unsigned)tid] = x[j];
+        }
+      }
+      if (me == 0 && tid == 0) {
+        s.e[i0 + st] = beta;
+        s.tau[i0 + st] = tau;
+      }
+      // own rows, four at a time: the update, the product with v_i, its sum.
+      // (Rows that are finished or beyond m are carried along; nothing reads them.)
+#pragma unroll
+      for (int q0 = Q0; q0 < ROWS; q0 += 4) {
+        double acc[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int q = q0 + u;
+          if (q >= ROWS) continue;
+          // (two rows' loads from LDS in flight: more cost registers)
+          if (LR > 0 && u % 2 == 0) __builtin_amdgcn_sched_barrier(0);
+          const double2 vw = own[q];
+#pragma unroll
+          for (int j = JS; j < SL; ++j) {
+            double *el = q < LR ? &alds[(q * SL + j) * kTriT + tid] : &A[q < LR ? 0 : q - LR][j];
+            const double e = *el - (vw.x * w[j] + vw.y * v[j]);
+            *el = e;
+            acc[u] = fma(e, x[j], acc[u]);
+          }
+        }
+        const double r = wave_sum4(acc[0], acc[1], acc[2], acc[3]);
+        if ((lane & 15) == 0) rowsum[q0 + (lane >> 4)][wave] = r;
+      }
+      if (me == (st + 1) % W) {  // row st + 1 goes out
+        const int qs = (st + 1) / W;
+        unsigned long long *xo = a.x + (int64_t)(st + 1) * a.lds;
+        unsigned off = (unsigned)tid * 8u;
+        asm volatile("" : "+v"(off)::"memory");  // what stands in LDS is read from there again
+#pragma unroll
+        for (int q = Q0; q < ROWS; ++q) {
+          if (q != qs) continue;
+#pragma unroll
+          for (int j = JS; j < SL; ++j) {
             const int c = tid + kTriT * j;
-            if (j >= js && c > st && c < m) tri_put(xo + c, A[q][j]);
+            const double e = q < LR ? alds[(q * SL + j) * kTriT + tid] : A[q < LR ? 0 : q - LR][j];
+            if (c > st && c < m) tri_put(tri_at(xo + kTriT * j, off), e);
           }
         }
       }
-      const double r = wave_reduce_n<RB>(acc, lane);
-      if (lane % (64 / RB) == 0) rowsum[wave][q0 + lane / (64 / RB)] = r;
-    }
-    __syncthreads();
-    if (tid < ROWS) {
-      const int lr = me + W * tid;
-      double t = rowsum[0][tid];
+      __syncthreads();
+      if (tid < 8 * ROWS4) {
+        const int q = tid >> 3, lr = me + W * q;
+        double t = rowsum[q][tid & 7];
+        t += dpp_f64<0x141>(t);  // mirror the half row (lanes 7 - l)
+        t += dpp_f64<0x4E>(t);
+        t += dpp_f64<0xB1>(t);
+        if ((tid & 7) == 0 && q < ROWS && lr > st && lr < m) tri_put(a.p + (int64_t)(st + 1) * a.lds + lr, tau * t);
+      }
 #pragma unroll
-      for (int u = 1; u < 8; ++u) t += rowsum[u][tid];
-      if (lr > st && lr < m) tri_put(a.p + (int64_t)(st + 1) * a.lds + lr, tau * t);
+      for (int j = JS; j < SL; ++j) v[j] = x[j];
     }
+  };
+  columns(std::integral_constant<int, 0>{});
+  if constexpr (JEND > 1) columns(std::integral_constant<int, 1>{});
+  if constexpr (JEND > 2) columns(std::integral_constant<int, 2>{});
+  if constexpr (JEND > 3) columns(std::integral_constant<int, 3>{});
+  if constexpr (JEND < SL) {
+    const int n = (int)a.n;
+    const int64_t mr = m - n;
 #pragma unroll
-    for (int j = 0; j < SL; ++j) v[j] = vn[j];
+    for (int j = 0; j < SL; ++j) {
+      const int c = tid + kTriT * j;
+      if (c < n || c >= m) continue;
+      if (me == 0) a.vrest[c - n] = v[j];
+#pragma unroll
+      for (int q = 0; q < ROWS; ++q) {
+        const int lr = me + W * q;
+        if (lr >= n && lr < m)
+          a.rest[(c - n) + (lr - n) * mr] = q < LR ? alds[(q * SL + j) * kTriT + tid] : A[q < LR ? 0 : q - LR][j];
+      }
+    }
   }
 }
 
-// Slots unset but the first (p of the step before and row i0; no step before:
-// zeros), the abort word cleared.
-__global__ __launch_bounds__(256) void k_tri_slots(SketchState s, TriRun a) {
-  const int64_t total = a.m * a.lds;
+// Slots unset but the first (p of the column before and row i0; no column
+// before: zeros), the abort word cleared before the first launch.
+__global__ __launch_bounds__(256) void k_tri_slots(TriRun a) {
+  const int64_t total = (a.n + (a.n < a.m ? 1 : 0)) * a.lds;
   for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < total; e += (int64_t)gridDim.x * 256) {
     unsigned long long pv = kTriUnset, xv = kTriUnset;
     if (e < a.m) {
-      pv = a.i0 > 0 ? (unsigned long long)__double_as_longlong(s.p[a.i0 + e]) : 0ull;
-      xv = (unsigned long long)__double_as_longlong(s.A[(a.i0 + e) + a.i0 * s.k]);
+      pv = a.i0 > 0 ? (unsigned long long)__double_as_longlong(a.p0[e]) : 0ull;
+      xv = (unsigned long long)__double_as_longlong(a.src[e]);
     }
     a.p[e] = pv;
     a.x[e] = xv;
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) *a.head = 0ull;
+  if (a.stage == 0 && blockIdx.x == 0 && threadIdx.x == 0) *a.head = 0ull;
+}
+
+// The trailing matrix that a launch left, with its p and v, back where a
+// launch per stage looks for them.
+__global__ __launch_bounds__(256) void k_tri_restore(SketchState s, TriRun a) {
+  const int64_t r = blockIdx.x;
+  for (int64_t c = threadIdx.x; c <= r; c += 256) s.A[(a.i0 + r) + (a.i0 + c) * s.k] = a.src[c + r * a.lsrc];
+  if (threadIdx.x == 0) {
+    s.p[a.i0 + r] = a.p0[r];
+    s.vcur[a.i0 + r] = a.v0[r];
+  }
 }
 
 // One triangle of the trailing matrix copied onto the other, 64 x 64 tiles
@@ -290,33 +376,59 @@ __global__ __launch_bounds__(256) void k_tri_mirror(SketchState s, int64_t i0, i
 
 namespace {
 
+int64_t round32(int64_t v) { return (v + 31) / 32 * 32; }
+
+// The launches for order k.  512 columns a slot, and as few rows to a
+// workgroup as 256 workgroups allow (four are summed together).  Above 2048
+// the registers do not hold everything and a column takes 8 us against 5: as
+// soon as 2048 columns are left the matrix is dealt out again.
 struct TriPlan {
-  int64_t i0, m;
-  int sl, rows, groups;
+  int launches;
+  TriRun run[2];
+  int sl[2];
+  size_t words;
 };
 
-// Registers per thread: SL x ROWS doubles of the matrix, at most 72 of the
-// 128 a thread can hold beside a step's vectors; so 512 columns a slot, and
-// the rows that 256 workgroups need.
-TriPlan tri_plan(int64_t k) {
+TriPlan tri_plan(const SketchState &s, void *slots, long long ticks) {
   TriPlan p{};
-  p.m = std::min<int64_t>(k, kTriMax);
-  p.i0 = k - p.m;
-  p.sl = p.m <= 512 ? 1 : p.m <= 1024 ? 2 : p.m <= 2048 ? 4 : 6;
-  p.rows = p.sl == 6 ? 12 : 16;
-  p.groups = (int)((p.m + p.rows - 1) / p.rows);
+  int64_t m = std::min(s.k, kTriMax), i0 = s.k - m;
+  unsigned long long *w = static_cast<unsigned long long *>(slots), *head = w;
+  w += 32;
+  const double *src = s.A + i0 * (s.k + 1), *p0 = s.p + i0, *v0 = s.vcur + i0;
+  int64_t lsrc = s.k;
+  for (;;) {
+    TriRun &a = p.run[p.launches];
+    const int sl = m <= 512 ? 1 : m <= 1024 ? 2 : m <= 2048 ? 4 : 7;
+    p.sl[p.launches] = sl;
+    a.i0 = i0;
+    a.m = m;
+    a.n = std::min<int64_t>(m, sl == 7 ? m - 2048 : m);
+    a.src = src;
+    a.lsrc = lsrc;
+    a.p0 = p0;
+    a.v0 = v0;
+    a.lds = (int64_t)kTriT * sl;
+    a.head = head;
+    a.stage = (unsigned long long)p.launches;
+    a.ticks = ticks;
+    ++p.launches;
+    const int64_t steps = a.n + (a.n < m ? 1 : 0), mr = m - a.n;
+    a.p = w;
+    a.x = w + steps * a.lds;
+    w += 2 * steps * a.lds;
+    if (mr == 0) break;
+    a.rest = reinterpret_cast<double *>(w);
+    a.vrest = a.rest + round32(mr * mr);
+    w += round32(mr * mr) + round32(mr);
+    src = a.rest;
+    lsrc = mr;
+    p0 = reinterpret_cast<const double *>(a.p + a.n * (a.lds + 1));
+    v0 = a.vrest;
+    i0 += a.n;
+    m = mr;
+  }
+  p.words = (size_t)(w - static_cast<unsigned long long *>(slots));
   return p;
-}
-
-TriRun tri_run(const TriPlan &p, void *slots) {
-  TriRun a{};
-  a.i0 = p.i0;
-  a.m = p.m;
-  a.lds = (p.m + 31) / 32 * 32;
-  a.head = static_cast<unsigned long long *>(slots);
-  a.p = a.head + 32;
-  a.x = a.p + p.m * a.lds;
-  return a;
 }
 
 int mirror(const SketchState &s, int64_t i0, int up, hipStream_t st) {
@@ -328,33 +440,49 @@ int mirror(const SketchState &s, int64_t i0, int up, hipStream_t st) {
 }  // namespace
 
 size_t tri_chip_bytes(int64_t k) {
-  const TriPlan p = tri_plan(k);
-  return sizeof(double) * (size_t)(32 + 2 * p.m * ((p.m + 31) / 32 * 32));
+  SketchState s{};
+  s.k = k;
+  return sizeof(double) * tri_plan(s, nullptr, 0).words;
 }
 
 int launch_tridiag_chip(const SketchState &s, void *slots, long long ticks, hipStream_t st) {
-  const TriPlan p = tri_plan(s.k);
-  TriRun a = tri_run(p, slots);
-  a.ticks = ticks;
-  if (p.i0 > 0) {
-    if (launch_tridiag(s, 0, p.i0, st)) return (int)hipErrorLaunchFailure;
-    if (mirror(s, p.i0, 1, st)) return (int)hipErrorLaunchFailure;
+  const TriPlan p = tri_plan(s, slots, ticks);
+  if (p.run[0].i0 > 0) {
+    if (launch_tridiag(s, 0, p.run[0].i0, st)) return (int)hipErrorLaunchFailure;
+    if (mirror(s, p.run[0].i0, 1, st)) return (int)hipErrorLaunchFailure;
   }
-  hipLaunchKernelGGL(k_tri_slots, dim3(2048), dim3(256), 0, st, s, a);
-  if (hipGetLastError() != hipSuccess) return (int)hipErrorLaunchFailure;
-  switch (p.sl) {
-    case 1: hipLaunchKernelGGL((k_tri_chip<1, 16>), dim3(p.groups), dim3(kTriT), 0, st, s, a); break;
-    case 2: hipLaunchKernelGGL((k_tri_chip<2, 16>), dim3(p.groups), dim3(kTriT), 0, st, s, a); break;
-    case 4: hipLaunchKernelGGL((k_tri_chip<4, 16>), dim3(p.groups), dim3(kTriT), 0, st, s, a); break;
-    default: hipLaunchKernelGGL((k_tri_chip<6, 12>), dim3(p.groups), dim3(kTriT), 0, st, s, a); break;
+  for (int l = 0; l < p.launches; ++l) {
+    const TriRun &a = p.run[l];
+    hipLaunchKernelGGL(k_tri_slots, dim3(2048), dim3(256), 0, st, a);
+    if (hipGetLastError() != hipSuccess) return (int)hipErrorLaunchFailure;
+    const dim3 block(kTriT), narrow((unsigned)std::min<int64_t>(128, a.m)), wide(256);
+    switch (p.sl[l]) {
+      case 1: hipLaunchKernelGGL((k_tri_chip<1, 4, 0, 128, 1>), narrow, block, 0, st, s, a); break;
+      case 2: hipLaunchKernelGGL((k_tri_chip<2, 4, 0, 256, 2>), wide, block, 0, st, s, a); break;
+      case 4: hipLaunchKernelGGL((k_tri_chip<4, 8, 0, 256, 4>), wide, block, 0, st, s, a); break;
+      default: {
+        constexpr int kRows = 5;  // in LDS
+        hipLaunchKernelGGL((k_tri_chip<7, 14 - kRows, kRows, 256, 3>), wide, block,
+                           (unsigned)sizeof(double) * kRows * 7 * kTriT, st, s, a);
+        break;
+      }
+    }
+    if (hipGetLastError() != hipSuccess) return (int)hipErrorLaunchFailure;
   }
-  return (int)hipGetLastError();
+  return 0;
 }
 
-int launch_tridiag_resume(const SketchState &s, hipStream_t st) {
-  const TriPlan p = tri_plan(s.k);
-  if (mirror(s, p.i0, 0, st)) return (int)hipErrorLaunchFailure;
-  return launch_tridiag(s, p.i0, s.k, st);
+int launch_tridiag_resume(const SketchState &s, void *slots, uint64_t flag, hipStream_t st) {
+  const TriPlan p = tri_plan(s, slots, 0);
+  const int l = flag == 2 && p.launches > 1 ? 1 : 0;
+  const TriRun &a = p.run[l];
+  if (l == 0) {
+    if (mirror(s, a.i0, 0, st)) return (int)hipErrorLaunchFailure;
+  } else {
+    hipLaunchKernelGGL(k_tri_restore, dim3((unsigned)a.m), dim3(256), 0, st, s, a);
+    if (hipGetLastError() != hipSuccess) return (int)hipErrorLaunchFailure;
+  }
+  return launch_tridiag(s, a.i0, s.k, st);
 }
 
 }  // namespace npga

@@ -88,3 +88,22 @@ def test_tridiagonal_wait_runs_out(npga, k):
     else:  # few workgroups: their words may be there at the first look
         np.testing.assert_allclose(sg.cpu().numpy(), sg1.cpu().numpy(), rtol=2.0 ** -23)
     assert gam == gam1
+
+
+@pytest.mark.parametrize("k", [2049, 3584 + 64])
+def test_tridiagonal_later_launch_gives_up(npga, k):
+    """Orders whose chain takes more than one launch, with no time to wait.
+    k = 2049: the first launch has one column and needs no wait, the second
+    gives up, so the launches go on from the matrix between the two."""
+    banner(f"tridiagonalisation, bounded wait in a later launch k={k}")
+    L, S, ell = _case(k)
+    Ld, Sd = to_dev(L), to_dev(S)
+    with tri_wait(0):
+        Le, sg, gam = npga.sketch_str(Ld, Sd, ell)
+    with tri_wait(-1):
+        Le1, sg1, gam1 = npga.sketch_str(Ld, Sd, ell)
+    s, s1 = sg.cpu().numpy().astype(np.float64), sg1.cpu().numpy().astype(np.float64)
+    np.testing.assert_allclose(s, s1, rtol=2.0 ** -23)
+    F = Le.cpu().numpy().astype(np.float64)
+    assert np.abs(F @ F.T - np.diag(s * s)).max() <= 1e-5 * s[0] ** 2
+    assert gam == gam1
