@@ -18,10 +18,12 @@
 //     double buffer) only after it has read step s + 1's, which the others
 //     write after reading step s's.
 // Bound by latency: the exchange, the tail's reductions and a barrier or two.
-// Per NPGA step, a launch per step and one launch: n = 64 on Sigma 12 and 4.2
-// us, n = 501 on Sigma 11 and 5.4 us (16 workgroups), n = 1001, T = 403 on L
-// 19 and 10.6 us (14 workgroups); whole solves 3.2 -> 1.34 ms, 4.6 -> 2.2 ms,
-// 16.1 -> 10.7 ms.
+// Per NPGA step, a launch per step and one launch: n = 64 on Sigma 12 and 3.8
+// us, n = 501 on Sigma 11 and 4.9 us (16 workgroups), n = 1001, T = 403 on L
+// 19 and 10.2 us (14 workgroups); whole solves 3.4 -> 1.29 ms, 4.6 -> 2.0 ms,
+// 15.2 -> 9.8 ms.  (Waiting before the first look at the others' words, which
+// halves a column of the tridiagonalisation, gains nothing here: 2 % at n =
+// 501, and a loss on L, where the looks are many and spread.)
 // With one workgroup there is no exchange.  Every wait is bounded: after
 // LoopArgs::wait_ticks a workgroup raises the abort word and leaves, the others
 // follow, the state is that of the last whole iteration, and the host goes

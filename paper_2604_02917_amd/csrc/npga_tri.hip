@@ -72,36 +72,6 @@ __device__ __forceinline__ double tri_sum(double v, double *buf) {
   return ((buf[0] + buf[1]) + (buf[2] + buf[3])) + ((buf[4] + buf[5]) + (buf[6] + buf[7]));
 }
 
-// a: lanes whose bit SWAP (32 or 16) is clear get a + its partner's a, the
-// others b + its partner's b.
-template <int SWAP>
-__device__ __forceinline__ double swap_add(double a, double b) {
-  const unsigned long long ua = (unsigned long long)__double_as_longlong(a);
-  const unsigned long long ub = (unsigned long long)__double_as_longlong(b);
-  typedef unsigned u2 __attribute__((ext_vector_type(2)));
-  u2 lo, hi;
-  if constexpr (SWAP == 32) {
-    lo = __builtin_amdgcn_permlane32_swap((unsigned)ua, (unsigned)ub, false, false);
-    hi = __builtin_amdgcn_permlane32_swap((unsigned)(ua >> 32), (unsigned)(ub >> 32), false, false);
-  } else {
-    lo = __builtin_amdgcn_permlane16_swap((unsigned)ua, (unsigned)ub, false, false);
-    hi = __builtin_amdgcn_permlane16_swap((unsigned)(ua >> 32), (unsigned)(ub >> 32), false, false);
-  }
-  return __longlong_as_double((long long)(((unsigned long long)hi.x << 32) | lo.x)) +
-         __longlong_as_double((long long)(((unsigned long long)hi.y << 32) | lo.y));
-}
-
-// Sums over the wavefront of four values per lane; the lanes of row l / 16
-// return the total of value l / 16.
-__device__ __forceinline__ double wave_sum4(double t0, double t1, double t2, double t3) {
-  double v = swap_add<16>(swap_add<32>(t0, t2), swap_add<32>(t1, t3));
-  v += dpp_f64<0x128>(v);  // rotate the row by 8
-  v += dpp_f64<0x124>(v);  // by 4
-  v += dpp_f64<0x4E>(v);   // swap pairs
-  v += dpp_f64<0xB1>(v);   // swap neighbours
-  return v;
-}
-
 __device__ __forceinline__ unsigned long long tri_get(const unsigned long long *p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -274,7 +244,7 @@ __global__ __launch_bounds__(kTriT) void k_tri_chip(SketchState s, TriRun a) {
             acc[u] = fma(e, x[j], acc[u]);
           }
         }
-        const double r = wave_sum4(acc[0], acc[1], acc[2], acc[3]);
+        const double r = wave_sum4_f64(acc[0], acc[1], acc[2], acc[3]);
         if ((lane & 15) == 0) rowsum[q0 + (lane >> 4)][wave] = r;
       }
       if (me == (st + 1) % W) {  // row st + 1 goes out
