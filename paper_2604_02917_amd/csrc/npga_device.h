@@ -121,6 +121,26 @@ __device__ __forceinline__ float wave_sum_f32(float v) {
   return ((r0 + r1) + r2) + r3;
 }
 
+// Two of them side by side.
+__device__ __forceinline__ void wave_sum2_f32(float &a, float &b) {
+  a += dpp_f32<0xB1>(a);
+  b += dpp_f32<0xB1>(b);
+  a += dpp_f32<0x4E>(a);
+  b += dpp_f32<0x4E>(b);
+  a += dpp_f32<0x141>(a);
+  b += dpp_f32<0x141>(b);
+  a += dpp_f32<0x140>(a);
+  b += dpp_f32<0x140>(b);
+  float r[2][4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    r[0][q] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(a), 16 * q));
+    r[1][q] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(b), 16 * q));
+  }
+  a = ((r[0][0] + r[0][1]) + r[0][2]) + r[0][3];
+  b = ((r[1][0] + r[1][1]) + r[1][2]) + r[1][3];
+}
+
 // Lanes whose bit SWAP (32 or 16) is clear get a + their partner's a, the
 // others b + their partner's b (one swap moves both ways).
 template <int SWAP>
@@ -230,16 +250,39 @@ __device__ __forceinline__ MinLoc minloc_pick(MinLoc a, MinLoc b) {
   return a;
 }
 
+// The wavefront's minimum in every lane: DPP moves within a row, lane swaps
+// between rows and halves, as the sums go (index below 2^31).  Six exchanges
+// through LDS took 0.25 us of a refinement step more, twice.
+template <int CTRL>
+__device__ __forceinline__ MinLoc dpp_minloc(MinLoc m) {
+  return minloc_pick(m, MinLoc{dpp_f64<CTRL>(m.v), __builtin_amdgcn_update_dpp(0, (int)m.i, CTRL, 0xf, 0xf, false)});
+}
+template <int SWAP>
+__device__ __forceinline__ MinLoc swap_minloc(MinLoc m) {
+  typedef unsigned u2 __attribute__((ext_vector_type(2)));
+  const unsigned long long u = (unsigned long long)__double_as_longlong(m.v);
+  auto both = [](unsigned w) {
+    if constexpr (SWAP == 32) return (u2)__builtin_amdgcn_permlane32_swap(w, w, false, false);
+    else return (u2)__builtin_amdgcn_permlane16_swap(w, w, false, false);
+  };
+  const u2 lo = both((unsigned)u), hi = both((unsigned)(u >> 32)), ix = both((unsigned)(int)m.i);
+  return minloc_pick(
+      MinLoc{__longlong_as_double((long long)(((unsigned long long)hi.x << 32) | lo.x)), (int64_t)(int)ix.x},
+      MinLoc{__longlong_as_double((long long)(((unsigned long long)hi.y << 32) | lo.y)), (int64_t)(int)ix.y});
+}
+__device__ __forceinline__ MinLoc wave_minloc(MinLoc m) {
+  m = dpp_minloc<0xB1>(m);
+  m = dpp_minloc<0x4E>(m);
+  m = dpp_minloc<0x141>(m);
+  m = dpp_minloc<0x140>(m);
+  m = swap_minloc<16>(m);
+  return swap_minloc<32>(m);
+}
+
 // buf, ibuf: 2 * NW entries each
 template <int NW = 4>
 __device__ __forceinline__ MinLoc block_minloc(MinLoc m, double *buf, int64_t *ibuf, int &parity) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    MinLoc o;
-    o.v = __shfl_xor(m.v, off, 64);
-    o.i = __shfl_xor(m.i, off, 64);
-    m = minloc_pick(m, o);
-  }
+  m = wave_minloc(m);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   double *b = buf + parity * NW;
   int64_t *bi = ibuf + parity * NW;

@@ -282,7 +282,7 @@ constexpr int64_t kLoopMaxBytes = 512 << 10;  // streamed and exchanged per work
 struct LoopArgs {
   const void *mat;          // Sigma (leading dim ld) or the factor L
   int64_t ld;
-  unsigned long long *xch;  // abort word, 7 unused, then two halves of `half` words
+  unsigned long long *xch;  // abort word, 7 unused, then 2 `half` words (factor path: three buffers in them)
   int64_t half;
   uint32_t seq0;            // sequence number before this launch's first step
   int32_t steps;            // steps of this launch at most

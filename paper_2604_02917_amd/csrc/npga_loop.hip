@@ -11,18 +11,22 @@
 //     the solver state in LDS and runs the serial tail on it, all of them
 //     the same arithmetic on the same numbers, so that an iteration needs
 //     one exchange (the gradient's pieces) and no broadcast of the new point;
-//   * the exchange has no barrier: a piece is an 8-byte word (float value,
-//     32-bit sequence number) stored and read at device scope, and a reader
-//     waits for the words it needs.  A word cannot be overwritten before it
-//     is read: a workgroup writes step s + 2's words (same half of the
-//     double buffer) only after it has read step s + 1's, which the others
-//     write after reading step s's.
+//   * the exchange has no barrier: words of 8 bytes stored and read at device
+//     scope, and a reader waits for the words it needs.  On the covariance
+//     path a word is one float and a 32-bit sequence number; a word cannot be
+//     overwritten before it is read: a workgroup writes step s + 2's words
+//     (same half of the double buffer) only after it has read step s + 1's,
+//     which the others write after reading step s's.  On the factor path,
+//     where every workgroup reads all the others' vectors, a word is two
+//     floats, and a word that no arithmetic produces stands for one that has
+//     not arrived (half the words and one round of looks for 16 workgroups:
+//     3.5 us of a step became 2.2).
 // Bound by latency: the exchange, the tail's reductions and a barrier or two.
 // Per NPGA step, a launch per step and one launch: n = 64 on Sigma 12 and 3.8
 // us, n = 501 on Sigma 11 and 4.9 us (16 workgroups), n = 1001, T = 403 on L
-// 19 and 10.2 us (14 workgroups); whole solves 3.4 -> 1.29 ms, 4.6 -> 2.0 ms,
-// 15.2 -> 9.8 ms.  (Waiting before the first look at the others' words, which
-// halves a column of the tridiagonalisation, gains nothing here: 2 % at n =
+// 19 and 9.0 us (14 workgroups; CG 10.0); whole solves 3.4 -> 1.3 ms, 4.6 -> 2.05 ms,
+// 15.2 -> 8.5 ms.  (Waiting before the first look at the others' words, which
+// halves a column of the tridiagonalisation, gains nothing here: 1 % at n =
 // 501, and a loss on L, where the looks are many and spread.)
 // With one workgroup there is no exchange.  Every wait is bounded: after
 // LoopArgs::wait_ticks a workgroup raises the abort word and leaves, the others
@@ -48,13 +52,19 @@ namespace {
 // leave of the LDS.
 constexpr int loop_resident(int E, bool symv) { return symv ? 32 / E : (E == 1 ? 16 : E == 2 ? 12 : 4); }
 
-// Words of one workgroup's piece of the factor path's exchange.
-constexpr int kLoopPiece(int E) { return 256 * E + 8; }
+// Words of one workgroup's piece of the factor path's exchange: a thread's
+// entries two to a word, and ||u||^2.
+constexpr int kLoopPairs(int E) { return E == 1 ? 1 : E / 2; }
+constexpr int kLoopPiece(int E) { return 256 * kLoopPairs(E) + 8; }
+constexpr unsigned long long kLoopUnset = 0xFFFFDEAD5EAF0001ull;  // (no arithmetic produces these NaN)
 
 enum LoopKind { kLoopSymv = 0, kLoopSweep = 1, kLoopSweep16 = 2 };
 
 __device__ __forceinline__ void put_word(unsigned long long *p, uint32_t value, uint32_t tag) {
   __hip_atomic_store(p, ((unsigned long long)tag << 32) | value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void set_word(unsigned long long *p, unsigned long long v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ unsigned long long get_word(const unsigned long long *p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -100,6 +110,28 @@ __device__ __forceinline__ bool get_words(const unsigned long long *p, uint32_t 
         miss |= (uint32_t)(v[x][y] >> 32) ^ tag;
         out[x][y] = __uint_as_float((uint32_t)v[x][y]);
       }
+    if (miss == 0u) return true;
+    if (w.give_up()) return false;
+  }
+}
+
+// A x B words p[i + a_stride a + b_stride b] (a clamped to a_last), all in
+// flight at once, until none of them is unset.
+template <int A, int B>
+__device__ __forceinline__ bool get_set_words(const unsigned long long *p, uint32_t i, uint32_t a_stride, int a_last,
+                                              uint32_t b_stride, unsigned long long (&v)[A][B], Waiter &w) {
+  if (w.ticks == 0) return false;
+  for (;;) {
+#pragma unroll
+    for (int x = 0; x < A; ++x)
+#pragma unroll
+      for (int y = 0; y < B; ++y)
+        v[x][y] = get_word(p + (i + (uint32_t)(x < a_last ? x : a_last) * a_stride + (uint32_t)y * b_stride));
+    uint32_t miss = 0u;
+#pragma unroll
+    for (int x = 0; x < A; ++x)
+#pragma unroll
+      for (int y = 0; y < B; ++y) miss |= v[x][y] == kLoopUnset ? 1u : 0u;
     if (miss == 0u) return true;
     if (w.give_up()) return false;
   }
@@ -210,7 +242,7 @@ __global__ __launch_bounds__(256, 1) void k_loop(SolveArgs m, LoopArgs la) {
   }
   __syncthreads();
 
-  auto dot = [&](const f4(&c)[E], const f4(&x)[E]) {
+  auto dot_part = [&](const f4(&c)[E], const f4(&x)[E]) {
     float d = 0.f;
 #pragma unroll
     for (int j = 0; j < E; ++j) {
@@ -219,8 +251,9 @@ __global__ __launch_bounds__(256, 1) void k_loop(SolveArgs m, LoopArgs la) {
       d = fmaf(c[j].z, x[j].z, d);
       d = fmaf(c[j].w, x[j].w, d);
     }
-    return wave_sum_f32(d);
+    return d;
   };
+  auto dot = [&](const f4(&c)[E], const f4(&x)[E]) { return wave_sum_f32(dot_part(c, x)); };
 
   Waiter wait{la.xch, la.seq0 + 1u, la.wait_ticks, 0, false};
   unsigned long long *words = la.xch + 8;
@@ -288,16 +321,21 @@ __global__ __launch_bounds__(256, 1) void k_loop(SolveArgs m, LoopArgs la) {
       double usq_w = 0.0;
 #pragma unroll
       for (int j = 0; j < E; ++j) g[j] = f4{0.f, 0.f, 0.f, 0.f};
-      auto take = [&](const f4(&c)[E], bool live) {
-        const float dd = dot(c, xr);
-        const float d = live ? dd : 0.f;
-        usq_w = fma((double)d, (double)d, usq_w);
+      // two items at a time: a product is a chain of some fifty dependent
+      // instructions
+      auto take2 = [&](const f4(&c0)[E], bool live0, const f4(&c1)[E], bool live1) {
+        float d0 = dot_part(c0, xr), d1 = dot_part(c1, xr);
+        wave_sum2_f32(d0, d1);
+        d0 = live0 ? d0 : 0.f;
+        d1 = live1 ? d1 : 0.f;
+        usq_w = fma((double)d0, (double)d0, usq_w);
+        usq_w = fma((double)d1, (double)d1, usq_w);
 #pragma unroll
         for (int j = 0; j < E; ++j) {
-          g[j].x = fmaf(c[j].x, d, g[j].x);
-          g[j].y = fmaf(c[j].y, d, g[j].y);
-          g[j].z = fmaf(c[j].z, d, g[j].z);
-          g[j].w = fmaf(c[j].w, d, g[j].w);
+          g[j].x = fmaf(c1[j].x, d1, fmaf(c0[j].x, d0, g[j].x));
+          g[j].y = fmaf(c1[j].y, d1, fmaf(c0[j].y, d0, g[j].y));
+          g[j].z = fmaf(c1[j].z, d1, fmaf(c0[j].z, d0, g[j].z));
+          g[j].w = fmaf(c1[j].w, d1, fmaf(c0[j].w, d0, g[j].w));
         }
       };
       constexpr int F = 4;  // streamed items in flight
@@ -307,16 +345,19 @@ __global__ __launch_bounds__(256, 1) void k_loop(SolveArgs m, LoopArgs la) {
 #pragma unroll
         for (int k = 0; k < F; ++k) load_item(ahead[k], gw + (R + k) * nwv);
       }
-      for (int k = 0; k < R && k * nwv < items; ++k) {
-        f4 c[E];
+      for (int k = 0; k < R && k * nwv < items; k += 2) {
+        f4 c[2][E];
 #pragma unroll
-        for (int j = 0; j < E; ++j) c[j] = slab_lds[((wave * R + k) * E + j) * 64 + lane];
-        take(c, gw + k * nwv < items);
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+          for (int j = 0; j < E; ++j) c[u][j] = slab_lds[((wave * R + k + u) * E + j) * 64 + lane];
+        take2(c[0], gw + k * nwv < items, c[1], gw + (k + 1) * nwv < items);
       }
       if (more) {
         for (int64_t k0 = R;;) {
 #pragma unroll
-          for (int k = 0; k < F; ++k) take(ahead[k], gw + (k0 + k) * nwv < items);
+          for (int k = 0; k < F; k += 2)
+            take2(ahead[k], gw + (k0 + k) * nwv < items, ahead[k + 1], gw + (k0 + k + 1) * nwv < items);
           k0 += F;
           if (k0 * nwv >= items) break;
 #pragma unroll
@@ -341,32 +382,47 @@ __global__ __launch_bounds__(256, 1) void k_loop(SolveArgs m, LoopArgs la) {
 #pragma unroll
         for (int j = 0; j < E; ++j) tot[j] = (double)part[j];
       } else {
-        // W pieces of NP words (the padding included) and two of usq
-        unsigned long long *buf = words + (s & 1) * la.half;
+        // W pieces.  Three buffers in turn; a step's word is unset again
+        // two steps before its next use, when every reader has shown (by its
+        // own next piece) that it is done with it, and before this thread's
+        // next piece, which a reader of the new word has to see first.
+        constexpr int PQ = kLoopPairs(E);
+        unsigned long long *buf = words + (uint32_t)(s % 3) * (uint32_t)(W * kLoopPiece(E));
         unsigned long long *own = buf + (uint32_t)me * (uint32_t)kLoopPiece(E);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #pragma unroll
-        for (int j = 0; j < E; ++j) put_word(own + tid + 256 * j, __float_as_uint(part[j]), tag);
-        if (tid < 2) {
-          const unsigned long long b = (unsigned long long)__double_as_longlong(up);
-          put_word(own + NP + tid, tid ? (uint32_t)(b >> 32) : (uint32_t)b, tag);
-        }
+        for (int j = 0; j < PQ; ++j)
+          set_word(own + tid + 256 * j,
+                   ((unsigned long long)__float_as_uint(E == 1 ? 0.f : part[(2 * j + 1) % E]) << 32) |
+                       __float_as_uint(part[2 * j % E]));
+        // ||u||^2 enters the objective of a stopping test only
+        const bool wants_usq = MODE == kTailNpga && st.iter % st.check_every == 0;
+        if (wants_usq && tid == 0) set_word(own + 256 * PQ, (unsigned long long)__double_as_longlong(up));
 #pragma unroll
         for (int j = 0; j < E; ++j) tot[j] = 0.0;
-        constexpr int G = E == 4 ? 8 : 16;  // pieces in flight, added in order
+        constexpr int G = 16;  // pieces in flight, added in order
         for (int w0 = 0; w0 < W && !bad; w0 += G) {
-          float v[G][E];
-          bad = !get_words<G, E>(buf + (uint32_t)w0 * (uint32_t)kLoopPiece(E), (uint32_t)tid, (uint32_t)kLoopPiece(E),
-                                 W - 1 - w0, 256u, tag, v, wait);
+          unsigned long long v[G][PQ];
+          bad = !get_set_words<G, PQ>(buf + (uint32_t)w0 * (uint32_t)kLoopPiece(E), (uint32_t)tid,
+                                      (uint32_t)kLoopPiece(E), W - 1 - w0, 256u, v, wait);
 #pragma unroll
           for (int x = 0; x < G; ++x)
 #pragma unroll
-            for (int j = 0; j < E; ++j) tot[j] += (w0 + x < W) ? (double)v[x][j] : 0.0;
+            for (int j = 0; j < E; ++j) {
+              const uint32_t u = (uint32_t)(v[x][j / 2] >> (32 * (j % 2)));
+              tot[j] += (w0 + x < W) ? (double)__uint_as_float(u) : 0.0;
+            }
         }
-        if (tid < W && !bad) {
-          float hl[1][2];
-          bad = !get_words<1, 2>(buf, (uint32_t)(tid * kLoopPiece(E) + NP), 0u, 0, 1u, tag, hl, wait);
-          ush[4 + tid] = __longlong_as_double(
-              (long long)(((unsigned long long)__float_as_uint(hl[0][1]) << 32) | __float_as_uint(hl[0][0])));
+        if (wants_usq && tid < W && !bad) {
+          unsigned long long v[1][1];
+          bad = !get_set_words<1, 1>(buf, (uint32_t)(tid * kLoopPiece(E) + 256 * PQ), 0u, 0, 0u, v, wait);
+          ush[4 + tid] = __longlong_as_double((long long)v[0][0]);
+        }
+        if (!bad) {  // the step before's words
+          unsigned long long *old = words + ((uint32_t)((s + 2) % 3) * (uint32_t)W + (uint32_t)me) * (uint32_t)kLoopPiece(E);
+#pragma unroll
+          for (int j = 0; j < PQ; ++j) set_word(old + tid + 256 * j, kLoopUnset);
+          if (tid == 0) set_word(old + 256 * PQ, kLoopUnset);
         }
       }
     }
@@ -375,7 +431,7 @@ __global__ __launch_bounds__(256, 1) void k_loop(SolveArgs m, LoopArgs la) {
         stalled = true;
         break;
       }
-      if constexpr (KIND != kLoopSymv) {
+      if constexpr (KIND != kLoopSymv && MODE == kTailNpga) {
         usq = ush[4];
         for (int w = 1; w < W; ++w) usq += ush[4 + w];
       }
@@ -430,6 +486,11 @@ __global__ __launch_bounds__(256, 1) void k_loop(SolveArgs m, LoopArgs la) {
   }
 }
 
+// The factor path's words before a launch.
+__global__ __launch_bounds__(256) void k_loop_unset(unsigned long long *p, int64_t words) {
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < words; i += (int64_t)gridDim.x * 256) p[i] = kLoopUnset;
+}
+
 // Workgroups of the loop for a shape (0: the launch-per-step path).  One
 // workgroup when it holds all the items (its products then take about the
 // time of an exchange).  Beyond, eight rows of Sigma a wavefront; on the
@@ -457,7 +518,7 @@ LoopPlan loop_plan(int64_t n, int64_t cols, int path, int dtype) {
   const int64_t pieces = w == 1 ? 0 : (symv ? 8 * n : 8 * n * w);
   if (streamed + pieces > kLoopMaxBytes) return p;
   p.groups = (int)w;
-  p.half = w == 1 ? 0 : (symv ? (int64_t)256 * e : w * kLoopPiece(e));
+  p.half = w == 1 ? 0 : (symv ? (int64_t)256 * e : (3 * w * kLoopPiece(e) + 1) / 2);
   return p;
 }
 
@@ -489,6 +550,8 @@ int launch_loop(const SolveArgs &a, const LoopArgs &la, int groups, int slots, i
   if (groups < 1 || groups > kLoopMaxGroups || a.dykstra || a.backtrack || a.pre_y ||
       (a.mode != kTailNpga && a.mode != kTailCG && a.mode != kTailPdas && a.mode != kTailLanczos))
     return (int)hipErrorInvalidValue;
+  if (path != NPGA_PATH_SYRK && groups > 1)
+    hipLaunchKernelGGL(k_loop_unset, dim3(64), dim3(256), 0, s, la.xch + 8, 2 * la.half);
   switch (slots) {
     case 1: launch_loop_kind<1>(a, la, groups, path, s); break;
     case 2: launch_loop_kind<2>(a, la, groups, path, s); break;
