@@ -852,23 +852,11 @@ int npga_project(const double *v, const double *mu, int64_t n, double r, double 
   if (!ws || !aligned(ws, 256) || ws_bytes < lay.total) return NPGA_ERR_WORKSPACE;
   DevState *pin = pinned_status();
   if (!pin) return NPGA_ERR_HIP;
-  DevState *st = reinterpret_cast<DevState *>(static_cast<char *>(ws) + lay.off_state);
-  npga_factor f{n, 1, (n + 3) / 4 * 4, ws, mu, 0.0, NPGA_F32, 0};
-  pin[2] = initial_state(&f, r, o);
-  HIPCHK(hipMemcpyAsync(st, &pin[2], sizeof(DevState), hipMemcpyHostToDevice, stream));
-  SolveArgs a{};
-  a.mu = mu;
-  a.n = n;
-  a.st = st;
-  LAUNCHCHK(npga::launch_prepare(a, stream));
-  HIPCHK(hipMemcpyAsync(&pin[3], st, sizeof(DevState), hipMemcpyDeviceToHost, stream));
+  LAUNCHCHK(npga::launch_project_only(v, mu, n, r, o.proj_tol, x,
+                                      reinterpret_cast<DevState *>(pinned_dev(pin, &pin[3].done)), lay.slots, stream));
   HIPCHK(hipStreamSynchronize(stream));
   if (pin[3].n_nonfinite > 0) return NPGA_ERR_NUMERIC;
   if (r > pin[3].mu_max) return NPGA_ERR_INFEASIBLE;
-  LAUNCHCHK(npga::launch_set_tolphi(st, o.proj_tol, stream));
-  LAUNCHCHK(npga::launch_project_only(v, mu, n, x, st, lay.slots, stream));
-  HIPCHK(hipMemcpyAsync(&pin[3], st, sizeof(DevState), hipMemcpyDeviceToHost, stream));
-  HIPCHK(hipStreamSynchronize(stream));
   if (nu_tau) {
     nu_tau[0] = pin[3].nu;
     nu_tau[1] = pin[3].tau;

@@ -304,7 +304,7 @@ int launch_sweep(const SolveArgs &a, int slots, hipStream_t s);
 int launch_reduce_tail(const SolveArgs &a, int slots, hipStream_t s);
 int launch_tail(const SolveArgs &a, int slots, int covariance, hipStream_t s);
 int launch_project_init(const SolveArgs &a, int slots, int use_x0, hipStream_t s);
-int launch_project_only(const double *v, const double *mu, int64_t n, double *x, DevState *st,
+int launch_project_only(const double *v, const double *mu, int64_t n, double r, double proj_tol, double *x, DevState *out,
                         int slots, hipStream_t s);
 int launch_project_dykstra(const double *v, const double *mu, int64_t n, double *x, DevState *st, int max_iter,
                            double tol, int slots, hipStream_t s);

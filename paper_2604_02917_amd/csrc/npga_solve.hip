@@ -836,31 +836,55 @@ __global__ __launch_bounds__(256) void k_cg_init(SolveArgs a) {
   cg_init_body<E>(a, redbuf);
 }
 
-// Standalone projection (npga_project entry point).
+// Pi_F(v) in one launch: the checks of mu, the tolerance and the projection,
+// the outcome straight into `out` in host memory.  The work is a few
+// microseconds; what a call costs is its launches, copies and waits (with a
+// state uploaded, two copies back and three launches 46 us at n = 500, 26
+// us so).
 template <int E>
-__global__ __launch_bounds__(256) void k_project_only(const double *vin, const double *muin, int64_t n,
-                                                      double *xout, DevState *st) {
-  __shared__ double redbuf[64];
+__global__ __launch_bounds__(256) void k_project_only(const double *vin, const double *muin, int64_t n, double r,
+                                                      double proj_tol, double *xout, DevState *out) {
+  __shared__ double redbuf[64], mxs[8];
   BlockReducer<5> red{redbuf, 0};
   const int tid = threadIdx.x;
-  double mu[E], v[E];
+  double mu[E], v[E], mx = -1.0e308, amx = 0.0, bad[5] = {0, 0, 0, 0, 0};
 #pragma unroll
   for (int j = 0; j < E; ++j) {
     const int64_t i = tid + 256 * j;
     mu[j] = (i < n) ? muin[i] : 0.0;
     v[j] = (i < n) ? vin[i] : -1.0e300;
+    const bool fin = isfinite(mu[j]);
+    bad[0] += fin ? 0.0 : 1.0;
+    mx = (i < n && fin) ? fmax(mx, mu[j]) : mx;
+    amx = fin ? fmax(amx, fabs(mu[j])) : amx;
   }
-  const ProjResult pr = project_F<E>(v, mu, st->r, st->tolphi, 0.0, -1.0e300, red);
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) {
+    mx = fmax(mx, __shfl_xor(mx, off, 64));
+    amx = fmax(amx, __shfl_xor(amx, off, 64));
+  }
+  if ((tid & 63) == 0) {
+    mxs[tid >> 6] = mx;
+    mxs[4 + (tid >> 6)] = amx;
+  }
+  red.sum(bad);  // its barrier also publishes mxs
+  mx = fmax(fmax(mxs[0], mxs[1]), fmax(mxs[2], mxs[3]));
+  amx = fmax(fmax(mxs[4], mxs[5]), fmax(mxs[6], mxs[7]));
+  if (tid == 0) {
+    out->n_nonfinite = bad[0];
+    out->mu_max = mx;
+  }
+  if (bad[0] > 0.0 || r > mx) return;
+  const ProjResult pr = project_F<E>(v, mu, r, proj_tol * fmax(fabs(r), amx), 0.0, -1.0e300, red);
 #pragma unroll
   for (int j = 0; j < E; ++j) {
     const int64_t i = tid + 256 * j;
     if (i < n) xout[i] = v[j];
   }
   if (tid == 0) {
-    st->nu = pr.nu;
-    st->tau = pr.tau;
-    st->proj_flags = pr.flags;
-    st->iter = pr.passes;
+    out->nu = pr.nu;
+    out->tau = pr.tau;
+    out->proj_flags = pr.flags;
   }
 }
 
@@ -1186,9 +1210,9 @@ int launch_cg_init(const SolveArgs &a, int slots, hipStream_t s) {
   return (int)hipGetLastError();
 }
 
-int launch_project_only(const double *v, const double *mu, int64_t n, double *x, DevState *st,
+int launch_project_only(const double *v, const double *mu, int64_t n, double r, double proj_tol, double *x, DevState *out,
                         int slots, hipStream_t s) {
-#define CALL(E) hipLaunchKernelGGL(k_project_only<E>, dim3(1), dim3(256), 0, s, v, mu, n, x, st)
+#define CALL(E) hipLaunchKernelGGL(k_project_only<E>, dim3(1), dim3(256), 0, s, v, mu, n, r, proj_tol, x, out)
   NPGA_SLOT_SWITCH(slots, CALL)
 #undef CALL
   return (int)hipGetLastError();
