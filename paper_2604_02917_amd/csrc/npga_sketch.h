@@ -39,7 +39,7 @@ int launch_tridiag(const SketchState &s, int64_t i_begin, int64_t i_end, hipStre
 // workgroups lasted longer than `ticks` of the 100 MHz counter);
 // launch_tridiag_resume, given that word, then does its columns and what
 // follows with a launch per stage.
-constexpr int64_t kTriMax = 3584;
+constexpr int64_t kTriMax = 4096;
 size_t tri_chip_bytes(int64_t k);
 int launch_tridiag_chip(const SketchState &s, void *slots, long long ticks, hipStream_t st);
 int launch_tridiag_resume(const SketchState &s, void *slots, uint64_t flag, hipStream_t st);

@@ -25,12 +25,12 @@
 // The operations are those of npga_sketch.hip, all in float64.  Bound by a
 // step's latency: the exchange (about 1.2 us) and three sums over the
 // workgroup, one after the other.  Measured, us a column: 2.2 up to order
-// 512, 2.3 to 1024, 2.9 to 2048, 5.9 from 3584 to 2048 (the registers do not
-// hold those, and some rows stand in LDS); by launches 12 at order 403 and 16
-// to 33 at 2048 to 4096.  Without the wait before the first look at the slots
-// (kNap) the same columns took 3.9, 4.5, 5.0 and 7.7.  All columns of a k = 403
-// sketch: 4.9 ms by launches, 0.87 ms here; k = 4096: 80 ms by launches, 32 ms
-// here, of which the first 512 columns, still by launches, 17 ms.
+// 512, 2.3 to 1024, 2.9 to 2048, 5.6 from 3584 to 2048 (the registers do not
+// hold those, and some rows stand in LDS), 17 from 4096 to 3584 (a quarter
+// of the elements stands in memory); by launches 12 at order 403 and 16 to 33
+// at 2048 to 4096.  Without the wait before the first look at the slots (kNap)
+// the same columns took 3.9, 4.5, 5.0 and 7.7.  All columns of a k = 403
+// sketch: 4.9 ms by launches, 0.87 ms here; k = 4096: 80 ms and 23 ms.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -57,11 +57,14 @@ struct TriRun {
   const double *p0, *v0;  // p and v of the column before (i0 > 0)
   unsigned long long *p, *x;  // slots of p and of the next row, one for each column
   int64_t lds;  // words between slots (a multiple of 32: no 256-byte line holds two columns' words)
+  double *edge;  // the elements that have no place on the chip (kTriEdge each thread)
   double *rest, *vrest;  // n < m: the trailing matrix of order m - n and its v afterwards
   unsigned long long *head;  // abort word: 0, or 1 + the number of the launch that gave up
   unsigned long long stage;
   long long ticks;
 };
+
+constexpr int kTriEdge = 30;  // two rows of eight slots, slot 0 of fourteen
 
 // Sum over the workgroup; every thread gets the same bits.  buf: its own
 // eight words for each of a step's sums, so one barrier is enough.
@@ -93,13 +96,19 @@ __device__ __forceinline__ void tri_put(unsigned long long *p, double v) {
 // first LR rows, which are finished first, stand in LDS, the others in
 // registers.  A loop for each 512 columns: slots and rows that are finished
 // before it begins are left out of it.
-template <int SL, int RR, int LR, int W, int JEND>
+//
+// EDGE (orders above 3584, up to 512 columns of it): slot 0 and the first two
+// rows stay in memory, kTriEdge doubles a thread, read and written once a
+// step (31 MB over the chip); all of them are finished when 3584 are left.
+template <int SL, int RR, int LR, int W, int JEND, bool EDGE = false>
 __global__ __launch_bounds__(kTriT) void k_tri_chip(SketchState s, TriRun a) {
-  constexpr int ROWS = RR + LR;
+  constexpr int QB = EDGE ? 2 : 0, JB = EDGE ? 1 : 0, SC = SL - JB;  // first row and slot on the chip, slots
+  constexpr int ROWS = RR + LR + QB;
   constexpr int ROWS4 = (ROWS + 3) / 4 * 4;
   // x 64 clocks, see below; the best of 12 to 40, flat within 2 around it
   constexpr int kNap = SL <= 2 ? 13 : SL == 4 ? 16 : 18;
-  extern __shared__ double alds[];  // LR x SL x 512
+  static_assert(!EDGE || (W == 256 && ROWS == 16 && JEND == 1), "");
+  extern __shared__ double alds[];  // LR x SC x 512
   __shared__ double sums[2][8], rowsum[ROWS4][8];
   __shared__ double2 own[ROWS4];  // v and w at the own rows
   __shared__ double pds, x0s;
@@ -108,18 +117,29 @@ __global__ __launch_bounds__(kTriT) void k_tri_chip(SketchState s, TriRun a) {
   const int me = blockIdx.x, m = (int)a.m;
   const int64_t k = s.k, i0 = a.i0;
   if (__syncthreads_or(tri_get(a.head) != 0ull)) return;
-  double A[RR][SL], v[SL];
+  double A[RR][SC], v[SL];
+  double *em = EDGE ? a.edge + (int64_t)me * kTriEdge * kTriT : nullptr;
+  auto in_memory = [](int q, int j) { return EDGE && (q < QB || j < JB); };
+  auto memory_at = [](int q, int j) { return (q < QB ? q * SL + j : QB * SL + q - QB) * kTriT; };
+  auto lds_at = [](int q, int j) { return ((q - QB) * SC + j - JB) * kTriT; };
+  // element (q, j); the indexes are constants wherever it is used
+  auto get = [&](int q, int j) __attribute__((always_inline)) -> double {
+    if (in_memory(q, j)) return em[memory_at(q, j) + (unsigned)tid];
+    if (q - QB < LR) return alds[lds_at(q, j) + tid];
+    return A[q - QB < LR ? 0 : q - QB - LR][j < JB ? 0 : j - JB];
+  };
+  auto put = [&](int q, int j, double e) __attribute__((always_inline)) {
+    if (in_memory(q, j)) em[memory_at(q, j) + (unsigned)tid] = e;
+    else if (q - QB < LR) alds[lds_at(q, j) + tid] = e;
+    else A[q - QB < LR ? 0 : q - QB - LR][j < JB ? 0 : j - JB] = e;
+  };
 #pragma unroll
   for (int q = 0; q < ROWS; ++q) {
     const double *row = a.src + std::min(me + W * q, m - 1) * a.lsrc;
     asm volatile("" : "+v"(tid));
 #pragma unroll
     for (int j = 0; j < SL; ++j) {
-      const double e = row[(unsigned)std::min(tid + kTriT * j, m - 1)];
-      if (q < LR)
-        alds[(q * SL + j) * kTriT + tid] = e;
-      else
-        A[q - LR][j] = e;
+      put(q, j, row[(unsigned)std::min(tid + kTriT * j, m - 1)]);
     }
   }
   if (tid < ROWS4) own[tid] = double2{0.0, 0.0};
@@ -225,27 +245,48 @@ __global__ __launch_bounds__(kTriT) void k_tri_chip(SketchState s, TriRun a) {
         s.tau[i0 + st] = tau;
       }
       // own rows, four at a time: the update, the product with v_i, its sum.
-      // (Rows that are finished or beyond m are carried along; nothing reads them.)
+      // (Rows that are finished or beyond m are carried along; nothing reads
+      // them.)  What stands in memory is asked for some groups ahead; the two
+      // rows there come last.
+      double m0[EDGE ? ROWS - QB : 1], mr[1][EDGE ? SL : 1];
+      if constexpr (EDGE) {
+#pragma unroll
+        for (int q = QB; q < QB + 4; ++q) m0[q - QB] = get(q, 0);
+      }
 #pragma unroll
       for (int q0 = Q0; q0 < ROWS; q0 += 4) {
+        if constexpr (EDGE) {
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int q = q0 + QB + 4; q < q0 + QB + 8 && q < ROWS; ++q) m0[q - QB] = get(q, 0);
+          if (q0 == 12) {
+#pragma unroll
+            for (int j = 0; j < SL; ++j) mr[0][j] = get(0, j);
+          }
+        }
         double acc[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-          const int q = q0 + u;
+          const int q = EDGE ? (q0 + u + QB) % ROWS : q0 + u;
           if (q >= ROWS) continue;
           // (two rows' loads from LDS in flight: more cost registers)
           if (LR > 0 && u % 2 == 0) __builtin_amdgcn_sched_barrier(0);
           const double2 vw = own[q];
 #pragma unroll
           for (int j = JS; j < SL; ++j) {
-            double *el = q < LR ? &alds[(q * SL + j) * kTriT + tid] : &A[q < LR ? 0 : q - LR][j];
-            const double e = *el - (vw.x * w[j] + vw.y * v[j]);
-            *el = e;
+            double e;
+            if constexpr (EDGE)
+              e = q == 0 ? mr[0][j] : (j < JB && q >= QB) ? m0[q < QB ? 0 : q - QB] : get(q, j);
+            else
+              e = get(q, j);
+            e -= vw.x * w[j] + vw.y * v[j];
+            put(q, j, e);
             acc[u] = fma(e, x[j], acc[u]);
           }
         }
         const double r = wave_sum4_f64(acc[0], acc[1], acc[2], acc[3]);
-        if ((lane & 15) == 0) rowsum[q0 + (lane >> 4)][wave] = r;
+        const int qr = EDGE ? (q0 + (lane >> 4) + QB) % ROWS : q0 + (lane >> 4);
+        if ((lane & 15) == 0) rowsum[qr][wave] = r;
       }
       if (me == (st + 1) % W) {  // row st + 1 goes out
         const int qs = (st + 1) / W;
@@ -253,12 +294,12 @@ __global__ __launch_bounds__(kTriT) void k_tri_chip(SketchState s, TriRun a) {
         unsigned off = (unsigned)tid * 8u;
         asm volatile("" : "+v"(off)::"memory");  // what stands in LDS is read from there again
 #pragma unroll
-        for (int q = Q0; q < ROWS; ++q) {
+        for (int q = Q0; q < (EDGE ? QB : ROWS); ++q) {  // (EDGE: row 512, the next launch's first, is in `rest`)
           if (q != qs) continue;
 #pragma unroll
           for (int j = JS; j < SL; ++j) {
             const int c = tid + kTriT * j;
-            const double e = q < LR ? alds[(q * SL + j) * kTriT + tid] : A[q < LR ? 0 : q - LR][j];
+            const double e = get(q, j);
             if (c > st && c < m) tri_put(tri_at(xo + kTriT * j, off), e);
           }
         }
@@ -292,7 +333,7 @@ __global__ __launch_bounds__(kTriT) void k_tri_chip(SketchState s, TriRun a) {
       for (int q = 0; q < ROWS; ++q) {
         const int lr = me + W * q;
         if (lr >= n && lr < m)
-          a.rest[(c - n) + (lr - n) * mr] = q < LR ? alds[(q * SL + j) * kTriT + tid] : A[q < LR ? 0 : q - LR][j];
+          a.rest[(c - n) + (lr - n) * mr] = get(q, j);
       }
     }
   }
@@ -350,12 +391,13 @@ int64_t round32(int64_t v) { return (v + 31) / 32 * 32; }
 
 // The launches for order k.  512 columns a slot, and as few rows to a
 // workgroup as 256 workgroups allow (four are summed together).  Above 2048
-// the registers do not hold everything and a column takes 8 us against 5: as
-// soon as 2048 columns are left the matrix is dealt out again.
+// the registers do not hold everything and a column takes 6 us against 3, and
+// above 3584 not the LDS either (17 us, 33 by launches): as soon as fewer columns are left the
+// matrix is dealt out again.
 struct TriPlan {
   int launches;
-  TriRun run[2];
-  int sl[2];
+  TriRun run[3];
+  int sl[3];
   size_t words;
 };
 
@@ -368,11 +410,11 @@ TriPlan tri_plan(const SketchState &s, void *slots, long long ticks) {
   int64_t lsrc = s.k;
   for (;;) {
     TriRun &a = p.run[p.launches];
-    const int sl = m <= 512 ? 1 : m <= 1024 ? 2 : m <= 2048 ? 4 : 7;
+    const int sl = m <= 512 ? 1 : m <= 1024 ? 2 : m <= 2048 ? 4 : m <= 3584 ? 7 : 8;
     p.sl[p.launches] = sl;
     a.i0 = i0;
     a.m = m;
-    a.n = std::min<int64_t>(m, sl == 7 ? m - 2048 : m);
+    a.n = sl == 8 ? m - 3584 : sl == 7 ? m - 2048 : m;
     a.src = src;
     a.lsrc = lsrc;
     a.p0 = p0;
@@ -386,6 +428,10 @@ TriPlan tri_plan(const SketchState &s, void *slots, long long ticks) {
     a.p = w;
     a.x = w + steps * a.lds;
     w += 2 * steps * a.lds;
+    if (sl == 8) {
+      a.edge = reinterpret_cast<double *>(w);
+      w += (int64_t)256 * kTriEdge * kTriT;
+    }
     if (mr == 0) break;
     a.rest = reinterpret_cast<double *>(w);
     a.vrest = a.rest + round32(mr * mr);
@@ -430,6 +476,10 @@ int launch_tridiag_chip(const SketchState &s, void *slots, long long ticks, hipS
       case 1: hipLaunchKernelGGL((k_tri_chip<1, 4, 0, 128, 1>), narrow, block, 0, st, s, a); break;
       case 2: hipLaunchKernelGGL((k_tri_chip<2, 4, 0, 256, 2>), wide, block, 0, st, s, a); break;
       case 4: hipLaunchKernelGGL((k_tri_chip<4, 8, 0, 256, 4>), wide, block, 0, st, s, a); break;
+      case 8:
+        hipLaunchKernelGGL((k_tri_chip<8, 9, 5, 256, 1, true>), wide, block, (unsigned)sizeof(double) * 5 * 7 * kTriT, st,
+                           s, a);
+        break;
       default: {
         constexpr int kRows = 5;  // in LDS
         hipLaunchKernelGGL((k_tri_chip<7, 14 - kRows, kRows, 256, 3>), wide, block,
@@ -444,7 +494,7 @@ int launch_tridiag_chip(const SketchState &s, void *slots, long long ticks, hipS
 
 int launch_tridiag_resume(const SketchState &s, void *slots, uint64_t flag, hipStream_t st) {
   const TriPlan p = tri_plan(s, slots, 0);
-  const int l = flag == 2 && p.launches > 1 ? 1 : 0;
+  const int l = flag >= 1 && flag <= (uint64_t)p.launches ? (int)flag - 1 : 0;
   const TriRun &a = p.run[l];
   if (l == 0) {
     if (mirror(s, a.i0, 0, st)) return (int)hipErrorLaunchFailure;

@@ -107,3 +107,15 @@ def test_tridiagonal_later_launch_gives_up(npga, k):
     F = Le.cpu().numpy().astype(np.float64)
     assert np.abs(F @ F.T - np.diag(s * s)).max() <= 1e-5 * s[0] ** 2
     assert gam == gam1
+
+
+@pytest.mark.parametrize("k", [3600, 3839, 3841, 4095, 4096, 4097])
+def test_one_launch_tridiagonal_edge(npga, k):
+    """Orders of which two rows a workgroup and a slot of columns stay in memory."""
+    test_one_launch_tridiagonal(npga, k)
+
+
+def test_tridiagonal_gives_up_after_the_edge(npga):
+    """k = 3585: the launch with elements in memory has one column and needs
+    no wait, the one after it gives up."""
+    test_tridiagonal_later_launch_gives_up(npga, 3585)
