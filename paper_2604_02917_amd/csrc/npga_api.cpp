@@ -1236,6 +1236,7 @@ struct BatchLayout {
 
 constexpr int kMaxSplits = 64;
 constexpr int64_t kUSplitMax = 512;
+constexpr int64_t kUSmallMax = 64;
 constexpr int kNumVec = 9;  // xbuf0, xbuf1, gbuf0, gbuf1, pvec, fvec, gvec, xa, ga
 
 // cov: the covariance form (Sigma, the bfloat16 planes the SYRK reads, and a
@@ -1261,7 +1262,7 @@ BatchLayout batch_layout(int64_t n, int64_t cols, int32_t m, bool cov = false) {
   l.off_vec = take(sizeof(double) * (size_t)kNumVec * (size_t)l.npad * (size_t)m);
   l.off_Ut = take(sizeof(float) * (size_t)l.ldut * (size_t)cols);
   l.off_P = take(sizeof(float) * (size_t)kMaxSplits * (size_t)l.ldpi * (size_t)l.ldpm);
-  const int64_t utiles_max = (cols + 31) / 32;
+  const int64_t utiles_max = (cols + 15) / 16;
   l.off_usq = take(sizeof(double) * (size_t)utiles_max * (size_t)l.ldq);
   l.off_status = take(sizeof(int32_t) * (size_t)(2 * (m + 1)));
   l.off_act = take(sizeof(int32_t) * (size_t)(m + 1));
@@ -1315,10 +1316,13 @@ npga::BatchArgs with_config(npga::BatchArgs b, const npga::BatchConfig &cfg, int
   b.splits = (int32_t)((cols + kc - 1) / kc);
   // The U GEMM: the configuration's tiles, or 32 x 32 tiles split over the
   // assets inside a workgroup while those are at most kUSplitMax workgroups
-  // (one to two rounds of the chip)
-  b.u_split = (cols + 31) / 32 * ((running + 31) / 32) <= kUSplitMax ? 1 : 0;
+  // (one to two rounds of the chip); on the bfloat16 cores 16 x 16 tiles while
+  // those fit the chip at once (64 of 32 x 32: n = 1000, T = 500, 128 targets
+  // 10.3 us by 32 x 32 and 8.0 us by 16 x 16; 200: 16 and 30 us)
+  const int64_t tiles = (cols + 31) / 32 * ((running + 31) / 32);
+  b.u_split = tiles > kUSplitMax ? 0 : b.Lt && tiles <= kUSmallMax ? 2 : 1;
   if (b.u_split) {
-    b.utiles = (int32_t)((cols + 31) / 32);
+    b.utiles = (int32_t)(b.u_split == 2 ? (cols + 15) / 16 : (cols + 31) / 32);
   } else if (b.Lt) {
     const int bt = cfg.g_bn == 32 ? 128 : 64;  // period tile of the bfloat16 U GEMM
     b.utiles = (int32_t)((cols + bt - 1) / bt);

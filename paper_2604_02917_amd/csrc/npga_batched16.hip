@@ -302,6 +302,102 @@ __global__ __launch_bounds__(512) void k_b16_u_split(BatchArgs b) {
 }
 
 // --------------------------------------------------------------------------
+// The same for the smallest products: 16 targets x 16 periods a workgroup,
+// 32-asset steps, six ahead.  A compute unit takes the lines of a load's rows
+// one after another, so few workgroups are bound by the rows each of them
+// reads: n = 1500, T = 701, 24 targets (22 workgroups of 32 x 32, 88 of 16 x
+// 16) 9.8 us there and 7.4 us here.  With more tiles than compute units the
+// operands read twice as often cost more: n = 2000, T = 1600, 128 targets 16
+// us there and 30 us here.
+// --------------------------------------------------------------------------
+__global__ __launch_bounds__(512) void k_b16_u_small(BatchArgs b) {
+  constexpr int D = 6;  // steps in flight
+  __shared__ float red[8][4][64];
+  const int64_t T = b.base.cols, n = b.base.n, ld = b.base.ld;
+  const int ma = *b.mact;
+  const int64_t t0 = (int64_t)blockIdx.x * 16;
+  const int c0 = (int)blockIdx.y * 16;
+  if (c0 >= ma) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int h = lane >> 4, r = lane & 15;
+  // lane: target c0 + r and period t0 + r, assets 8 h .. 8 h + 7 of a step;
+  // targets, periods and steps past the last read the last and are dropped
+  const int c = c0 + r < ma ? c0 + r : ma - 1;
+  const float *X = b.base.xs + (int64_t)b.act[c] * b.ldx + 8 * h;
+  const uint16_t *L = static_cast<const uint16_t *>(b.base.L) + (t0 + r < T ? t0 + r : T - 1) * ld;
+  const int64_t last = (ld - 8) / 8 * 8;  // columns hold ld >= n entries, ld % 8 == 0
+  const int steps = (int)((n + 31) / 32);
+  const int cnt = (steps - wave + 7) >> 3;  // this wavefront's steps: wave, wave + 8, ...
+  f4 xa[D][2];
+  u4v lb[D];
+  auto load = [&](int slot, int t) {
+    const int64_t k0 = 32 * (int64_t)(wave + 8 * (t < cnt ? t : cnt - 1));
+    xa[slot][0] = *reinterpret_cast<const f4 *>(X + k0);  // X columns are padded to a multiple of 256 with zeros
+    xa[slot][1] = *reinterpret_cast<const f4 *>(X + k0 + 4);
+    const int64_t kl = k0 + 8 * h;
+    lb[slot] = *reinterpret_cast<const u4v *>(L + (kl < last ? kl : last));
+  };
+  f4 acc = f4{0.f, 0.f, 0.f, 0.f};
+  if (cnt > 0) {
+#pragma unroll
+    for (int t = 0; t < D; ++t) {
+      load(t, t);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    for (int s0 = 0; s0 < cnt; s0 += D) {
+#pragma unroll
+      for (int u = 0; u < D; ++u) {
+        if (s0 + u < cnt) {
+          const int64_t k = 32 * (int64_t)(wave + 8 * (s0 + u)) + 8 * h;
+          const float v8[8] = {xa[u][0].x, xa[u][0].y, xa[u][0].z, xa[u][0].w,
+                               xa[u][1].x, xa[u][1].y, xa[u][1].z, xa[u][1].w};
+          u4v w[3];
+          split8(v8, w);
+          // asset rows past n (ld may exceed n) are not data
+          u4v lv = lb[u];
+          if (k + 8 > n) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              const int64_t row = k + 2 * q;
+              lv[q] &= row + 1 < n ? 0xffffffffu : (row < n ? 0x0000ffffu : 0u);
+            }
+          }
+          const bf8 bb = __builtin_bit_cast(bf8, lv);
+#pragma unroll
+          for (int pl = 2; pl >= 0; --pl)
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8, w[pl]), bb, acc, 0, 0, 0);
+        }
+        if (s0 + D < cnt) load(u, s0 + u + D);
+      }
+    }
+  }
+#pragma unroll
+  for (int v = 0; v < 4; ++v) red[wave][v][lane] = acc[v];
+  __syncthreads();
+  if (wave >= 4) return;
+  // register v = wave of lane (h, r): target c0 + 4 h + v, period t0 + r
+  double s = 0.0;
+#pragma unroll
+  for (int w = 0; w < 8; ++w) s += (double)red[w][wave][lane];
+  const float val = (t0 + r < T) ? (float)s : 0.f;
+  const int cc = c0 + 4 * h + wave;
+  double q = (double)val * (double)val;
+#pragma unroll
+  for (int off = 1; off < 16; off <<= 1) q += __shfl_xor(q, off, 64);
+  if (cc >= ma) return;
+  if (t0 + r < T) {
+    uint32_t hh, mm, ll;
+    split3(val, hh, mm, ll);
+    uint16_t *u = b.U16 + (int64_t)cc * b.ldu16 + t0 + r;
+    u[0] = (uint16_t)hh;
+    u[b.u16plane] = (uint16_t)mm;
+    u[2 * b.u16plane] = (uint16_t)ll;
+  }
+  if (r == 0) b.usq_part[(int64_t)blockIdx.x * b.ldq + b.act[cc]] = q;
+}
+
+// --------------------------------------------------------------------------
 // P[s] = Lt_{:, T_s} U_{T_s}: BM assets x BN GEMM columns over the period
 // range of split s; U's three planes give three products per step.
 // --------------------------------------------------------------------------
@@ -439,8 +535,12 @@ int launch_b16_gemm(const BatchArgs &b, const BatchConfig &c, hipStream_t s) {
   const int64_t T = b.base.cols, n = b.base.n;
   const int bn = c.g_bn;  // width of the target tiles
   if (b.u_split) {
-    const dim3 gu((unsigned)((T + 31) / 32), (unsigned)((b.running + 31) / 32));
-    hipLaunchKernelGGL(k_b16_u_split, gu, dim3(512), 0, s, b);
+    const int w = b.u_split == 2 ? 16 : 32;
+    const dim3 gu((unsigned)((T + w - 1) / w), (unsigned)((b.running + w - 1) / w));
+    if (w == 16)
+      hipLaunchKernelGGL(k_b16_u_small, gu, dim3(512), 0, s, b);
+    else
+      hipLaunchKernelGGL(k_b16_u_split, gu, dim3(512), 0, s, b);
   } else if (bn == 128) {
     const dim3 gu((unsigned)((T + 63) / 64), (unsigned)((b.m + 127) / 128));
     hipLaunchKernelGGL((k_b16_u<128, 64, 2, 2>), gu, dim3(256), 0, s, b);

@@ -239,7 +239,7 @@ struct BatchArgs {
   uint16_t *Xp;
   int64_t xpstride;
   int64_t stages;
-  int32_t u_split;     // the U GEMM by 32 x 32 tiles split over the assets inside a workgroup
+  int32_t u_split;     // the U GEMM by 32 x 32 (1) or 16 x 16 (2) tiles split over the assets inside a workgroup
   int32_t running;     // host's upper bound of *mact (columns a launch has to cover)
 };
 

@@ -60,3 +60,12 @@ def test_covariance_form_edges(npga, n, T, m):
     for k, j in enumerate(pick):
         assert infos[j]["status"] == 0 and infos[j]["refined"] == 1, (j, infos[j])
         _check_parity(Xh[j], infos[j], L_o, mu_o, rs[j], 0.0, ref[k], f"target {j}")
+
+
+@pytest.mark.parametrize("n,T,m", [(15, 7, 1), (31, 16, 15), (33, 17, 16), (255, 15, 17), (257, 100, 33), (1500, 701, 24),
+                                   (40, 2048, 32), (40, 2049, 32), (1000, 512, 128)])
+def test_gradient_small_tiles(npga, n, T, m):
+    """The bfloat16 U product by 16 x 16 tiles (up to 64 tiles of 32 x 32):
+    32-asset steps of eight wavefronts; the last but one shape is the first
+    past the bound.  The bar of test_gradient_edges."""
+    test_gradient_edges(npga, n, T, m, "bf16")
