@@ -1237,6 +1237,7 @@ struct BatchLayout {
 constexpr int kMaxSplits = 64;
 constexpr int64_t kUSplitMax = 512;
 constexpr int64_t kUSmallMax = 64;
+constexpr int64_t kGSmallMaxCols = 2048;
 constexpr int kNumVec = 9;  // xbuf0, xbuf1, gbuf0, gbuf1, pvec, fvec, gvec, xa, ga
 
 // cov: the covariance form (Sigma, the bfloat16 planes the SYRK reads, and a
@@ -1314,6 +1315,11 @@ npga::BatchArgs with_config(npga::BatchArgs b, const npga::BatchConfig &cfg, int
   const int64_t kc = ((cols + cfg.splits - 1) / cfg.splits + 31) / 32 * 32;
   b.kchunk = kc;
   b.splits = (int32_t)((cols + kc - 1) / kc);
+  // The bfloat16 G GEMM of a small product by 16 x 16 tiles that fit the chip
+  // at once, over all periods: the tails then read one sum (as two float32)
+  // where the configuration has a sum for every range
+  b.g_small = b.Lt && cols <= kGSmallMaxCols && (b.base.n + 31) / 32 * ((running + 31) / 32) <= kUSmallMax ? 1 : 0;
+  if (b.g_small) b.splits = 2;
   // The U GEMM: the configuration's tiles, or 32 x 32 tiles split over the
   // assets inside a workgroup while those are at most kUSplitMax workgroups
   // (one to two rounds of the chip); on the bfloat16 cores 16 x 16 tiles while

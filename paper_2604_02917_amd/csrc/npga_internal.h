@@ -240,6 +240,7 @@ struct BatchArgs {
   int64_t xpstride;
   int64_t stages;
   int32_t u_split;     // the U GEMM by 32 x 32 (1) or 16 x 16 (2) tiles split over the assets inside a workgroup
+  int32_t g_small;     // the G GEMM by 16 x 16 tiles split over the periods inside a workgroup
   int32_t running;     // host's upper bound of *mact (columns a launch has to cover)
 };
 
