@@ -1281,7 +1281,7 @@ BatchLayout batch_layout(int64_t n, int64_t cols, int32_t m, bool cov = false) {
     l.stages = npga::split_stages(n);
     l.xpstride = 48 * l.stages;
     l.off_planes = take(std::max(npga::syrk_split_bytes(n, cols), sizeof(uint16_t) * (size_t)npga::split_k_elems(n, n)));
-    l.off_xp = take(sizeof(uint16_t) * (size_t)m * (size_t)l.xpstride);
+    l.off_xp = take(sizeof(uint16_t) * (size_t)((m + 31) / 32 * 32) * (size_t)l.xpstride);
     l.off_l32 = take(sizeof(float) * (size_t)l.ld32 * (size_t)cols);
   } else {
     // bfloat16 factors: U planes and the row-major copy of L
@@ -1678,7 +1678,7 @@ int npga_solve_batched(const npga_factor *f, const double *r_targets, int32_t m,
     b.Xp = reinterpret_cast<uint16_t *>(base + lay.off_xp);
     b.xpstride = lay.xpstride;
     b.stages = lay.stages;
-    LAUNCHCHK(npga::launch_zero_f32(reinterpret_cast<float *>(b.Xp), (int64_t)m * lay.xpstride / 2, stream));
+    LAUNCHCHK(npga::launch_zero_f32(reinterpret_cast<float *>(b.Xp), (int64_t)((m + 31) / 32 * 32) * lay.xpstride / 2, stream));
     b.base.L = sigma;
     b.base.ld = lay.lds;
     b.base.cols = f->n;

@@ -477,18 +477,27 @@ __global__ __launch_bounds__(256) void k_bgemm_g(BatchArgs b) {
 // and its gap are saved.
 // --------------------------------------------------------------------------
 
-// The planes of x (n floats at xs in LDS; zeros past n) into target j's fragment pieces: one 16-byte group of each plane a thread.
+// Target j's place in the planes of X: a fragment of 32 targets, 16 assets
+// and one plane is 64 pieces of 16 bytes, piece 32 h + j % 32 the assets 8 h ..
+// 8 h + 7 of target j.
+constexpr int kXFrag = 512;
+__device__ __forceinline__ uint16_t *x_planes(const BatchArgs &b, int j) {
+  return b.Xp + (int64_t)(j >> 5) * 32 * b.xpstride + 8 * (j & 31);
+}
+
+// The planes of x (n floats at xs in LDS; zeros past n) into target j's
+// pieces: one 16-byte group of each plane a thread.
 __device__ __forceinline__ void store_x_planes(const BatchArgs &b, int j, const float *xs) {
-  uint16_t *out = b.Xp + (int64_t)j * b.xpstride;
+  uint16_t *out = x_planes(b, j);
   for (int64_t q = threadIdx.x; 8 * q < b.base.n; q += 256) {
     float v[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] = (8 * q + e < b.base.n) ? xs[8 * q + e] : 0.f;
     u4v w[3];
     split8(v, w);
-    uint16_t *o = out + (q >> 1) * 48 + (q & 1) * 8;
+    uint16_t *o = out + (q >> 1) * 3 * kXFrag + (q & 1) * 256;
 #pragma unroll
-    for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<u4v *>(o + 16 * pl) = w[pl];
+    for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<u4v *>(o + kXFrag * pl) = w[pl];
   }
 }
 
@@ -497,7 +506,8 @@ __device__ __forceinline__ void store_x_planes(const BatchArgs &b, int j, const 
 // target's state says which iterate buffer is the current one, and the tail
 // works on copies in LDS (state, mu, both iterates where they fit); a load
 // after a barrier or a store would cost its latency each time.  n = 2000,
-// 128 targets: 13.1 us with the loads where they are used, 11.2 us so; n = 1500, 24
+// 128 targets: 13.1 us with the loads where they are used, 11.2 us so (12.0
+// with the planes it writes in k_cov16's fragments); n = 1500, 24
 // targets and 22 splits: 14.8 and 13.6 us.
 template <int E>
 __global__ __launch_bounds__(256) void k_btail(BatchArgs b) {
@@ -877,7 +887,9 @@ static int launch_bgemm_t(const BatchArgs &b, const BatchConfig &c, hipStream_t 
 // stages ahead; no LDS and no barrier until the four sums meet at the end.
 // Bound by the 64 bytes a cycle a compute unit takes from its L2 (12 KiB a
 // stage at 64 columns) and by latency: at n = 2000 a compute unit has 32
-// stages.
+// stages.  128 targets 10.5 us, 32 or fewer 6.6 us; with each target's planes
+// by themselves (a load of X's then touched 32 lines, not eight) 12.5 and 6.8,
+// and with loads past the last stage 13.1 and 7.1.
 template <int NC>
 __global__ __launch_bounds__(256, 1) void k_cov16(BatchArgs b) {
   constexpr int D = 4;  // stages in flight
@@ -908,7 +920,8 @@ __global__ __launch_bounds__(256, 1) void k_cov16(BatchArgs b) {
 #pragma unroll
   for (int q = 0; q < NC; ++q) {
     const int c = c0 + 32 * q + r;
-    pb[q] = b.Xp + (int64_t)b.act[c < ma ? c : ma - 1] * b.xpstride + (kb + wave) * 48 + 8 * h;
+    const int j = b.act[c < ma ? c : ma - 1];
+    pb[q] = x_planes(b, j) + (kb + wave) * 3 * kXFrag + 256 * h;
   }
   typedef bf16x8_t frag_t;
   frag_t fa[D][2][3], fb[D][NC][3];
@@ -922,7 +935,7 @@ __global__ __launch_bounds__(256, 1) void k_cov16(BatchArgs b) {
             __builtin_bit_cast(frag_t, *reinterpret_cast<const u4v *>(pa[g] + s * kPanelStage + pl * 4 * kFrag));
 #pragma unroll
       for (int q = 0; q < NC; ++q)
-        fb[slot][q][pl] = __builtin_bit_cast(frag_t, *reinterpret_cast<const u4v *>(pb[q] + s * 48 + 16 * pl));
+        fb[slot][q][pl] = __builtin_bit_cast(frag_t, *reinterpret_cast<const u4v *>(pb[q] + (s * 3 + pl) * kXFrag));
     }
   };
   v16f acc[2][NC];
@@ -953,7 +966,7 @@ __global__ __launch_bounds__(256, 1) void k_cov16(BatchArgs b) {
               for (int q = 0; q < NC; ++q)
                 acc[g][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[u][q][kx[k]], fa[u][g][ka[k]], acc[g][q], 0, 0, 0);
         }
-        load(u, t0 + u + D);
+        if (t0 + u + D < cnt) load(u, t0 + u + D);
       }
     }
   }

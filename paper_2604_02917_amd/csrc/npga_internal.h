@@ -231,9 +231,9 @@ struct BatchArgs {
   // covariance form: the gradient is 2 Sigma X by one GEMM whose contraction
   // is split into `splits` ranges of `kchunk` 16-row stages; the tails take
   // f = x^T g / 2.  Sp: Sigma as three bfloat16 planes in fragment order
-  // (`stages` stages); Xp: target j's float32 iterate as three planes,
-  // [stage][plane][16] from Xp + j xpstride, written by the kernel that
-  // writes the iterate (zeros past n)
+  // (`stages` stages); Xp: the targets' float32 iterates as three planes in
+  // fragment order, 32 targets to a fragment (xpstride a target's share),
+  // written by the kernels that write the iterates (zeros past n)
   int32_t covariance;
   const uint16_t *Sp;
   uint16_t *Xp;
