@@ -173,7 +173,15 @@ __global__ __launch_bounds__(256, 1) void k_loop(SolveArgs m, LoopArgs la) {
   __shared__ float dsh[KIND == kLoopSymv ? NP : 1];
   __shared__ double redbuf[red_buf_doubles<4>()], mbuf[8], ush[4 + kLoopMaxGroups];
   __shared__ int64_t ibuf[8];
-  if (m.st->done != kRunning) return;  // nobody changes it before the first exchange
+  if (m.st->done != kRunning) {  // (nobody changes it before the first exchange)
+    // the phase was over before it began (an estimate that overflowed, a start
+    // projection that was not bracketed): the host waits for the code
+    if (blockIdx.x == 0 && threadIdx.x == 0 && m.host_done) {
+      m.host_done[1] = 0;
+      m.host_done[0] = m.st->done;
+    }
+    return;
+  }
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t n = m.n;
