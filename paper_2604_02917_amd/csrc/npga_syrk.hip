@@ -495,6 +495,14 @@ __global__ __launch_bounds__(256, 1) void k_mm16(Mm16 m) {
     MM16_STEP(0, 2), MM16_STEP(1, -1), MM16_STEP(0, -1), MM16_STEP(1, -1);
     MM16_STEP(0, 3), MM16_STEP(1, -1), MM16_STEP(0, -1), MM16_STEP(1, -1);
   }
+  if (s > 0 && s < ns) {
+    // 4, 8 or 12 stages are left.  They begin new sums: block 0 holds a whole
+    // period by now, and without this its last sum ran over up to 28 stages.
+    // (Flushes at the quarters of the last, shorter period instead: 7.27 ms
+    // against 7.11 at n = 5440, T = 48374, more registers live in the loop.)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) flush(q, 0, 16);
+  }
   for (; s < ns; s += 2) MM16_STEP(0, -1), MM16_STEP(1, -1);
 #undef MM16_STEP
 #undef MM16_J
