@@ -17,15 +17,15 @@
 //     overwritten before it is read: a workgroup writes step s + 2's words
 //     (same half of the double buffer) only after it has read step s + 1's,
 //     which the others write after reading step s's.  On the factor path,
-//     where every workgroup reads all the others' vectors, a word is two
-//     floats, and a word that no arithmetic produces stands for one that has
-//     not arrived (half the words and one round of looks for 16 workgroups:
-//     3.5 us of a step became 2.2).
+//     where every workgroup reads all the others' vectors, a word is all
+//     data, and a word that no arithmetic produces stands for one that has
+//     not arrived (fewer words than with a number in each, and one round of
+//     looks for 16 workgroups).
 // Bound by latency: the exchange, the tail's reductions and a barrier or two.
 // Per NPGA step, a launch per step and one launch: n = 64 on Sigma 12 and 3.8
 // us, n = 501 on Sigma 11 and 4.9 us (16 workgroups), n = 1001, T = 403 on L
-// 19 and 9.0 us (14 workgroups; CG 10.0); whole solves 3.4 -> 1.3 ms, 4.6 -> 2.05 ms,
-// 15.2 -> 8.5 ms.  (Waiting before the first look at the others' words, which
+// 19 and 10.3 us (14 workgroups; CG 11.3); whole solves 3.4 -> 1.3 ms, 4.6 -> 2.05 ms,
+// 15.2 -> 10.0 ms.  (Waiting before the first look at the others' words, which
 // halves a column of the tridiagonalisation, gains nothing here: 1 % at n =
 // 501, and a loss on L, where the looks are many and spread.)
 // With one workgroup there is no exchange.  Every wait is bounded: after
@@ -37,6 +37,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdint>
+#include <type_traits>
 
 #include "npga_device.h"
 #include "npga_internal.h"
@@ -52,10 +53,18 @@ namespace {
 // leave of the LDS.
 constexpr int loop_resident(int E, bool symv) { return symv ? 32 / E : (E == 1 ? 16 : E == 2 ? 12 : 4); }
 
-// Words of one workgroup's piece of the factor path's exchange: a thread's
-// entries two to a word, and ||u||^2.
-constexpr int kLoopPairs(int E) { return E == 1 ? 1 : E / 2; }
-constexpr int kLoopPiece(int E) { return 256 * kLoopPairs(E) + 8; }
+// Words of one workgroup's piece of the factor path's exchange, and ||u||^2.
+// A piece is a float64 sum over the workgroup's columns, and no float32
+// rounding may come between it and the total: with few pieces, each of many
+// columns, it would weigh more than in the launches' sums of four columns
+// each.  Up to two entries a thread go as float64; four as their float32
+// values, two to a word, and a word of the four remainders in bfloat16 (32
+// bits in all).  Error of L L^T x against float64, relative, n = 1001, T =
+// 403 / n = 300, T = 1400: the launches 2.0e-8 / 0.9e-8, float32 sums and
+// pieces 2.4e-8 / 1.4e-8, float32 pieces alone 2.0e-8 / 0.94e-8, so 1.8e-8 /
+// 0.8e-8.  At n = 1001, T = 403 the solve takes 8.9, 9.4 and 10.0 ms.
+constexpr int kLoopWords(int E) { return E <= 2 ? E : 3; }
+constexpr int kLoopPiece(int E) { return 256 * kLoopWords(E) + 8; }
 constexpr unsigned long long kLoopUnset = 0xFFFFDEAD5EAF0001ull;  // (no arithmetic produces these NaN)
 
 enum LoopKind { kLoopSymv = 0, kLoopSweep = 1, kLoopSweep16 = 2 };
@@ -168,7 +177,9 @@ __global__ __launch_bounds__(256, 1) void k_loop(SolveArgs m, LoopArgs la) {
   __shared__ DevState st;
   __shared__ double vec[8][NP];
   __shared__ __attribute__((aligned(16))) float xs[NP];
-  __shared__ f4 comb[KIND == kLoopSymv ? 1 : 4 * 64 * E];
+  constexpr int CW = E <= 2 ? 4 : 2;  // wavefronts' sums that fit beside the rest
+  typedef double d4 __attribute__((ext_vector_type(4)));
+  __shared__ __attribute__((aligned(32))) double comb[KIND == kLoopSymv ? 4 : CW * NP];
   __shared__ f4 slab_lds[KIND == kLoopSymv ? 1 : 4 * R * E * 64];
   __shared__ float dsh[KIND == kLoopSymv ? NP : 1];
   __shared__ double redbuf[red_buf_doubles<4>()], mbuf[8], ush[4 + kLoopMaxGroups];
@@ -325,12 +336,13 @@ __global__ __launch_bounds__(256, 1) void k_loop(SolveArgs m, LoopArgs la) {
         for (int j = 0; j < E; ++j) sum[j] = got[0][j];
       }
     } else {
-      f4 g[E];
+      d4 g[E];
       double usq_w = 0.0;
 #pragma unroll
-      for (int j = 0; j < E; ++j) g[j] = f4{0.f, 0.f, 0.f, 0.f};
+      for (int j = 0; j < E; ++j) g[j] = d4{0.0, 0.0, 0.0, 0.0};
       // two items at a time: a product is a chain of some fifty dependent
-      // instructions
+      // instructions.  Their sum leaves float32 (the launches add four
+      // columns at least before theirs does).
       auto take2 = [&](const f4(&c0)[E], bool live0, const f4(&c1)[E], bool live1) {
         float d0 = dot_part(c0, xr), d1 = dot_part(c1, xr);
         wave_sum2_f32(d0, d1);
@@ -340,10 +352,10 @@ __global__ __launch_bounds__(256, 1) void k_loop(SolveArgs m, LoopArgs la) {
         usq_w = fma((double)d1, (double)d1, usq_w);
 #pragma unroll
         for (int j = 0; j < E; ++j) {
-          g[j].x = fmaf(c1[j].x, d1, fmaf(c0[j].x, d0, g[j].x));
-          g[j].y = fmaf(c1[j].y, d1, fmaf(c0[j].y, d0, g[j].y));
-          g[j].z = fmaf(c1[j].z, d1, fmaf(c0[j].z, d0, g[j].z));
-          g[j].w = fmaf(c1[j].w, d1, fmaf(c0[j].w, d0, g[j].w));
+          g[j].x += (double)fmaf(c1[j].x, d1, c0[j].x * d0);
+          g[j].y += (double)fmaf(c1[j].y, d1, c0[j].y * d0);
+          g[j].z += (double)fmaf(c1[j].z, d1, c0[j].z * d0);
+          g[j].w += (double)fmaf(c1[j].w, d1, c0[j].w * d0);
         }
       };
       constexpr int F = 4;  // streamed items in flight
@@ -373,53 +385,122 @@ __global__ __launch_bounds__(256, 1) void k_loop(SolveArgs m, LoopArgs la) {
         }
       }
       if (lane == 0) ush[wave] = usq_w;
-      // entry i of the wavefronts' sums: float i of comb, wavefront stride NP
-      const float *cf = reinterpret_cast<const float *>(comb);
-      float part[E];
+      // the wavefronts' sums meet in float64
+      double part[E];
+      auto sums_at = [&](int w, int j) { return reinterpret_cast<d4 *>(comb + w * NP + 4 * lane + 256 * j); };
+      if (wave >= 4 - CW) {
 #pragma unroll
-      for (int j = 0; j < E; ++j) comb[wave * 64 * E + lane + 64 * j] = g[j];
+        for (int j = 0; j < E; ++j) *sums_at(wave - (4 - CW), j) = g[j];
+      }
       __syncthreads();
+      if constexpr (CW == 2) {
+        if (wave < 2) {
+#pragma unroll
+          for (int j = 0; j < E; ++j) *sums_at(wave, j) += g[j];
+        }
+        __syncthreads();
+      }
 #pragma unroll
       for (int j = 0; j < E; ++j) {
-        const int i = tid + 256 * j;
-        part[j] = ((cf[i] + cf[NP + i]) + cf[2 * NP + i]) + cf[3 * NP + i];
+        const double *cf = comb + tid + 256 * j;
+        part[j] = CW == 2 ? cf[0] + cf[NP] : (cf[0] + cf[NP]) + (cf[2 * NP % (CW * NP)] + cf[3 * NP % (CW * NP)]);
       }
       const double up = ((ush[0] + ush[1]) + ush[2]) + ush[3];
       usq = up;
       if (W == 1) {
 #pragma unroll
-        for (int j = 0; j < E; ++j) tot[j] = (double)part[j];
+        for (int j = 0; j < E; ++j) tot[j] = part[j];
       } else {
         // W pieces.  Three buffers in turn; a step's word is unset again
         // two steps before its next use, when every reader has shown (by its
         // own next piece) that it is done with it, and before this thread's
         // next piece, which a reader of the new word has to see first.
-        constexpr int PQ = kLoopPairs(E);
+        constexpr int PQ = kLoopWords(E);
         unsigned long long *buf = words + (uint32_t)(s % 3) * (uint32_t)(W * kLoopPiece(E));
         unsigned long long *own = buf + (uint32_t)me * (uint32_t)kLoopPiece(E);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if constexpr (E <= 2) {
 #pragma unroll
-        for (int j = 0; j < PQ; ++j)
-          set_word(own + tid + 256 * j,
-                   ((unsigned long long)__float_as_uint(E == 1 ? 0.f : part[(2 * j + 1) % E]) << 32) |
-                       __float_as_uint(part[2 * j % E]));
+          for (int j = 0; j < E; ++j) set_word(own + tid + 256 * j, (unsigned long long)__double_as_longlong(part[j]));
+        } else {
+          unsigned long long w[3] = {0ull, 0ull, 0ull};
+#pragma unroll
+          for (int j = 0; j < E; ++j) {
+            const float hi = (float)part[j];
+            const float lo = isfinite(hi) ? (float)(part[j] - (double)hi) : 0.f;
+            w[j / 2] |= (unsigned long long)__float_as_uint(hi) << (32 * (j % 2));
+            w[2] |= (unsigned long long)(__float_as_uint(lo) >> 16) << (16 * j);
+          }
+#pragma unroll
+          for (int j = 0; j < PQ; ++j) set_word(own + tid + 256 * j, w[j]);
+        }
         // ||u||^2 enters the objective of a stopping test only
         const bool wants_usq = MODE == kTailNpga && st.iter % st.check_every == 0;
         if (wants_usq && tid == 0) set_word(own + 256 * PQ, (unsigned long long)__double_as_longlong(up));
 #pragma unroll
         for (int j = 0; j < E; ++j) tot[j] = 0.0;
-        constexpr int G = 16;  // pieces in flight, added in order
-        for (int w0 = 0; w0 < W && !bad; w0 += G) {
-          unsigned long long v[G][PQ];
-          bad = !get_set_words<G, PQ>(buf + (uint32_t)w0 * (uint32_t)kLoopPiece(E), (uint32_t)tid,
-                                      (uint32_t)kLoopPiece(E), W - 1 - w0, 256u, v, wait);
+        float rest[E];  // (E = 4: the remainders)
 #pragma unroll
-          for (int x = 0; x < G; ++x)
+        for (int j = 0; j < E; ++j) rest[j] = 0.f;
+        // G pieces in flight, added in order; past the last, the last again.
+        // The remainders are asked for when the values are there, and arrive
+        // while those are added.
+        auto pieces = [&](auto g_c, int w0) {
+          constexpr int G = decltype(g_c)::value, VQ = E <= 2 ? PQ : PQ - 1;
+          unsigned long long v[G][VQ];
+          const unsigned long long *from = buf + (uint32_t)w0 * (uint32_t)kLoopPiece(E);
+          bad = !get_set_words<G, VQ>(from, (uint32_t)tid, (uint32_t)kLoopPiece(E), W - 1 - w0, 256u, v, wait);
+          unsigned long long r[E <= 2 ? 1 : G][1];
+          if constexpr (E > 2) {
+#pragma unroll
+            for (int x = 0; x < G; ++x) {
+              const int xc = x < W - 1 - w0 ? x : W - 1 - w0;
+              r[x][0] = get_word(from + (tid + 256 * VQ + (uint32_t)xc * (uint32_t)kLoopPiece(E)));
+            }
+            __builtin_amdgcn_sched_barrier(0);
+          }
+#pragma unroll
+          for (int x = 0; x < G; ++x) {
+            const uint32_t keep = w0 + x < W ? 0xffffffffu : 0u;
 #pragma unroll
             for (int j = 0; j < E; ++j) {
-              const uint32_t u = (uint32_t)(v[x][j / 2] >> (32 * (j % 2)));
-              tot[j] += (w0 + x < W) ? (double)__uint_as_float(u) : 0.0;
+              if constexpr (E <= 2)
+                tot[j] += __longlong_as_double((long long)(v[x][j] & (((unsigned long long)keep << 32) | keep)));
+              else
+                tot[j] += (double)__uint_as_float((uint32_t)(v[x][j / 2] >> (32 * (j % 2))) & keep);
             }
+          }
+          if constexpr (E > 2) {
+            uint32_t miss = 0u;
+#pragma unroll
+            for (int x = 0; x < G; ++x) miss |= r[x][0] == kLoopUnset ? 1u : 0u;
+            if (miss && !bad)
+              bad = !get_set_words<G, 1>(from, (uint32_t)tid + 256u * VQ, (uint32_t)kLoopPiece(E), W - 1 - w0, 0u, r, wait);
+#pragma unroll
+            for (int x = 0; x < G; ++x) {
+              const uint32_t keep = w0 + x < W ? 0xffffffffu : 0u;
+#pragma unroll
+              for (int j = 0; j < E; ++j) {
+                const uint32_t lo = (uint32_t)(r[x][0] >> (32 * (j / 2)));
+                rest[j] += __uint_as_float((j % 2 ? lo & 0xffff0000u : lo << 16) & keep);
+              }
+            }
+          }
+        };
+        for (int w0 = 0; w0 < W && !bad; w0 += 16) {
+          const int left = W - w0;
+          if (left > 12)
+            pieces(std::integral_constant<int, 16>{}, w0);
+          else if (left > 8)
+            pieces(std::integral_constant<int, 12>{}, w0);
+          else if (left > 4)
+            pieces(std::integral_constant<int, 8>{}, w0);
+          else
+            pieces(std::integral_constant<int, 4>{}, w0);
+        }
+        if constexpr (E > 2) {
+#pragma unroll
+          for (int j = 0; j < E; ++j) tot[j] += (double)rest[j];
         }
         if (wants_usq && tid < W && !bad) {
           unsigned long long v[1][1];
@@ -504,7 +585,8 @@ __global__ __launch_bounds__(256) void k_loop_unset(unsigned long long *p, int64
 // time of an exchange).  Beyond, eight rows of Sigma a wavefront; on the
 // factor path, where every workgroup reads all the others' n-vectors, as
 // many as balance that against the columns a workgroup works through, or as
-// hold all the columns.
+// hold all the columns (n = 1001, T = 403: 14 workgroups 10.0 ms a solve, 16
+// the same, 12 and 10 10.4, 8 10.8).
 LoopPlan loop_plan(int64_t n, int64_t cols, int path, int dtype) {
   LoopPlan p{};
   const int e = slots_for(n);
