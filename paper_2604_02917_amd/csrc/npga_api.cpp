@@ -367,7 +367,7 @@ double step_lanczos_tol(const npga_options &o) {
 }
 
 int estimate_step(const Carved &c, int path, int slots, const npga_options &o, hipStream_t s, double lz_tol,
-                  LoopRun *lr = nullptr, int32_t *host_words = nullptr) {
+                  LoopRun *lr = nullptr) {
   if (o.alpha > 0.0) return npga::launch_set_alpha(c.st, o.step_safety, s, o.alpha);  // given by the caller
   if (npga::launch_random_unit(c.a.xbuf0, c.a.xs, c.a.n, o.seed, s)) return 1;
   Carved cp = c;
@@ -377,7 +377,6 @@ int estimate_step(const Carved &c, int path, int slots, const npga_options &o, h
     if (npga::launch_lanczos_init(cp.a, lz_tol, s)) return 1;
     steps = std::min(o.power_iters, npga::kLanczosMax);
     if (lr && lr->on) {
-      cp.a.host_done = host_words;
       if (loop_launch(cp, lr, path, slots, steps, s)) return 1;
       return npga::launch_set_alpha(c.st, o.step_safety, s);
     }
@@ -623,14 +622,13 @@ size_t npga_solve_workspace_size(int64_t n, int64_t cols, const npga_options *op
   return t;
 }
 
-// kAgainByLaunches: a one-launch phase could not run to its end (the waits
-// between its workgroups are bounded) before anything was decided; the
-// caller repeats the solve with a launch per step.
+// kAgainByLaunches: the step-size estimate as one launch could not run to its
+// end (the waits between its workgroups are bounded) and nothing ran after
+// it; the caller repeats the solve with a launch per step.
 constexpr int kAgainByLaunches = -1;
 
 static int solve_once(const npga_factor *f, double r, const npga_options *opt, float *x, npga_result *res,
-                      void *ws, size_t ws_bytes, hipStream_t stream, bool by_loop = true) {
-  const auto t0 = Clock::now();
+                      void *ws, size_t ws_bytes, hipStream_t stream, Clock::time_point t0, bool by_loop) {
   npga_options o;
   npga_default_options(&o);
   if (opt) o = *opt;
@@ -679,10 +677,7 @@ static int solve_once(const npga_factor *f, double r, const npga_options *opt, f
   // step size alpha = 1/(safety L_f_hat) from ||L_eff||_2^2 (Sec. 3.1 Remark)
   LoopRun lr;
   if (by_loop) LAUNCHCHK(loop_start(c, &lr, stream));
-  const bool lz_loop = lr.on;
-  int32_t *lz_words = &pin[1].done;  // done code and steps run, stored by the device
-  lz_words[1] = 0;
-  LAUNCHCHK(estimate_step(c, path, slots, o, stream, step_lanczos_tol(o), &lr, pinned_dev(pin, lz_words)));
+  LAUNCHCHK(estimate_step(c, path, slots, o, stream, step_lanczos_tol(o), &lr));
 
   // x^0 = Pi_F(x_in or 1/n)
   LAUNCHCHK(npga::launch_set_vector(c.a.xbuf0, o.warm_start ? x : nullptr, nullptr, f->n,
@@ -697,10 +692,7 @@ static int solve_once(const npga_factor *f, double r, const npga_options *opt, f
   int e = run_phase(c, path, slots, o.check_every, main_chunks, stream, pin, evs, ev0, &done, &tol_ms, &tm,
                     &lr);
   if (e) return e;
-  if (lz_loop && *static_cast<const volatile int32_t *>(lz_words + 1) < 0) {
-    HIPCHK(hipStreamSynchronize(stream));
-    return kAgainByLaunches;
-  }
+  if (done == npga::kStalled) return kAgainByLaunches;
   const int main_done = done;
   HIPCHK(hipMemcpyAsync(&pin[2], c.st, sizeof(DevState), hipMemcpyDeviceToHost, stream));
   HIPCHK(hipStreamSynchronize(stream));
@@ -836,11 +828,12 @@ int npga_solve(const npga_factor *f, double r, const npga_options *opt, float *x
   npga_options o;
   npga_default_options(&o);
   if (opt) o = *opt;
-  int e = solve_once(f, r, &o, x, res, ws, ws_bytes, stream);
-  if (e == kAgainByLaunches) e = solve_once(f, r, &o, x, res, ws, ws_bytes, stream, false);
+  const auto t0 = Clock::now();
+  int e = solve_once(f, r, &o, x, res, ws, ws_bytes, stream, t0, true);
+  if (e == kAgainByLaunches) e = solve_once(f, r, &o, x, res, ws, ws_bytes, stream, t0, false);
   if (e != NPGA_ERR_BRACKET || o.projection == 1) return e;
   o.projection = 1;
-  return solve_once(f, r, &o, x, res, ws, ws_bytes, stream, false);
+  return solve_once(f, r, &o, x, res, ws, ws_bytes, stream, t0, false);
 }
 
 int npga_project(const double *v, const double *mu, int64_t n, double r, double *x, double *nu_tau,

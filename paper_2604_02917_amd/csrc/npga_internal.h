@@ -21,6 +21,7 @@ enum DoneCode : int32_t {
   kMaxIter = 2,
   kNumeric = 3,
   kBracket = 4,
+  kStalled = 5,  // a one-launch step-size estimate that gave up a wait: nothing after it runs
 };
 
 // Tail modes of the reduce-and-update kernel.

@@ -31,7 +31,9 @@
 // With one workgroup there is no exchange.  Every wait is bounded: after
 // LoopArgs::wait_ticks a workgroup raises the abort word and leaves, the others
 // follow, the state is that of the last whole iteration, and the host goes
-// on with the launch-per-step path.
+// on with the launch-per-step path.  An estimate that ended so leaves the
+// state kStalled, at which the phase after it does not begin, and the host
+// starts again with that path.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -556,6 +558,12 @@ __global__ __launch_bounds__(256, 1) void k_loop(SolveArgs m, LoopArgs la) {
 
   if (me != 0) return;
   // the first workgroup's copies are the result
+  if constexpr (MODE == kTailLanczos) {
+    if (stalled) {  // the iterations cannot start from an unfinished estimate
+      if (tid == 0) st.done = kStalled;
+      __syncthreads();
+    }
+  }
   double *dst[8] = {m.xbuf0, m.xbuf1, m.gbuf0, m.gbuf1, nullptr, m.pvec, m.fvec, m.gvec};
 #pragma unroll
   for (int q = 0; q < 8; ++q)
