@@ -278,9 +278,13 @@ int npga_auto_path(int64_t n, int64_t cols, int32_t dtype);
  * work may keep some of the workgroups from starting) the launch ends and
  * the solve goes on with a launch per step, with the same result.  The
  * sketch's eigensolver does the same (its tridiagonalisation: up to 256
- * workgroups).  us = 0: it ends at the first exchange; us < 0: always a
- * launch per step.  Applies to the calling host thread; returns the previous
- * value.                                                                   */
+ * workgroups, one to a compute unit).  A stream whose compute units do not
+ * hold the workgroups together (hipExtStreamCreateWithCUMask) takes the
+ * launches without a wait.  Tridiagonalisations of several host threads of
+ * a process take turns on the chip; beside other processes' work, or a
+ * solve's launch that starts at the same time, the wait is the bound.
+ * us = 0: it ends at the first exchange; us < 0: always a launch per step.
+ * Applies to the calling host thread; returns the previous value.          */
 int64_t npga_set_loop_wait(int64_t us);
 int npga_solve(const npga_factor *f, double r, const npga_options *opt, float *x,
                npga_result *res, void *ws, size_t ws_bytes, hipStream_t stream);

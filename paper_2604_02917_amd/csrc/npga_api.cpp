@@ -100,6 +100,22 @@ int sweep_grid_for(int64_t cols) {
   return (int)std::max<int64_t>(1, std::min<int64_t>(g, 256));
 }
 
+int stream_compute_units(hipStream_t s) {
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+    return 0;
+  constexpr uint32_t kWords = 32;
+  uint32_t mask[kWords] = {};
+  if (hipExtStreamGetCUMask(s, kWords, mask) != hipSuccess) {
+    (void)hipGetLastError();
+    return cus;
+  }
+  int held = 0;
+  for (uint32_t w : mask) held += __builtin_popcount(w);
+  return held > 0 ? std::min(held, cus) : cus;
+}
+
 size_t loop_bytes(int64_t n, int64_t cols, int path) {
   const int64_t half = std::max(loop_plan(n, cols, path, NPGA_F32).half, loop_plan(n, cols, path, NPGA_BF16).half);
   return sizeof(unsigned long long) * (size_t)(8 + 2 * half);
@@ -333,11 +349,14 @@ int step(const Carved &c, int path, int slots, hipStream_t s) {
 
 // The exchange words cleared for a solve that may use the one-launch phases
 // (backtracking, Dykstra's projections, float64 products and the
-// preconditioned face solves take the launches).
+// preconditioned face solves take the launches, and a stream of fewer
+// compute units than workgroups, which wait for each other).
 int loop_start(const Carved &c, LoopRun *lr, hipStream_t s) {
   lr->seq = 0;
   lr->on = c.loop.groups > 0 && !c.a.dykstra && !c.a.backtrack && g_loop_wait_us >= 0;
   if (!lr->on || c.loop.groups == 1) return 0;
+  lr->on = c.loop.groups <= npga::stream_compute_units(s);
+  if (!lr->on) return 0;
   return npga::launch_zero_f32(reinterpret_cast<float *>(c.xch), 2 * (8 + 2 * c.loop.half), s);
 }
 
@@ -1137,11 +1156,12 @@ int npga_sketch_str_ex(const float *L, int64_t n, int64_t T, int64_t ldl, const 
   // truncation stage: eigenpairs of G = Y^T Y
   LAUNCHCHK(npga::launch_gram_f64(Y, lay.ldy, n, k, s.A, stream));
   LAUNCHCHK(npga::launch_frob(Y, lay.ldy, n, k, frob, kFrobParts, stream));
-  // the tridiagonalisation in one launch; should a wait inside it run out,
-  // that launch's columns and what follows once more, by launches
+  // the tridiagonalisation in one launch, where its workgroups fit the
+  // stream's compute units at once; should a wait inside it run out, that
+  // launch's columns and what follows once more, by launches
   void *slots = base + lay.off_planes;
   double *h = reinterpret_cast<double *>(&pin[3]);  // [0, 1]: gamma; or ell, bad input; [2]: the launch's flag
-  bool by_chip = g_loop_wait_us >= 0;
+  bool by_chip = g_loop_wait_us >= 0 && npga::tri_chip_fits(k, stream);
   if (by_chip)
     LAUNCHCHK(npga::launch_tridiag_chip(s, slots, 100 * (long long)g_loop_wait_us, stream));
   else

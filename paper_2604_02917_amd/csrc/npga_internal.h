@@ -295,6 +295,8 @@ struct LoopPlan {
   int64_t half;
 };
 LoopPlan loop_plan(int64_t n, int64_t cols, int path, int dtype);
+// Compute units that launches on a stream may run on (those of its mask).
+int stream_compute_units(hipStream_t s);
 int launch_loop(const SolveArgs &a, const LoopArgs &la, int groups, int slots, int path, hipStream_t s);
 
 // ---- launchers (defined in the .hip files; return hipError_t as int) ----

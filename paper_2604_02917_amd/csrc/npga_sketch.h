@@ -38,9 +38,13 @@ int launch_tridiag(const SketchState &s, int64_t i_begin, int64_t i_end, hipStre
 // afterwards if a launch could not run to its end (a wait between its
 // workgroups lasted longer than `ticks` of the 100 MHz counter);
 // launch_tridiag_resume, given that word, then does its columns and what
-// follows with a launch per stage.
+// follows with a launch per stage.  Launches of several streams of a process
+// follow each other, whichever host threads make them.
 constexpr int64_t kTriMax = 4096;
 size_t tri_chip_bytes(int64_t k);
+// Whether the workgroups of each of its launches fit the stream's compute
+// units together (they wait for each other).
+bool tri_chip_fits(int64_t k, hipStream_t st);
 int launch_tridiag_chip(const SketchState &s, void *slots, long long ticks, hipStream_t st);
 int launch_tridiag_resume(const SketchState &s, void *slots, uint64_t flag, hipStream_t st);
 int launch_bisect(const SketchState &s, int64_t ell, hipStream_t st);

@@ -35,6 +35,7 @@
 
 #include <algorithm>
 #include <cstdint>
+#include <mutex>
 #include <type_traits>
 
 #include "npga_device.h"
@@ -461,35 +462,92 @@ size_t tri_chip_bytes(int64_t k) {
   return sizeof(double) * tri_plan(s, nullptr, 0).words;
 }
 
+namespace {
+
+struct TriKernel {
+  void (*fn)(SketchState, TriRun);
+  unsigned groups, lds;
+};
+TriKernel tri_kernel(int sl, int64_t m) {
+  constexpr int kRows7 = 5, kRows8 = 5;  // rows in LDS
+  constexpr unsigned row = (unsigned)sizeof(double) * 7 * kTriT;
+  switch (sl) {
+    case 1: return {k_tri_chip<1, 4, 0, 128, 1>, (unsigned)std::min<int64_t>(128, m), 0};
+    case 2: return {k_tri_chip<2, 4, 0, 256, 2>, 256, 0};
+    case 4: return {k_tri_chip<4, 8, 0, 256, 4>, 256, 0};
+    case 8: return {k_tri_chip<8, 14 - kRows8, kRows8, 256, 1, true>, 256, kRows8 * row};
+    default: return {k_tri_chip<7, 14 - kRows7, kRows7, 256, 3>, 256, kRows7 * row};
+  }
+}
+
+// The launches of two streams do not run side by side: each would hold a part
+// of the chip and wait for workgroups that the other keeps from starting.  A
+// stream's turn begins when the launches of the turn before it have ended
+// (an event the stream waits for; the host does not).
+class ChipTurn {
+  static constexpr int kDevices = 64;
+  static std::mutex lock_;
+  static hipEvent_t last_[kDevices];
+  std::lock_guard<std::mutex> held_;
+  hipStream_t st_;
+  int dev_ = -1;
+
+ public:
+  explicit ChipTurn(hipStream_t st) : held_(lock_), st_(st) {}
+  int begin() {
+    int d = 0;
+    if (hipGetDevice(&d) != hipSuccess || d < 0 || d >= kDevices) return 1;
+    if (last_[d]) {
+      if (hipStreamWaitEvent(st_, last_[d], 0) != hipSuccess) return 1;
+    } else if (hipEventCreateWithFlags(&last_[d], hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess) {
+      last_[d] = nullptr;
+      return 1;
+    }
+    dev_ = d;
+    return 0;
+  }
+  int end() { return hipEventRecord(last_[dev_], st_) == hipSuccess ? 0 : 1; }
+};
+std::mutex ChipTurn::lock_;
+hipEvent_t ChipTurn::last_[ChipTurn::kDevices] = {};
+
+}  // namespace
+
+bool tri_chip_fits(int64_t k, hipStream_t st) {
+  SketchState s{};
+  s.k = k;
+  const TriPlan p = tri_plan(s, nullptr, 0);
+  const int cus = stream_compute_units(st);
+  for (int l = 0; l < p.launches; ++l) {
+    const TriKernel t = tri_kernel(p.sl[l], p.run[l].m);
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(t.fn), kTriT, t.lds) !=
+        hipSuccess) {
+      (void)hipGetLastError();
+      return false;
+    }
+    if ((int64_t)per_cu * cus < (int64_t)t.groups) return false;
+  }
+  return true;
+}
+
 int launch_tridiag_chip(const SketchState &s, void *slots, long long ticks, hipStream_t st) {
   const TriPlan p = tri_plan(s, slots, ticks);
   if (p.run[0].i0 > 0) {
     if (launch_tridiag(s, 0, p.run[0].i0, st)) return (int)hipErrorLaunchFailure;
     if (mirror(s, p.run[0].i0, 1, st)) return (int)hipErrorLaunchFailure;
   }
+  ChipTurn turn(st);
+  if (turn.begin()) return (int)hipErrorUnknown;
   for (int l = 0; l < p.launches; ++l) {
     const TriRun &a = p.run[l];
     hipLaunchKernelGGL(k_tri_slots, dim3(2048), dim3(256), 0, st, a);
     if (hipGetLastError() != hipSuccess) return (int)hipErrorLaunchFailure;
-    const dim3 block(kTriT), narrow((unsigned)std::min<int64_t>(128, a.m)), wide(256);
-    switch (p.sl[l]) {
-      case 1: hipLaunchKernelGGL((k_tri_chip<1, 4, 0, 128, 1>), narrow, block, 0, st, s, a); break;
-      case 2: hipLaunchKernelGGL((k_tri_chip<2, 4, 0, 256, 2>), wide, block, 0, st, s, a); break;
-      case 4: hipLaunchKernelGGL((k_tri_chip<4, 8, 0, 256, 4>), wide, block, 0, st, s, a); break;
-      case 8:
-        hipLaunchKernelGGL((k_tri_chip<8, 9, 5, 256, 1, true>), wide, block, (unsigned)sizeof(double) * 5 * 7 * kTriT, st,
-                           s, a);
-        break;
-      default: {
-        constexpr int kRows = 5;  // in LDS
-        hipLaunchKernelGGL((k_tri_chip<7, 14 - kRows, kRows, 256, 3>), wide, block,
-                           (unsigned)sizeof(double) * kRows * 7 * kTriT, st, s, a);
-        break;
-      }
-    }
+    const TriKernel t = tri_kernel(p.sl[l], a.m);
+    hipLaunchKernelGGL(t.fn, dim3(t.groups), dim3(kTriT), t.lds, st, s, a);
     if (hipGetLastError() != hipSuccess) return (int)hipErrorLaunchFailure;
   }
-  return 0;
+  return turn.end() ? (int)hipErrorUnknown : 0;
 }
 
 int launch_tridiag_resume(const SketchState &s, void *slots, uint64_t flag, hipStream_t st) {
