@@ -124,8 +124,10 @@ typedef struct npga_options {
                             method of the paper's Remark.  Both approach ||L_eff||^2
                             from below; step_safety covers the remainder              */
   int32_t batch_config;  /* batched solves: tile configuration 0..NPGA_BATCH_CONFIGS-1
-                            (see npga_batched_tune), or -1 for the built-in choice
-                            from the shape; default -1                               */
+                            (see npga_batched_tune) of both products while as many
+                            targets run as its tiles are wide, or -1 for the built-in
+                            choice from the shape, which has kernels of its own for
+                            small products; default -1                               */
   double alpha;          /* > 0: the fixed step of Algorithm 1, given by the caller
                             (Algorithm 1 takes alpha as an input; convergence needs
                             alpha <= 1/L_f); no step estimate is made.  0 (default):
@@ -477,7 +479,9 @@ int npga_sketch_str(const float *L, int64_t n, int64_t T, int64_t ldl, int64_t k
  * npga_batched_tune - times each tile configuration on this factor and m
  * (reps U+G GEMM pairs each, HIP events on `stream`) and returns the fastest
  * in *best; ms_out (host, NPGA_BATCH_CONFIGS entries, may be NULL) receives
- * the mean time per pair.  Uses the workspace of npga_solve_batched.
+ * the mean time per pair.  (The built-in choice is not among them; for
+ * small products it is the faster one.)  Uses the workspace of
+ * npga_solve_batched.
  * ------------------------------------------------------------------------- */
 #define NPGA_MAX_BATCH 1024
 #define NPGA_BATCH_CONFIGS 12

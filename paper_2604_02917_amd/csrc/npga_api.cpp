@@ -1316,8 +1316,10 @@ bool batch_uses_covariance(int requested, int64_t n, int64_t cols) {
 }
 
 // Split and tile counts of a configuration for this factor and at most
-// `running` running targets.
-npga::BatchArgs with_config(npga::BatchArgs b, const npga::BatchConfig &cfg, int32_t running) {
+// `running` running targets.  named: the caller asked for this one, and both
+// products take its tiles; else the kernels for small products, which are not
+// in the table, are part of the choice.
+npga::BatchArgs with_config(npga::BatchArgs b, const npga::BatchConfig &cfg, int32_t running, bool named) {
   const int64_t cols = b.base.cols;
   if (b.covariance) {
     npga::cov_plan(b, running);
@@ -1331,7 +1333,7 @@ npga::BatchArgs with_config(npga::BatchArgs b, const npga::BatchConfig &cfg, int
   // The bfloat16 G GEMM of a small product by 16 x 16 tiles that fit the chip
   // at once, over all periods: the tails then read one sum (as two float32)
   // where the configuration has a sum for every range
-  b.g_small = b.Lt && cols <= kGSmallMaxCols && (b.base.n + 31) / 32 * ((running + 31) / 32) <= kUSmallMax ? 1 : 0;
+  b.g_small = !named && b.Lt && cols <= kGSmallMaxCols && (b.base.n + 31) / 32 * ((running + 31) / 32) <= kUSmallMax ? 1 : 0;
   if (b.g_small) b.splits = 2;
   // The U GEMM: the configuration's tiles, or 32 x 32 tiles split over the
   // assets inside a workgroup while those are at most kUSplitMax workgroups
@@ -1339,7 +1341,7 @@ npga::BatchArgs with_config(npga::BatchArgs b, const npga::BatchConfig &cfg, int
   // those fit the chip at once (64 of 32 x 32: n = 1000, T = 500, 128 targets
   // 10.3 us by 32 x 32 and 8.0 us by 16 x 16; 200: 16 and 30 us)
   const int64_t tiles = (cols + 31) / 32 * ((running + 31) / 32);
-  b.u_split = tiles > kUSplitMax ? 0 : b.Lt && tiles <= kUSmallMax ? 2 : 1;
+  b.u_split = named || tiles > kUSplitMax ? 0 : b.Lt && tiles <= kUSmallMax ? 2 : 1;
   if (b.u_split) {
     b.utiles = (int32_t)(b.u_split == 2 ? (cols + 15) / 16 : (cols + 31) / 32);
   } else if (b.Lt) {
@@ -1359,7 +1361,7 @@ bool use_b16(const npga_factor *f) {
 // Per-target vectors are laid out target-major inside each block: vector k
 // of target j at v + k * (npad m) + j * npad.
 npga::BatchArgs carve_batch(const npga_factor *f, const BatchLayout &l, void *ws, int32_t m,
-                            const npga::BatchConfig &cfg) {
+                            const npga::BatchConfig &cfg, bool named) {
   char *base = static_cast<char *>(ws);
   npga::BatchArgs b{};
   SolveArgs &a = b.base;
@@ -1399,7 +1401,7 @@ npga::BatchArgs carve_batch(const npga_factor *f, const BatchLayout &l, void *ws
     b.ldu16 = l.ldu16;
     b.u16plane = (int64_t)m * l.ldu16;
   }
-  return with_config(b, cfg, m);
+  return with_config(b, cfg, m, named);
 }
 
 // Per-call preparation of the bfloat16 path: Lt = L row-major (zero past
@@ -1491,7 +1493,7 @@ int pcg_build(const npga_factor *f, const SolveLayout &l, char *base, hipStream_
   b.act = act;
   b.mact = act + npga::kPreK;
   const npga::BatchConfig &cfg = batch_config_of(-1, f->n, f->cols, npga::kPreK);
-  b = with_config(b, cfg, npga::kPreK);
+  b = with_config(b, cfg, npga::kPreK, false);
   if (b.splits > npga::kPreMaxSplits || b.utiles > (f->cols + 31) / 32) return 1;
   if (npga::launch_pre_omega(a.xs, l.ldp, f->n, s)) return 1;
   if (npga::launch_bact_all(b, act, act + npga::kPreK, s)) return 1;
@@ -1514,7 +1516,7 @@ const npga::BatchConfig &config_for_running(const npga::BatchConfig &req, int64_
 // Runs chunks of check_every batched iterations until no target is running.
 // t_done[j] receives the GPU time from ev0 to the end of the chunk in which
 // target j stopped (unchanged for targets that stopped before the phase).
-int run_batch_phase(const npga::BatchArgs &b0, const npga::BatchConfig &req, int slots, int check_every,
+int run_batch_phase(const npga::BatchArgs &b0, const npga::BatchConfig &req, bool named, int slots, int check_every,
                     int64_t max_chunks, hipStream_t s, int32_t *dev_status, int32_t *pin_status,
                     int32_t *pin_status_dev, hipEvent_t *evs,
                     hipEvent_t ev0, double *t_done, SweepTimer *tm) {
@@ -1527,7 +1529,7 @@ int run_batch_phase(const npga::BatchArgs &b0, const npga::BatchConfig &req, int
   auto issue = [&](int slot) -> int {
     const npga::BatchConfig &cfg =
         b0.covariance ? req : config_for_running(req, b0.base.n, b0.base.cols, running);
-    const npga::BatchArgs b = with_config(b0, cfg, running);
+    const npga::BatchArgs b = with_config(b0, cfg, running, named && &cfg == &req);
     for (int i = 0; i < check_every; ++i) {
       if (i == 0 && tm && hipEventRecord(tm->a[slot], s) != hipSuccess) return NPGA_ERR_HIP;
       if (npga::launch_bgemm(b, cfg, s)) return NPGA_ERR_HIP;
@@ -1625,7 +1627,8 @@ int npga_solve_batched(const npga_factor *f, const double *r_targets, int32_t m,
   // plans its GEMM from the running targets)
   const npga::BatchConfig &cfg = batch_config_of(o.batch_config, f->n, f->cols, m);
   Carved c = carve(f, lay.single, ws, NPGA_PATH_GEMV);
-  npga::BatchArgs b = carve_batch(f, lay, ws, m, cfg);
+  const bool named = o.batch_config >= 0;
+  npga::BatchArgs b = carve_batch(f, lay, ws, m, cfg, named);
   const int slots = lay.single.slots;
   int32_t *dev_status = reinterpret_cast<int32_t *>(static_cast<char *>(ws) + lay.off_status);
 
@@ -1699,7 +1702,7 @@ int npga_solve_batched(const npga_factor *f, const double *r_targets, int32_t m,
     b.Lt = nullptr;
     b.U16 = nullptr;
     b.covariance = 1;
-    b = with_config(b, cfg, m);
+    b = with_config(b, cfg, m, named);
   }
   LAUNCHCHK(batch_prepare_b16(b, lay, stream));
   LAUNCHCHK(npga::launch_bset_x0(b, o.warm_start ? X : nullptr, ldx, stream));
@@ -1708,7 +1711,7 @@ int npga_solve_batched(const npga_factor *f, const double *r_targets, int32_t m,
 
   std::vector<double> t_done(m, -1.0);
   const int64_t main_chunks = (int64_t)o.max_iter / o.check_every + 4;
-  int e = run_batch_phase(b, cfg, slots, o.check_every, main_chunks, stream, dev_status, bp->status,
+  int e = run_batch_phase(b, cfg, named, slots, o.check_every, main_chunks, stream, dev_status, bp->status,
                           bp->status_dev, evs, ev0,
                           t_done.data(), &tm);
   if (e) return e;
@@ -1735,7 +1738,7 @@ int npga_solve_batched(const npga_factor *f, const double *r_targets, int32_t m,
       LAUNCHCHK(npga::launch_bphase_reset(br, o.refine_tol, o.refine_max_iter, stream));
       LAUNCHCHK(npga::launch_bcg_init(br, slots, stream));
       const int64_t ref_chunks = (int64_t)o.refine_max_iter / o.check_every + 4;
-      e = run_batch_phase(br, cfg, slots, o.check_every, ref_chunks, stream, dev_status, bp->status,
+      e = run_batch_phase(br, cfg, named, slots, o.check_every, ref_chunks, stream, dev_status, bp->status,
                           bp->status_dev, evs, ev0,
                           t_unused.data(), nullptr);
       if (e) return e;
@@ -1805,7 +1808,7 @@ int npga_gradient_batched(const npga_factor *f, const float *X, int64_t ldx, int
   npga_options o;
   npga_default_options(&o);
   const npga::BatchConfig &cfg = batch_config_of(config, f->n, f->cols, m);
-  npga::BatchArgs b = carve_batch(f, lay, ws, m, cfg);
+  npga::BatchArgs b = carve_batch(f, lay, ws, m, cfg, config >= 0);
   b.base.mode = npga::kTailGrad;
   b.base.gbuf0 = G;
   b.base.gbuf1 = nullptr;
@@ -1836,7 +1839,7 @@ int npga_batched_tune(const npga_factor *f, int32_t m, int32_t reps, int32_t *be
   HIPCHK(events.make(&z, false));
   {
     const npga::BatchConfig &c0 = npga::kBatchConfigTable[0];
-    npga::BatchArgs b0 = carve_batch(f, lay, ws, m, c0);
+    npga::BatchArgs b0 = carve_batch(f, lay, ws, m, c0, true);
     LAUNCHCHK(batch_prepare_b16(b0, lay, stream));
     LAUNCHCHK(npga::launch_bset_x0(b0, nullptr, 0, stream));  // zero GEMM input
     LAUNCHCHK(npga::launch_bact_all(b0, const_cast<int32_t *>(b0.act), const_cast<int32_t *>(b0.mact), stream));
@@ -1845,7 +1848,7 @@ int npga_batched_tune(const npga_factor *f, int32_t m, int32_t reps, int32_t *be
   int32_t best_id = 0;
   for (int c = 0; c < npga::kBatchConfigs; ++c) {
     const npga::BatchConfig &cfg = npga::kBatchConfigTable[c];
-    npga::BatchArgs b = carve_batch(f, lay, ws, m, cfg);
+    npga::BatchArgs b = carve_batch(f, lay, ws, m, cfg, true);
     LAUNCHCHK(npga::launch_bgemm(b, cfg, stream));  // warm-up
     HIPCHK(hipEventRecord(a, stream));
     for (int r = 0; r < reps; ++r) LAUNCHCHK(npga::launch_bgemm(b, cfg, stream));
