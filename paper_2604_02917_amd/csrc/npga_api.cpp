@@ -79,6 +79,20 @@ bool read_status(const int32_t *word, int32_t *out) {
   return v != kStatusUnset;
 }
 
+// The same for a float64 word: unset is a NaN that no arithmetic produces.
+constexpr uint64_t kDoubleUnset = 0xFFFFDEAD5EAF0001ull;
+
+void unset_double(double *word) { *reinterpret_cast<volatile uint64_t *>(word) = kDoubleUnset; }
+
+bool double_stored(const double *word) {
+  const volatile uint64_t *w = reinterpret_cast<const volatile uint64_t *>(word);
+  if (*w != kDoubleUnset) return true;
+  const auto t0 = std::chrono::steady_clock::now();
+  while (*w == kDoubleUnset && std::chrono::steady_clock::now() - t0 < std::chrono::milliseconds(1)) {
+  }
+  return *w != kDoubleUnset;
+}
+
 #define HIPCHK(expr)                                   \
   do {                                                 \
     if ((expr) != hipSuccess) return NPGA_ERR_HIP;     \
@@ -864,16 +878,24 @@ int npga_project(const double *v, const double *mu, int64_t n, double r, double 
   if (!ws || !aligned(ws, 256) || ws_bytes < lay.total) return NPGA_ERR_WORKSPACE;
   DevState *pin = pinned_status();
   if (!pin) return NPGA_ERR_HIP;
+  // the launch stores the outcome's words in no order, so each is unset first
+  const double *words[] = {&pin[3].n_nonfinite, &pin[3].mu_max, &pin[3].nu, &pin[3].tau};
+  for (const double *w : words) unset_double(const_cast<double *>(w));
+  pin[3].proj_flags = kStatusUnset;
   LAUNCHCHK(npga::launch_project_only(v, mu, n, r, o.proj_tol, x,
                                       reinterpret_cast<DevState *>(pinned_dev(pin, &pin[3].done)), lay.slots, stream));
   HIPCHK(hipStreamSynchronize(stream));
+  if (!double_stored(words[0]) || !double_stored(words[1])) return NPGA_ERR_HIP;
   if (pin[3].n_nonfinite > 0) return NPGA_ERR_NUMERIC;
   if (r > pin[3].mu_max) return NPGA_ERR_INFEASIBLE;
+  int32_t flags = 0;
+  if (!read_status(&pin[3].proj_flags, &flags) || !double_stored(words[2]) || !double_stored(words[3]))
+    return NPGA_ERR_HIP;
   if (nu_tau) {
     nu_tau[0] = pin[3].nu;
     nu_tau[1] = pin[3].tau;
   }
-  if (pin[3].proj_flags & 2) return NPGA_ERR_BRACKET;
+  if (flags & 2) return NPGA_ERR_BRACKET;
   return NPGA_OK;
 }
 
