@@ -274,7 +274,7 @@ size_t npga_solve_workspace_size(int64_t n, int64_t cols, const npga_options *op
 int npga_auto_path(int64_t n, int64_t cols, int32_t dtype);
 
 /* For up to 2048 assets npga_solve may run a whole phase (step-size
- * estimate, iterations, refinement round) as one launch of up to 32
+ * estimate, iterations, refinement round) as one launch of up to 64
  * workgroups that wait for each other's gradient pieces.  The waits are
  * bounded: when one lasts longer than `us` microseconds (default 50000; other
  * work may keep some of the workgroups from starting) the launch ends and

@@ -279,8 +279,8 @@ size_t loop_bytes(int64_t n, int64_t cols, int path);  // exchange words of the 
 int sweep_grid_for(int64_t cols);
 
 // A phase of a small solve in one launch (npga_loop.hip).
-constexpr int kLoopMaxGroups = 32;
-constexpr int64_t kLoopMaxBytes = 512 << 10;  // streamed and exchanged per workgroup and iteration
+constexpr int kLoopMaxGroups = 64;
+constexpr int kLoopMaxPieces = 32;  // workgroups of the factor path, which read each other's vectors
 struct LoopArgs {
   const void *mat;          // Sigma (leading dim ld) or the factor L
   int64_t ld;

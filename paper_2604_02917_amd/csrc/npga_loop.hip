@@ -184,7 +184,7 @@ __global__ __launch_bounds__(256, 1) void k_loop(SolveArgs m, LoopArgs la) {
   __shared__ __attribute__((aligned(32))) double comb[KIND == kLoopSymv ? 4 : CW * NP];
   __shared__ f4 slab_lds[KIND == kLoopSymv ? 1 : 4 * R * E * 64];
   __shared__ float dsh[KIND == kLoopSymv ? NP : 1];
-  __shared__ double redbuf[red_buf_doubles<4>()], mbuf[8], ush[4 + kLoopMaxGroups];
+  __shared__ double redbuf[red_buf_doubles<4>()], mbuf[8], ush[4 + kLoopMaxPieces];
   __shared__ int64_t ibuf[8];
   if (m.st->done != kRunning) {  // (nobody changes it before the first exchange)
     // the phase was over before it began (an estimate that overflowed, a start
@@ -588,18 +588,30 @@ __global__ __launch_bounds__(256) void k_loop_unset(unsigned long long *p, int64
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < words; i += (int64_t)gridDim.x * 256) p[i] = kLoopUnset;
 }
 
+// Columns of L up to which a step of the loop takes no longer than one by
+// launches, for the entries a thread has.  A step by launches takes 13 to 14
+// us whatever the shape (17 on a host that launches more slowly), the loop's
+// grows with the columns of a wavefront.  Measured, us a step, float32 /
+// bfloat16: n = 256 12.7 / 13.4 at 8000 columns, 14.6 / 15.4 at 10000; n = 512
+// 12.7 / 13.1 at 4000, 14.3 / 15.0 at 5000; n = 1000 12.6 / 14.5 at 1000 (17 by
+// launches there), 13.7 / 16.8 at 1200, 14.8 / 19.1 at 2000.
+constexpr int64_t kLoopMaxCols(int E) { return E == 1 ? 8192 : E == 2 ? 4096 : 1024; }
+
 // Workgroups of the loop for a shape (0: the launch-per-step path).  One
 // workgroup when it holds all the items (its products then take about the
-// time of an exchange).  Beyond, eight rows of Sigma a wavefront; on the
-// factor path, where every workgroup reads all the others' n-vectors, as
-// many as balance that against the columns a workgroup works through, or as
-// hold all the columns (n = 1001, T = 403: 14 workgroups 10.0 ms a solve, 16
-// the same, 12 and 10 10.4, 8 10.8).
+// time of an exchange).  Beyond, eight rows of Sigma a wavefront (n = 2000:
+// 10.1 us a step by 63 workgroups, 13.2 by 32, 12.6 by launches; n = 1000: 5.8
+// by 32, 9.6 by 16); on the factor path, where every workgroup reads all the
+// others' n-vectors, as many as balance that against the columns a workgroup
+// works through, or as hold all the columns (n = 1001, T = 403: 14 workgroups
+// 10.0 ms a solve, 16 the same, 12 and 10 10.4, 8 10.8), and at most
+// kLoopMaxPieces (n = 300, T = 4000: 12.7 us a step by 32, 12.5 by 45, 17.6 by
+// 16).
 LoopPlan loop_plan(int64_t n, int64_t cols, int path, int dtype) {
   LoopPlan p{};
   const int e = slots_for(n);
   const bool symv = path == NPGA_PATH_SYRK;
-  if (e < 1 || e > (symv ? 8 : 4)) return p;
+  if (e < 1 || e > (symv ? 8 : 4) || (!symv && cols > kLoopMaxCols(e))) return p;
   const int64_t items = symv ? n : cols;
   const int64_t esz = dtype == NPGA_BF16 ? 2 : 4;
   const int64_t held = 4 * loop_resident(e, symv);
@@ -607,14 +619,8 @@ LoopPlan loop_plan(int64_t n, int64_t cols, int path, int dtype) {
   if (items > held) {
     const int64_t balance = std::lround(std::sqrt((double)(cols * esz) / 8.0));
     w = symv ? (items + 31) / 32 : std::max<int64_t>(2, std::min<int64_t>((items + held - 1) / held, balance));
-    w = std::min<int64_t>(w, kLoopMaxGroups);
+    w = std::min<int64_t>(w, symv ? kLoopMaxGroups : kLoopMaxPieces);
   }
-  // bytes a compute unit moves per iteration (64 a cycle): streamed items
-  // and the other workgroups' pieces
-  const int64_t resident = w * held;
-  const int64_t streamed = std::max<int64_t>(0, items - resident) * n * esz / w;
-  const int64_t pieces = w == 1 ? 0 : (symv ? 8 * n : 8 * n * w);
-  if (streamed + pieces > kLoopMaxBytes) return p;
   p.groups = (int)w;
   p.half = w == 1 ? 0 : (symv ? (int64_t)256 * e : (3 * w * kLoopPiece(e) + 1) / 2);
   return p;
@@ -645,7 +651,7 @@ static void launch_loop_kind(const SolveArgs &a, const LoopArgs &la, int groups,
 }
 
 int launch_loop(const SolveArgs &a, const LoopArgs &la, int groups, int slots, int path, hipStream_t s) {
-  if (groups < 1 || groups > kLoopMaxGroups || a.dykstra || a.backtrack || a.pre_y ||
+  if (groups < 1 || groups > (path == NPGA_PATH_SYRK ? kLoopMaxGroups : kLoopMaxPieces) || a.dykstra || a.backtrack || a.pre_y ||
       (a.mode != kTailNpga && a.mode != kTailCG && a.mode != kTailPdas && a.mode != kTailLanczos))
     return (int)hipErrorInvalidValue;
   if (path != NPGA_PATH_SYRK && groups > 1)
