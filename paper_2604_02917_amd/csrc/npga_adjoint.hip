@@ -123,6 +123,10 @@ __global__ __launch_bounds__(256) void k_adj_init(SolveArgs a, const double *rhs
       a.gvec[i] = q[j];
       a.pvec[i] = p[j];
       a.xs[i] = (float)p[j];
+    } else {
+      // the sweeps read the padding too (against zeros of L); nothing before
+      // this has written it, and later writers store the first n entries
+      a.xs[i] = 0.0f;
     }
   }
   if (tid == 0) {
