@@ -20,12 +20,12 @@
 //     where every workgroup reads all the others' vectors, a word is all
 //     data, and a word that no arithmetic produces stands for one that has
 //     not arrived (fewer words than with a number in each, and one round of
-//     looks for 16 workgroups).
+//     looks for 14 to 16 workgroups).
 // Bound by latency: the exchange, the tail's reductions and a barrier or two.
 // Per NPGA step, a launch per step and one launch: n = 64 on Sigma 12 and 3.8
 // us, n = 501 on Sigma 11 and 4.9 us (16 workgroups), n = 1001, T = 403 on L
-// 19 and 10.3 us (14 workgroups; CG 11.3); whole solves 3.4 -> 1.3 ms, 4.6 -> 2.05 ms,
-// 15.2 -> 10.0 ms.  (Waiting before the first look at the others' words, which
+// 19 and 10.0 us (14 workgroups; CG 11.0); whole solves 3.4 -> 1.25 ms, 4.6 -> 2.0
+// ms, 15.2 -> 9.65 ms.  (Waiting before the first look at the others' words, which
 // halves a column of the tridiagonalisation, gains nothing here: 1 % at n =
 // 501, and a loss on L, where the looks are many and spread.)
 // With one workgroup there is no exchange.  Every wait is bounded: after
@@ -64,7 +64,7 @@ constexpr int loop_resident(int E, bool symv) { return symv ? 32 / E : (E == 1 ?
 // bits in all).  Error of L L^T x against float64, relative, n = 1001, T =
 // 403 / n = 300, T = 1400: the launches 2.0e-8 / 0.9e-8, float32 sums and
 // pieces 2.4e-8 / 1.4e-8, float32 pieces alone 2.0e-8 / 0.94e-8, so 1.8e-8 /
-// 0.8e-8.  At n = 1001, T = 403 the solve takes 8.9, 9.4 and 10.0 ms.
+// 0.8e-8.  At n = 1001, T = 403 the solve takes 8.9, 9.4 and 9.65 ms.
 constexpr int kLoopWords(int E) { return E <= 2 ? E : 3; }
 constexpr int kLoopPiece(int E) { return 256 * kLoopWords(E) + 8; }
 constexpr unsigned long long kLoopUnset = 0xFFFFDEAD5EAF0001ull;  // (no arithmetic produces these NaN)
@@ -489,16 +489,27 @@ __global__ __launch_bounds__(256, 1) void k_loop(SolveArgs m, LoopArgs la) {
             }
           }
         };
-        for (int w0 = 0; w0 < W && !bad; w0 += 16) {
+        // (16 pieces with remainders in flight cost register copies: n = 1001,
+        // 14 workgroups, 10.0 ms a solve by rounds of 16, 12, 8 and 4, 9.65 so)
+        constexpr int GM = E > 2 ? 14 : 16;
+        for (int w0 = 0; w0 < W && !bad; w0 += GM) {
           const int left = W - w0;
-          if (left > 12)
-            pieces(std::integral_constant<int, 16>{}, w0);
-          else if (left > 8)
+          if (left > 14)
+            pieces(std::integral_constant<int, GM>{}, w0);
+          else if (left > 12)
+            pieces(std::integral_constant<int, 14>{}, w0);
+          else if (left > 10)
             pieces(std::integral_constant<int, 12>{}, w0);
-          else if (left > 4)
+          else if (left > 8)
+            pieces(std::integral_constant<int, 10>{}, w0);
+          else if (left > 6)
             pieces(std::integral_constant<int, 8>{}, w0);
-          else
+          else if (left > 4)
+            pieces(std::integral_constant<int, 6>{}, w0);
+          else if (left > 2)
             pieces(std::integral_constant<int, 4>{}, w0);
+          else
+            pieces(std::integral_constant<int, 2>{}, w0);
         }
         if constexpr (E > 2) {
 #pragma unroll
@@ -592,9 +603,9 @@ __global__ __launch_bounds__(256) void k_loop_unset(unsigned long long *p, int64
 // launches, for the entries a thread has.  A step by launches takes 13 to 14
 // us whatever the shape (17 on a host that launches more slowly), the loop's
 // grows with the columns of a wavefront.  Measured, us a step, float32 /
-// bfloat16: n = 256 12.7 / 13.4 at 8000 columns, 14.6 / 15.4 at 10000; n = 512
-// 12.7 / 13.1 at 4000, 14.3 / 15.0 at 5000; n = 1000 12.6 / 14.5 at 1000 (17 by
-// launches there), 13.7 / 16.8 at 1200, 14.8 / 19.1 at 2000.
+// bfloat16: n = 256 12.8 / 13.3 at 8000 columns, 14.7 / 15.3 at 10000; n = 512
+// 12.8 / 13.2 at 4000, 14.4 / 15.0 at 5000; n = 1000 12.4 / 15.0 at 1000 (17 by
+// launches there), 13.7 / 16.5 at 1200, 15.4 / 18.6 at 2000.
 constexpr int64_t kLoopMaxCols(int E) { return E == 1 ? 8192 : E == 2 ? 4096 : 1024; }
 
 // Workgroups of the loop for a shape (0: the launch-per-step path).  One
@@ -604,7 +615,7 @@ constexpr int64_t kLoopMaxCols(int E) { return E == 1 ? 8192 : E == 2 ? 4096 : 1
 // by 32, 9.6 by 16); on the factor path, where every workgroup reads all the
 // others' n-vectors, as many as balance that against the columns a workgroup
 // works through, or as hold all the columns (n = 1001, T = 403: 14 workgroups
-// 10.0 ms a solve, 16 the same, 12 and 10 10.4, 8 10.8), and at most
+// 9.65 ms a solve, 16 10.7, 12 10.4, 10 10.0, 8 10.9), and at most
 // kLoopMaxPieces (n = 300, T = 4000: 12.7 us a step by 32, 12.5 by 45, 17.6 by
 // 16).
 LoopPlan loop_plan(int64_t n, int64_t cols, int path, int dtype) {
