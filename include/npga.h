@@ -366,9 +366,12 @@ int npga_syrk_split(const float *L, int64_t n, int64_t T, int64_t ld, float *Sig
  *   Leff    device n x ell float32 output (ldle >= n, multiple of 4)
  *   sigma   device ell float32 output: leading singular values of Y
  *   gamma_out (host) receives gamma
- *   ws      npga_sketch_workspace_size(n, T, k, ell) bytes (it includes the
+ *   ws      npga_sketch_workspace_size(n, T, k, ell) bytes.  They include one
+ *           buffer for the larger of two uses that follow each other: the
  *           three bfloat16 planes of L and S, 6 (ceil128(n) + ceil128(k))
- *           ceil64(T) bytes, and up to 96 MiB of partial tiles)
+ *           ceil64(T) bytes, with up to 96 MiB of partial tiles (Gaussian
+ *           sketch), and the tridiagonalisation's exchange slots (both
+ *           sketches: 10 MB at k = 600, 67 MB at 2048, 357 MB from 4096)
  * Requires 1 <= ell <= k <= 8192.  Y = L S runs on the bfloat16 matrix
  * cores with three-plane operands (the six plane products of weight
  * >= 2^-24 per entry product; float32 accumulation, float64 every 256

@@ -351,11 +351,12 @@ __device__ __forceinline__ void mm16_store(const Mm16 &m, int bi, int bj, int wr
 // instructions, 384 of LDS reads, 384 of loads at 64 bytes a cycle.  With
 // everything but the matrix instructions taken out the loads and LDS reads
 // took 4.6 ms at n = 5440, T = 48384, the matrix instructions alone 4.2, the
-// kernel 6.5 (1.32 PFLOP/s of plane products; issuing a stage's six loads
-// in one go instead of between the products: 7.1).  Before, with eight
+// kernel 6.5 (1.32 PFLOP/s of plane products) called again and again, 7.4 to
+// 7.8 in the trace of a training step (issuing a stage's six loads in one go
+// instead of between the products: 7.1 and not 6.5).  Before, with eight
 // wavefronts of 32 x 64, register staging and padded LDS rows: 11.1 ms at
-// that size (n = 4000, T = 16000: 2.74 ms, now 1.37; n = 501, T = 2003:
-// 103 us, now 17 and the join's 11).
+// that size (planes and product together, n = 4000, T = 16000: 2.74 ms, now
+// 1.32; n = 501, T = 2003: 103 us for the product, now 15 and the join's 12).
 template <bool SYM>
 __global__ __launch_bounds__(256, 1) void k_mm16(Mm16 m) {
   __shared__ __attribute__((aligned(16))) uint16_t ring[kMmRing * 2 * kPanelStage];

@@ -4,8 +4,11 @@
 // reflector before it, so the columns are a serial chain; with a launch per
 // stage of a step (npga_sketch.hip) a column costs a read and a write of the
 // trailing matrix and three launches.  Here up to 256 workgroups hold the
-// last kTriMax columns' trailing matrix in registers, whole rows (both
-// triangles) dealt out cyclically, and run the whole chain in one launch:
+// last kTriMax columns' trailing matrix, whole rows (both triangles) dealt out
+// cyclically: in registers up to order 2048, five rows of a workgroup's
+// fourteen in LDS up to 3584, two rows more and the first columns in memory up
+// to 4096.  The chain of an order is one launch, which goes on in a launch of
+// the next smaller kind when what is left fits that:
 //
 //   step i: every workgroup has p = tau_{i-1} A v_{i-1} and row i of the
 //   matrix, both before the rank-2 update of step i - 1.  Each one forms w =
@@ -20,7 +23,10 @@
 // Entries are stored and read at device scope.  Every wait is bounded: a
 // workgroup whose wait runs out raises the abort word and all leave; the
 // upper triangle (or what the launch before left) still holds the trailing
-// matrix, and the caller goes on with a launch per stage.
+// matrix, and the caller goes on with a launch per stage.  A stream whose
+// compute units do not hold a launch's workgroups together takes those
+// launches at once (tri_chip_fits), and the streams of a process take turns
+// (ChipTurn).
 //
 // The operations are those of npga_sketch.hip, all in float64.  Bound by a
 // step's latency: the exchange (about 1.2 us) and three sums over the
